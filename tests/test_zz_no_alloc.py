@@ -2,6 +2,8 @@
 (hf_column_stats_noalloc, counters in a static device array of the library)
 against the context-based entry point, bit for bit, on two calls in a row, the
 second on a smaller vector."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -27,6 +29,7 @@ def test_noalloc_entry_point_matches_context_entry_point_twice():
     ctx = hf.Context(model, 4, 0, "f32")
     for n, seed, n_bins in ((3_000_017, 1, 50), (40_001, 2, 256)):   # the second call on a smaller vector
         h = torch.from_numpy(_vec(n, seed)).cuda()
+        gc.collect()   # tensors that earlier tests left in reference cycles must not be freed inside the measured call
         before = torch.cuda.memory_allocated()
         below, mx, hist = hf.hf_column_stats_noalloc(h, n, THRESHOLDS, n_bins)
         assert torch.cuda.memory_allocated() == before
