@@ -97,8 +97,11 @@ int64_t round_up(int64_t a, int64_t b) { return (a + b - 1) / b * b; }
 // Pinned host memory for the few scalars a context reads back.  Pinning takes 0.15 ms, which every new context
 // would pay in its first call, so 64 slots of one 160 KB block serve the contexts alive at a time (taken and given back
 // under a lock; the block stays until the process ends) and contexts beyond those pin their own.
+// Coherent: kernels store results here and the host reads them after no more than an event (run_small), which for
+// memory without that flag promises nothing.
 namespace {
 constexpr int HOST_SLOTS = 64, HOST_SLOT_DOUBLES = 320;
+constexpr unsigned HOST_FLAGS = hipHostMallocPortable | hipHostMallocCoherent;
 static_assert(LZ_AHEAD * S_COUNT + 3 + CS_STATS_WORDS <= HOST_SLOT_DOUBLES, "slot size");
 std::mutex g_slots_mu;
 double* g_slots = nullptr;
@@ -108,7 +111,7 @@ hipError_t take_host_slot(double** out, int* slot) {
   {
     std::lock_guard<std::mutex> lk(g_slots_mu);
     if (!g_slots) {
-      const hipError_t e = hipHostMalloc((void**)&g_slots, HOST_SLOTS * HOST_SLOT_DOUBLES * sizeof(double), hipHostMallocPortable);
+      const hipError_t e = hipHostMalloc((void**)&g_slots, HOST_SLOTS * HOST_SLOT_DOUBLES * sizeof(double), HOST_FLAGS);
       if (e != hipSuccess) { g_slots = nullptr; return e; }
     }
     for (int i = 0; i < HOST_SLOTS; ++i)
@@ -120,7 +123,7 @@ hipError_t take_host_slot(double** out, int* slot) {
       }
   }
   *slot = -1;
-  return hipHostMalloc((void**)out, HOST_SLOT_DOUBLES * sizeof(double), hipHostMallocPortable);
+  return hipHostMalloc((void**)out, HOST_SLOT_DOUBLES * sizeof(double), HOST_FLAGS);
 }
 }  // namespace
 
