@@ -111,6 +111,7 @@ struct hf_ctx {
   // q_k and q_{k-1} themselves (cur_q / prev_q) and lz_vec holds only r and, once the basis is
   // full, the last q; otherwise lz_vec rotates q, q_prev and r.
   float* lz_vec[3] = {nullptr, nullptr, nullptr};
+  float* lz_hq = nullptr;  // short vectors: the products of a run that the host enqueues ahead, so that r stays the last iteration's
   int iq = 0, iqp = 1, ir = 2;
   void* basis = nullptr;
   // bf16 copies of the rows of an fp32 basis, kept by contexts with bf16 parameters: row k is the
@@ -152,8 +153,8 @@ struct hf_ctx {
   // iterations finished.  HF_EBREAKDOWN as lanczos_update.
   int run_small(const void* params, const void* inputs, const int32_t* labels, int batch, int seq, int m, double tol, double* alpha,
                 double* beta, int* done, hipStream_t st);
-  // the small update of iteration lz_k into slot `host`; hipErrorNotSupported: vectors too long
-  hipError_t enqueue_small_update(float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st);
+  // the small update of iteration lz_k (hq = H q_k, the residual into r) into slot `host`; hipErrorNotSupported: vectors too long
+  hipError_t enqueue_small_update(const float* hq, float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st);
   // what a finished iteration k with norm bt leaves: true if the run goes on
   bool advance(int k, double bt, double tol);
   int flag_error(const double* host);

@@ -234,6 +234,7 @@ int hf_ctx::plan_and_alloc() {
   // Lanczos
   if (max_m > 0) {
     for (int i = 0; i < 3; ++i) pl.add(lz_vec[i], n * 4);
+    if (lz_small(n, 0)) pl.add(lz_hq, n * 4);
     ldq = round_up(n, 64);
     if (desc.basis_dtype != HF_NONE) pl.add(basis, (int64_t)max_m * ldq * (desc.basis_dtype == HF_BF16 ? 2 : 4));
     if (desc.basis_dtype == HF_F32 && bf) pl.add(basis_bf, (int64_t)max_m * ldq * 2);
@@ -836,18 +837,18 @@ int hf_ctx::flag_error(const double* host) {  // the product's input checks; q_{
   return HF_OK;
 }
 
-hipError_t hf_ctx::enqueue_small_update(float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st) {
+hipError_t hf_ctx::enqueue_small_update(const float* hq, float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st) {
   const int k = lz_k;
   if (lz_reorth == HF_REORTH_FULL) {
     if (!lz_rows_are_vectors() || !lz_small(n, k + 1)) return hipErrorNotSupported;
     float* row = k + 1 < max_m ? (float*)basis + (int64_t)(k + 1) * ldq : nullptr;
     bf16* vdst = !bf ? nullptr : ((basis_bf && row) ? basis_bf + (int64_t)(k + 1) * ldq : vb);
     next_vb = vdst;
-    return lz_small_full((const float*)basis, ldq, r, n, k + 1, row, row ? nullptr : lz_vec[iq], vdst, tol, hvp_flags, scal, host, chained, st);
+    return lz_small_full((const float*)basis, ldq, hq, r, n, k + 1, row, row ? nullptr : lz_vec[iq], vdst, tol, hvp_flags, scal, host, chained, st);
   }
   if (!lz_small(n, 0)) return hipErrorNotSupported;
   next_vb = bf ? vb : nullptr;
-  return lz_small_three(r, cur_q(), prev_q(), bf ? vb : nullptr, n, k > 0, lz_beta_prev, tol, hvp_flags, scal, host, chained, st);
+  return lz_small_three(hq, hq == r ? nullptr : r, cur_q(), prev_q(), bf ? vb : nullptr, n, k > 0, lz_beta_prev, tol, hvp_flags, scal, host, chained, st);
 }
 
 bool hf_ctx::advance(int k, double bt, double tol) {
@@ -870,7 +871,7 @@ int hf_ctx::lanczos_update(float* r, double tol, double* alpha_k, double* beta_k
   const bool rows = lz_rows_are_vectors();
   float* q = cur_q();
   float* qp = prev_q();
-  const hipError_t es = enqueue_small_update(r, tol, hvp_flags, host_scal, 0, st);  // scalars on the host included
+  const hipError_t es = enqueue_small_update(r, r, tol, hvp_flags, host_scal, 0, st);  // scalars on the host included
   if (es != hipErrorNotSupported) {
     CK(es);
   } else if (lz_reorth == HF_REORTH_FULL) {
@@ -905,14 +906,14 @@ int hf_ctx::lanczos_update(float* r, double tol, double* alpha_k, double* beta_k
 }
 
 // A run whose iterations are a few kernels of microseconds each spends a third of its time between the host's wait and
-// its next launch.  Here the host enqueues iteration k before it has seen k - 1 and k - 2; the kernels chain the state on the
-// device and stop by themselves, so a breakdown or a bad input costs at most LZ_AHEAD - 1 products that change nothing.
+// its next launch.  Here the host enqueues iteration k before it has seen k - 1 and k - 2; the updates chain the state on the
+// device and stop by themselves.  After a breakdown or a bad input at most LZ_AHEAD - 1 products still run; they
+// write lz_hq only, so every vector of the run is what single steps would have left.
 int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* labels, int batch, int seq, int m, double tol,
                       double* alpha, double* beta, int* done, hipStream_t st) {
   hf_ctx* c = this;
   for (auto& ev : ahead_ev)
     if (!ev) CK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
-  float* r = lz_vec[ir];
   int k = 0, seen = 0;
   auto drop = [&](int to) {  // iterations to .. k-1 did not advance: undo the host's bookkeeping for them
     if (!lz_rows_are_vectors() && ((k - to) & 1)) std::swap(iq, iqp);
@@ -922,9 +923,9 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
   *done = 0;
   while (seen < m) {
     if (k < m && k - seen < LZ_AHEAD) {
-      int rc = hvp_enqueue(params, inputs, labels, batch, seq, cur_q(), r, st);
+      int rc = hvp_enqueue(params, inputs, labels, batch, seq, cur_q(), lz_hq, st);
       if (rc == HF_OK) {
-        hipError_t e = enqueue_small_update(r, tol, flags, host_scal + (k % LZ_AHEAD) * S_COUNT, 1, st);
+        hipError_t e = enqueue_small_update(lz_hq, lz_vec[ir], tol, flags, host_scal + (k % LZ_AHEAD) * S_COUNT, 1, st);
         if (e == hipSuccess) e = hipEventRecord(ahead_ev[k % LZ_AHEAD], st);
         if (e != hipSuccess) rc = fail(HF_EDEVICE, std::string("run_small: ") + hipGetErrorString(e));
       }
@@ -940,10 +941,10 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
     CK(hipEventSynchronize(ahead_ev[seen % LZ_AHEAD]));
     const double* h = host_scal + (seen % LZ_AHEAD) * S_COUNT;
     if (const int rc = flag_error(h); rc != HF_OK) { CK(hipStreamSynchronize(st)); drop(seen); return rc; }
-    alpha[seen] = h[S_ALPHA];
-    beta[seen] = h[S_BETA];
-    *done = ++seen;
     const double bt = h[S_BETA];
+    alpha[seen] = h[S_ALPHA];
+    beta[seen] = bt;
+    *done = ++seen;
     lz_beta_prev = bt;
     if (!(bt >= tol) || !(bt > 0.0)) {
       CK(hipStreamSynchronize(st));

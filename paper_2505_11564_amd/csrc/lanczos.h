@@ -49,12 +49,13 @@ hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, 
 // Vectors so short that one block does the whole update of an iteration (see lanczos.hip): full orthogonalisation against an
 // fp32 basis, and the three-term recurrence.  `host`: S_COUNT doubles of pinned host memory that also receive the scalars.
 // chained: return at once after an iteration that could not advance; the three-term kernel takes beta_{k-1} from scal.
+// hq / w = H q_k; the residual goes to r (may be hq), and without a basis, where it is never stored, w itself to keep if given.
 constexpr int LZ_AHEAD = 3;  // iterations of such a run the host may be ahead of
 constexpr int64_t LZ_SMALL_N = 8192, LZ_SMALL_WORK = 256 * 1024;
 bool lz_small(int64_t n, int64_t rows);
-hipError_t lz_small_full(const float* Q, int64_t ldq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
+hipError_t lz_small_full(const float* Q, int64_t ldq, const float* hq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
                          const int* flags, double* scal, double* host, int chained, hipStream_t st);
-hipError_t lz_small_three(const float* w, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
+hipError_t lz_small_three(const float* w, float* keep, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
                           const int* flags, double* scal, double* host, int chained, hipStream_t st);
 hipError_t lz_widen(const void* src, int is_bf16, float* dst, int64_t n, hipStream_t st);
 

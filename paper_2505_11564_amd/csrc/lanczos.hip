@@ -583,8 +583,8 @@ __device__ __forceinline__ void small_scalars(double* scal, double* host, double
 }
 
 // Full orthogonalisation against an fp32 basis of nq = k + 1 rows: the first Gram-Schmidt pass on w = H q_k itself, a
-// second one where it shrank the norm below 1/sqrt(2), q_{k+1} = r / beta_k into any of row, spill, vb.
-__global__ __launch_bounds__(1024) void lz_small_full_kernel(const float* __restrict__ Q, int64_t ldq, float* r, int n, int nq,
+// second one where it shrank the norm below 1/sqrt(2), q_{k+1} = r / beta_k into any of row, spill, vb.  r may be hq (= H q_k).
+__global__ __launch_bounds__(1024) void lz_small_full_kernel(const float* __restrict__ Q, int64_t ldq, const float* hq, float* r, int n, int nq,
                                                              float* row, float* spill, bf16* vb, double tol, const int* flags,
                                                              double* scal, double* host, int chained) {
   extern __shared__ double sm_c[];  // [nq + 1] coefficients, then w
@@ -592,7 +592,7 @@ __global__ __launch_bounds__(1024) void lz_small_full_kernel(const float* __rest
   __shared__ double red[16];
   const int t = threadIdx.x, wave = t >> 6;
   if (chained && scal[S_STOP] != 0.0) return;
-  for (int i = t; i < n; i += 1024) w[i] = r[i];
+  for (int i = t; i < n; i += 1024) w[i] = hq[i];
   __syncthreads();
   double alpha = 0.0, before = 0.0, beta = 0.0;
   for (int pass = 0; pass < 2; ++pass) {
@@ -632,9 +632,9 @@ __global__ __launch_bounds__(1024) void lz_small_full_kernel(const float* __rest
   if (t == 0) small_scalars(scal, host, alpha, beta, flags, ok, chained);
 }
 
-// Three-term recurrence: alpha_k, beta_k, and q_{k+1} over qp.
-__global__ __launch_bounds__(1024) void lz_small_three_kernel(const float* __restrict__ wv, const float* __restrict__ q, float* qp, bf16* vb,
-                                                              int n, int use_prev, float bprev, double tol, const int* flags,
+// Three-term recurrence: alpha_k, beta_k, and q_{k+1} over qp; keep (may be NULL) takes a copy of wv = H q_k.
+__global__ __launch_bounds__(1024) void lz_small_three_kernel(const float* __restrict__ wv, float* __restrict__ keep, const float* __restrict__ q,
+                                                              float* qp, bf16* vb, int n, int use_prev, float bprev, double tol, const int* flags,
                                                               double* scal, double* host, int chained) {
   extern __shared__ float sm_w[];
   __shared__ double red[16];
@@ -646,6 +646,7 @@ __global__ __launch_bounds__(1024) void lz_small_three_kernel(const float* __res
   double s = 0.0;
   for (int i = t; i < n; i += 1024) {
     float x = wv[i];
+    if (keep) keep[i] = x;
     if (use_prev) x = fmaf(-bprev, qp[i], x);
     sm_w[i] = x;
     s += (double)x * (double)q[i];
@@ -789,16 +790,16 @@ hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, 
 
 bool lz_small(int64_t n, int64_t rows) { return n <= LZ_SMALL_N && n * (rows + 2) <= LZ_SMALL_WORK; }
 
-hipError_t lz_small_full(const float* Q, int64_t ldq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
+hipError_t lz_small_full(const float* Q, int64_t ldq, const float* hq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
                          const int* flags, double* scal, double* host, int chained, hipStream_t st) {
   const size_t lds = (size_t)(nq + 1) * 8 + (size_t)n * 4;  // below 64 KB: n <= 8192, nq <= 2000
-  hipLaunchKernelGGL(lz_small_full_kernel, dim3(1), dim3(1024), lds, st, Q, ldq, r, (int)n, nq, row, spill, vb, tol, flags, scal, host, chained);
+  hipLaunchKernelGGL(lz_small_full_kernel, dim3(1), dim3(1024), lds, st, Q, ldq, hq, r, (int)n, nq, row, spill, vb, tol, flags, scal, host, chained);
   return hipGetLastError();
 }
 
-hipError_t lz_small_three(const float* w, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
+hipError_t lz_small_three(const float* w, float* keep, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
                           const int* flags, double* scal, double* host, int chained, hipStream_t st) {
-  hipLaunchKernelGGL(lz_small_three_kernel, dim3(1), dim3(1024), (size_t)n * 4, st, w, q, qp, vb, (int)n, use_prev, (float)beta_prev, tol,
+  hipLaunchKernelGGL(lz_small_three_kernel, dim3(1), dim3(1024), (size_t)n * 4, st, w, keep, q, qp, vb, (int)n, use_prev, (float)beta_prev, tol,
                      flags, scal, host, chained);
   return hipGetLastError();
 }
