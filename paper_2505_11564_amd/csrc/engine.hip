@@ -915,9 +915,11 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
   for (auto& ev : ahead_ev)
     if (!ev) CK(hipEventCreateWithFlags(&ev, hipEventDisableTiming));
   int k = 0, seen = 0;
+  double beta_seen = lz_beta_prev;  // of the last iteration that is known to have advanced
   auto drop = [&](int to) {  // iterations to .. k-1 did not advance: undo the host's bookkeeping for them
     if (!lz_rows_are_vectors() && ((k - to) & 1)) std::swap(iq, iqp);
     lz_k = to;
+    lz_beta_prev = beta_seen;
     vb_of = nullptr;
   };
   *done = 0;
@@ -945,7 +947,6 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
     alpha[seen] = h[S_ALPHA];
     beta[seen] = bt;
     *done = ++seen;
-    lz_beta_prev = bt;
     if (!(bt >= tol) || !(bt > 0.0)) {
       CK(hipStreamSynchronize(st));
       drop(seen - 1);
@@ -953,6 +954,8 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
       lz_done = 1;
       return HF_EBREAKDOWN;
     }
+    beta_seen = bt;
   }
+  lz_beta_prev = beta_seen;
   return HF_OK;
 }

@@ -79,20 +79,24 @@ def test_run_ahead_stops_at_a_breakdown_and_at_bad_labels(reorth, basis):
     res = ctx.hf_slq(pd, xd, yd, 256, 1, zd, 1, 10, reorth, tol=tol)
     assert res["status"] == hf.binding.HF_EBREAKDOWN and res["m_eff"][0] == expect + 1 == ctx.hf_lanczos_iterations()
     np.testing.assert_array_equal(res["alpha"][0][:expect + 1], free["alpha"][0][:expect + 1])
-    # the vectors left behind are those of single steps: products enqueued ahead of the breakdown change
+    # the vectors and the state left behind are those of single steps: products enqueued ahead of the breakdown change
     # nothing (with a basis q_k's row was not written, on either way)
     def left_behind():
         which = (1, 2) if reorth == "full" else (0, 1, 2)
         vecs = [torch.empty(ctx.n, device="cuda") for _ in which]
         for w, dst in zip(which, vecs):
             ctx.hf_lanczos_get_vector(w, dst)
-        return vecs
-    run_vecs = left_behind()
+        state = torch.zeros(ctx.hf_lanczos_state_bytes(), dtype=torch.uint8, device="cuda")
+        ctx.hf_lanczos_export(state, state.numel())
+        return vecs, state[:128].cpu()   # the header: iterations, end reached, beta_{k-1}
+    run_vecs, run_header = left_behind()
     ctx.hf_lanczos_init(zd, reorth)
     statuses = [ctx.hf_lanczos_step(pd, xd, yd, 256, 1, tol)[2] for _ in range(expect + 1)]
     assert statuses[:-1] == [hf.binding.HF_OK] * expect and statuses[-1] == hf.binding.HF_EBREAKDOWN
-    for a, b in zip(run_vecs, left_behind()):
+    step_vecs, step_header = left_behind()
+    for a, b in zip(run_vecs, step_vecs):
         assert torch.equal(a, b)
+    assert torch.equal(run_header, step_header)
     # two probes, the first of which breaks down: the second starts afresh
     z2 = torch.stack([zd, torch.from_numpy(si.make_probe(len(p), 2)).cuda()])
     both = ctx.hf_slq(pd, xd, yd, 256, 1, z2, 2, 10, reorth, tol=tol)
