@@ -39,9 +39,11 @@ struct LayerBuf {
   float* att_stat;
 };
 
-// mlp.hip: MLP products whose weights fit LDS run in one kernel that leaves at most MLP_BLOCKS partial results.
-constexpr int MLP_BLOCKS = 64, MLP_FUSED_MAX_BATCH = 16384;
+// mlp.hip: MLP products whose weights fit LDS run in one kernel of at most MLP_BLOCKS blocks, each of which leaves a
+// partial result.
+constexpr int MLP_BLOCKS = 256, MLP_FUSED_MAX_BATCH = 65536;
 bool mlp_fused_fits(const hf_model_desc& d);
+int mlp_blocks(int B);
 
 }  // namespace hf
 

@@ -155,8 +155,8 @@ int hf_ctx::plan_and_alloc() {
     pl.add(loss_rows, B * 4);
     if (bf) pl.add(xin, B * desc.mlp_in * e);
     if (mlp_fused_fits(desc)) {
-      pl.add(mlp_part, (int64_t)MLP_BLOCKS * n * 4);
-      pl.add(mlp_part_loss, MLP_BLOCKS * 8);
+      pl.add(mlp_part, mlp_blocks(max_batch) * n * 4);
+      pl.add(mlp_part_loss, mlp_blocks(max_batch) * 8);
     }
   } else {
     const int64_t S = desc.max_seq, B = max_batch, T = B * S, D = desc.d_model, F = desc.d_ff, H = desc.n_head;

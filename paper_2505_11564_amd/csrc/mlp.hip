@@ -6,6 +6,11 @@
 // leaves its share of H v (n floats) in the workspace; a second kernel adds the blocks' shares in a fixed order.
 // Measured at that shape: 13 + 4 us for the two, against 62 us of kernels in 15 launches (with the products of
 // gemm_f32.hip); an iteration of a run 33 us, 136 before.
+// Blocks: one per eight samples up to one per CU (the largest weights take a CU's LDS), then several turns each.  With at most
+// 64 blocks, whatever the batch, a large one lost to the chain of products.  hf_hvp, us (chain / 64 blocks / 256 blocks and the
+// sum spread over eight groups of lanes): 128-64-10 at 256 samples 97 / 55 / 54, 2048 138 / 134 / 62, 16384 451 / 839 / 250, 65536
+// 1553 / - / 917; 32-32-10 88 / 34 / 33, 124 / 58 / 34, 428 / 269 / 94, 1493 / - / 292; 100-70-31 118 / 64 / 62, 202 / 159 /
+// 68, 852 / 1029 / 297, 3093 / - / 1102.  Larger batches (MLP_FUSED_MAX_BATCH) have not been measured and take the chain.
 //   f = x W1 + b1, g = tanh f, z = g W2 + b2, p = softmax z, and along v:
 //   f_t = x W1_t + b1_t, g_t = g' f_t, z_t = g_t W2 + g W2_t + b2_t
 //   dz = (p - onehot) s, dz_t = p (z_t - <p, z_t>) s;  dg = dz W2^T, dg_t = dz_t W2^T + dz W2_t^T
@@ -204,29 +209,43 @@ __global__ __launch_bounds__(256) void mlp_hvp_kernel(MlpP p) {
   }
 }
 
-// H v = sum of the blocks' shares (+ what out holds); block 0 also the loss.
+// H v = sum of the blocks' shares (+ what out holds); block 0 also the loss.  A block takes 32 elements; its eight groups of
+// 32 lanes add every eighth share each and meet in LDS, always in the same order.
 __global__ __launch_bounds__(256) void mlp_sum_kernel(const float* __restrict__ part, const double* __restrict__ part_loss, int nblk,
                                                       int n, const int* __restrict__ flags, double weight, int accumulate,
                                                       float* __restrict__ out, double* __restrict__ loss, double* __restrict__ host) {
-  const int j = blockIdx.x * 256 + threadIdx.x;
+  __shared__ double red[8][32];
+  const int t = threadIdx.x, lane = t & 31, grp = t >> 5;
+  const int j = blockIdx.x * 32 + lane;
+  double s = 0.0;
   if (j < n) {
-    double s = accumulate ? (double)out[j] : 0.0;
 #pragma unroll 8
-    for (int b = 0; b < nblk; ++b) s += (double)part[(int64_t)b * n + j];
+    for (int b = grp; b < nblk; b += 8) s += (double)part[(int64_t)b * n + j];
+  }
+  red[grp][lane] = s;
+  __syncthreads();
+  if (grp == 0 && j < n) {
+    s = accumulate ? (double)out[j] : 0.0;
+#pragma unroll
+    for (int g = 0; g < 8; ++g) s += red[g][lane];
     out[j] = (float)s;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    double s = 0.0;
-    for (int b = 0; b < nblk; ++b) s += part_loss[b];
-    const double l = (accumulate ? loss[0] : 0.0) + weight * s / (double)max(1, flags[1]);
-    loss[0] = l;
-    host[0] = (double)flags[0]; host[1] = (double)flags[1]; host[2] = l;
+  if (blockIdx.x == 0 && t >= 64 && t < 128) {
+    double l = 0.0;
+    for (int b = t - 64; b < nblk; b += 64) l += part_loss[b];
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+    if (t == 64) {
+      l = (accumulate ? loss[0] : 0.0) + weight * l / (double)max(1, flags[1]);
+      loss[0] = l;
+      host[0] = (double)flags[0]; host[1] = (double)flags[1]; host[2] = l;
+    }
   }
 }
 
 int mlp_blocks(int B) { return std::min(MLP_BLOCKS, (B + MLP_ROWS - 1) / MLP_ROWS); }
 
-// 150 of the 160 KB of LDS; more samples than that are better spread over whole products.
+// 150 of the 160 KB of LDS.
 bool mlp_fused_fits(const hf_model_desc& d) {
   return d.param_dtype == HF_F32 && mlp_lds_floats(d.mlp_in, d.mlp_hidden, d.mlp_out) * 4 <= 150 * 1024;
 }
@@ -246,7 +265,7 @@ int hf_ctx::hvp_mlp_fused(const float* params, const float* inputs, const int32_
   hipError_t e = once.lds_limit((const void*)mlp_hvp_kernel, 150 * 1024);
   if (e == hipSuccess) {
     hipLaunchKernelGGL(mlp_hvp_kernel, dim3(nb), dim3(256), lds, st, p);
-    hipLaunchKernelGGL(mlp_sum_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st, mlp_part, mlp_part_loss, nb, (int)n, flags,
+    hipLaunchKernelGGL(mlp_sum_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, mlp_part, mlp_part_loss, nb, (int)n, flags,
                        (double)seed, acc_mode, out, loss_dev, host_hvp);
     e = hipGetLastError();
   }

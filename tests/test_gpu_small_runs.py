@@ -17,7 +17,8 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("sizes,batch", [((1, 1, 2), 1), ((13, 33, 65), 37), ((100, 70, 31), 1000), ((256, 30, 64), 520),
-                                         ((256, 256, 100), 64), ((7, 5, 3), 20000)])
+                                         ((256, 256, 100), 64), ((7, 5, 3), 20000), ((128, 64, 10), 2055), ((7, 5, 3), 65536),
+                                         ((7, 5, 3), 65537)])
 def test_mlp_product(sizes, batch):
     from gpu_util import gpu_hvp, rel_l2
     model = si._mlp(*sizes)
