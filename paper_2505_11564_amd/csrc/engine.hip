@@ -389,9 +389,10 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
   }
   if (accumulate) CK(launch_fill_f32((float*)(flags + 1), 1, 0.f, st));
   else CK(launch_fill_f32((float*)flags, 2, 0.f, st));
-  // Small models: every weight-gradient product of a layer splits k and adds into a cleared
-  // result, and the vectors between them are accumulated with atomics as well.  One pass over the
-  // layers' whole range then replaces a fill per matrix and per group of vectors.
+  // Small models: where every weight-gradient product of a layer, launched alone, would split k and add into a cleared
+  // result, the layers' whole range is cleared in one pass (the vectors between the matrices are accumulated with atomics as
+  // well), which replaces a fill per matrix and per group of vectors.  The grouped launch of a GPT layer may then still
+  // leave k whole and write every element itself; the pass over the matrices buys nothing there.
   dw_prezeroed = 0;
   if (!accumulate && bf && desc.arch != HF_ARCH_MLP && layers_end > layers_begin) {
     const int T = batch * seq, D = desc.d_model, F = desc.d_ff;
@@ -651,9 +652,10 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     const LayerOff& o = loff[l];
     // ---- MLP branch
     // GPT: the four weight-gradient products of a layer that do not fill the chip on their own are
-    // only described here and launched together once the last of their operands exists; the two norm adjoints of a layer then write their bf16 copies to
-    // different buffers, so that the first is still there when the group runs.  fp32 parameters: the
-    // norm adjoints work in place, so the products of a branch are launched together before its norm.
+    // only described here and launched together once the last of their operands exists; the two norm
+    // adjoints of a layer then write their bf16 copies to different buffers, so that the first is still
+    // there when the group runs.  fp32 parameters: the norm adjoints work in place, so the products of
+    // a branch are launched together before its norm.
     Gemm dw[4];
     int ndw = 0;
     const bool group_dw = !bf || (!llama && gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F) < GROUP_MAX_TILES256);

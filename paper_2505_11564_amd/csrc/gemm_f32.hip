@@ -361,10 +361,11 @@ static hipError_t launch_f32_cfg(const F32Group& gg, int grid, bool vec, hipStre
 struct F32Cfg { int bm, bn, bk; double slab_clk; };
 static const F32Cfg kF32Cfg[] = {{64, 64, 32, 930.}, {128, 64, 32, 1720.}, {32, 32, 64, 665.}};
 
-// Estimated clocks of a launch whose products have cnt[i] blocks of len[i] clocks, longest first.  Up to four blocks are
-// resident per CU, dealt to the CUs in turn, and their matrix pipes are busy 68, 79, 92 and 99 % of the time with one to
-// four of them: launches of up to four blocks per CU last as long as the fullest CU, others as long as
-// the average and about two blocks more.
+// Estimated clocks of a launch whose products have cnt[i] blocks of len[i] clocks, longest first.  Up to four blocks of the
+// two small tiles are resident per CU (35 and 37 KB of LDS each), dealt to the CUs in turn, and their matrix pipes are
+// busy 68, 79, 92 and 99 % of the time with one to four of them: launches of up to four blocks per CU last as
+// long as the fullest CU, others as long as the average and about two blocks more.  The 128 x 64 tile (53 to 55 KB) has room
+// for two or three: there the busy share of the last ones, and the limit of four, flatter it.
 static double f32_estimate(const int64_t* cnt, const double* len, int n) {
   static const double kBusy[] = {1., 0.68, 0.79, 0.92, 0.99};
   int64_t blocks = 0;
@@ -403,7 +404,8 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   int order[F32_GROUP_MAX];
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order, order + n, [&](int a, int b) { return (int64_t)ps[a].nterm * ps[a].K > (int64_t)ps[b].nterm * ps[b].K; });
-  // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  A cut costs each block
+  // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  (Under klimit the blocks
+  // are priced with the whole k, about twice their average: only the tile is chosen there, and all tiles are priced alike.)  A cut costs each block
   // about 2000 clocks (partial tile out; twice that with the twice as large tile) and the launch 8000 (arrivals, sums).
   // Measured (us; uncut 64 x 64, uncut 32 x 32, best and its tile / parts, chosen): primal product and tangent
   // 1024x768x768 45.8 46.5 41.7 64/2 41.7, 1024x2304x768 118 115 106 64/3 106, 1024x3072x768 135 149 135 64/1 137,

@@ -496,9 +496,19 @@ static void choose_tile_and_split(const GemmP& p, int nb, int allow_splitk, int 
   // (the pipeline fills sooner).
   const int64_t t256 = tiles(256, 256);
   const bool even256 = t256 >= 256 && t256 * 100 >= ((t256 + 255) / 256) * 256 * 85;
-  // A contraction so long (the head adjoint: k = vocabulary) that its parts outweigh the adds which join them keeps the
-  // large tile with one part per CU: 4096 x 768 x 50257, 240 blocks of 256 x 256 in five parts against 1536 of 128 x 128
-  // in eight, primal product and tangent together 943 against 1103 us.
+  // A contraction so long (the adjoint of a tied head: k = vocabulary) that its parts outweigh the adds which join them keeps
+  // the large tile with one part per CU: 4096 x 768 x 50257, 240 blocks of 256 x 256 in five parts against 1536 of 128 x 128
+  // in eight, primal product and tangent together 943 against 1103 us.  Slabs are counted over the terms, so the tangent (two)
+  // changes at k = 16384 and the primal product at 32768.  Whole products of one layer (us, 128 x 128 / this rule):
+  // rows x width  k = 12000  16391      24000      32000      33000      50257
+  // 4096 x 768    1576/1579  1884/1847  2367/2329  2805/2766  2983/2923  3948/3839
+  // 4096 x 640    1342/1340  1684/1674  2147/2133  2546/2492  2698/2683  3637/3528
+  // 3072 x 768    1279/1279  1505/1475  1871/1845  2202/2177  2357/2344  3110/3019
+  // 2048 x 1280   1401/1404  1741/1727  1949/1931  2370/2333  2565/2538  3307/3177
+  // 3333 x 768    1423/1419  1620/1624  2091/2082  2445/2437  2589/2613  3432/3409
+  // 2048 x 1600   1729/1730  2089/2104  2354/2375  2839/2832  3015/3070  3971/3932
+  // (below 16384 the two are the same code: 0.3 % apart).  2048 x 1600 loses up to 1.8 % below the longest k and gains 1 %
+  // there; padding is not what tells it apart (640 columns leave more of the 256-wide tiles empty, and gain).
   const bool long256 = allow_splitk && !p.out_bf16 && !p.klimit && p.nterm * (p.K / 64) >= 512 && t256 > 0 &&
                        t256 * (256 / t256) * 100 >= 256 * 85;
   int cfg;

@@ -181,7 +181,8 @@ __global__ __launch_bounds__(CS_THREADS) void colstats_hist_kernel(const float* 
   }
 }
 
-// Each block sees at most n / CS_BLOCKS + 4096 entries, so its 32-bit counters cannot overflow for n < 2^40.
+// Each block sees at most n / CS_BLOCKS + 4096 entries, so its 32-bit counters cannot overflow for n <= 2^40 - 2^20 (fourteen
+// times what 288 GB hold).
 static inline int colstats_blocks(int64_t n) { return (int)std::max<int64_t>(1, std::min<int64_t>(cdiv64(n, 4 * CS_THREADS), CS_BLOCKS)); }
 
 hipError_t launch_colstats_pass1(const float* h, int64_t n, const ColThresholds& thr, unsigned long long* stats, hipStream_t st) {
