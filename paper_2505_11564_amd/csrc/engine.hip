@@ -324,18 +324,6 @@ struct Lin {
     g.in_bf16 = bf; g.out_bf16 = out_bf16;
     scratch(g);
     g.A[0] = dY; g.B[0] = Wp(woff); g.C = dX; g.Cadd = add;
-    // Few output tiles and a long contraction (the head: K = vocabulary): two
-    // split-K products; otherwise one dual-output product.
-    const int64_t tiles = ((int64_t)(M + 127) / 128) * ((Kin + 127) / 128);
-    if (bf && !out_bf16 && tiles < 256 && Nout >= 8192 && (tiles * 2 > 256 || !c->gemm_ws)) {
-      g.allow_splitk = 1;
-      CK(launch_gemm(g, st));
-      Gemm t = g;
-      t.C = dX_t; t.Cadd = add_t;
-      t.A[0] = dY_t; t.B[0] = Wp(woff); t.A[1] = dY; t.B[1] = Wt(woff);
-      CK(launch_gemm(t, st));
-      return HF_OK;
-    }
     g.At = dY_t; g.Bt = Wt(woff); g.Ct = dX_t; g.Cadd_t = add_t;
     CK(launch_gemm(g, st));
     return HF_OK;

@@ -218,12 +218,11 @@ hipError_t launch_gemm(const Gemm& g, hipStream_t st) {
   // dual output: one fused launch when the MFMA path applies, else two products
   if (g.M <= 0 || g.N <= 0 || g.nb1 <= 0 || g.nb2 <= 0) return hipSuccess;
   if (!g.At || !g.Bt || !g.A[0] || !g.B[0] || !g.C || ((g.Cadd || g.Cadd_t) && g.out_bf16)) return hipErrorInvalidValue;
-  // Measured: the fused kernel wins only when the product alone cannot fill
-  // the GPU (fewer than ~256 tiles of 128 x 128); larger products run faster
-  // as two launches with their own tile shapes.
+  // Batched products (attention): the fused kernel wins only when the product alone cannot fill the GPU (fewer than ~256
+  // tiles of 128 x 128); larger ones run faster as two products one head wide.
   const int64_t tiles128 = ((int64_t)(g.M + 127) / 128) * ((g.N + 127) / 128) * g.nb1 * g.nb2;
   if (g.epi != EPI_NONE && !g.in_bf16) return hipErrorInvalidValue;
-  if (g.in_bf16 && g.M >= 8 && g.N >= 8 && (g.epi != EPI_NONE || tiles128 < 256)) {
+  if (g.in_bf16 && g.M >= 8 && g.N >= 8 && (g.epi != EPI_NONE || g.nb1 * g.nb2 == 1 || tiles128 < 256)) {
     auto ok = [&](const void* x, int64_t ld, int64_t s1, int64_t s2, int rows_contig, int R) {
       return ((uintptr_t)x % 16) == 0 && ld % 8 == 0 && s1 % 8 == 0 && s2 % 8 == 0 && (!rows_contig || ld >= ((R + 7) / 8) * 8);
     };
@@ -232,7 +231,7 @@ hipError_t launch_gemm(const Gemm& g, hipStream_t st) {
       if (g.A[i]) fast = ok(g.A[i], g.lda, g.sA1, g.sA2, g.transA, g.M) && ok(g.B[i], g.ldb, g.sB1, g.sB2, !g.transB, g.N);
     }
     if (fast) {
-      hipError_t e = launch_gemm_dual(g, st);
+      hipError_t e = g.epi != EPI_NONE ? launch_gemm_dual(g, st) : launch_gemm_linear(g, st);
       if (e != hipErrorNotSupported) return e;
     }
   }

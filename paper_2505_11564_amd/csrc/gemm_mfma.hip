@@ -35,8 +35,7 @@ namespace hf {
 // slab j's stage is free), multiplies that last k-step and the first k-steps of
 // slab j+1 while the loads of slab j+2 go to the freed stage.
 // 128x128 tiles with 32-deep slabs are compiled for three resident blocks per
-// CU (768 slots), which fits the 576- and 768-tile products of the small
-// models in one round; the other shapes take what registers they need.
+// CU (768 slots); the other shapes take what registers they need.
 constexpr int cmin(int a, int b) { return a < b ? a : b; }
 
 template <int BM, int BN, int KT, int NS>
@@ -496,28 +495,13 @@ static void choose_tile_and_split(const GemmP& p, int nb, int allow_splitk, int 
   // (the pipeline fills sooner).
   const int64_t t256 = tiles(256, 256);
   const bool even256 = t256 >= 256 && t256 * 100 >= ((t256 + 255) / 256) * 256 * 85;
-  // A contraction so long (the adjoint of a tied head: k = vocabulary) that its parts outweigh the adds which join them keeps
-  // the large tile with one part per CU: 4096 x 768 x 50257, 240 blocks of 256 x 256 in five parts against 1536 of 128 x 128
-  // in eight, primal product and tangent together 943 against 1103 us.  Slabs are counted over the terms, so the tangent (two)
-  // changes at k = 16384 and the primal product at 32768.  Whole products of one layer (us, 128 x 128 / this rule):
-  // rows x width  k = 12000  16391      24000      32000      33000      50257
-  // 4096 x 768    1576/1579  1884/1847  2367/2329  2805/2766  2983/2923  3948/3839
-  // 4096 x 640    1342/1340  1684/1674  2147/2133  2546/2492  2698/2683  3637/3528
-  // 3072 x 768    1279/1279  1505/1475  1871/1845  2202/2177  2357/2344  3110/3019
-  // 2048 x 1280   1401/1404  1741/1727  1949/1931  2370/2333  2565/2538  3307/3177
-  // 3333 x 768    1423/1419  1620/1624  2091/2082  2445/2437  2589/2613  3432/3409
-  // 2048 x 1600   1729/1730  2089/2104  2354/2375  2839/2832  3015/3070  3971/3932
-  // (below 16384 the two are the same code: 0.3 % apart).  2048 x 1600 loses up to 1.8 % below the longest k and gains 1 %
-  // there; padding is not what tells it apart (640 columns leave more of the 256-wide tiles empty, and gain).
-  const bool long256 = allow_splitk && !p.out_bf16 && !p.klimit && p.nterm * (p.K / 64) >= 512 && t256 > 0 &&
-                       t256 * (256 / t256) * 100 >= 256 * 85;
   int cfg;
   if (force_cfg >= 0 && force_cfg < kNumCfg) cfg = force_cfg;
   else if (!p.transB && N <= 64 && M >= 128) cfg = 4;
   else if (!p.transB && N <= 128 && N > 64 && p.klimit) cfg = 1;  // causal: 128-row tiles pair up heavy and light rows
   else if (!p.transB && N <= 128 && N > 64 && tiles(256, 128) >= 128) cfg = 3;
   else if (p.transA && !p.transB) cfg = t256 >= 160 ? 0 : 1;
-  else if (!p.transA && !p.transB) cfg = even256 || long256 ? 0 : (p.K >= 1536 ? 1 : 2);
+  else if (!p.transA && !p.transB) cfg = even256 ? 0 : (p.K >= 1536 ? 1 : 2);
   else cfg = even256 ? 0 : 1;
   const int bm = kCfg[cfg].bm, bn = kCfg[cfg].bn;
   const int64_t nt = tiles(bm, bn);
@@ -531,10 +515,9 @@ static void choose_tile_and_split(const GemmP& p, int nb, int allow_splitk, int 
     const int64_t slots = (bm == 256) ? 256 : 512;
     const int slabs = p.nterm * (p.K / 64);
     if (nt * 2 <= slots) ks = (int)std::min<int64_t>(std::min<int64_t>(slots / nt, std::max(1, slabs / 8)), 16);
-    // A very long k (the head adjoint: k = vocabulary, 1500 slabs) can afford more parts than
-    // are resident at once: take the smallest count whose blocks fill whole rounds of the slots
-    // (192 tiles x 8 = 3 x 512 instead of 384 of 512).  For shorter k the extra atomic passes
-    // over C cost more than the fuller rounds gain (measured on the weight-gradient products).
+    // A very long k (H v blocks over tens of thousands of tokens) can afford more parts than are resident at once: take the
+    // smallest count whose blocks fill whole rounds of the slots.  For shorter k the extra atomic passes over C cost more
+    // than the fuller rounds gain.
     auto full_rounds = [&](int k2) { const int64_t rem = (nt * k2) % slots; return rem == 0 || rem >= slots - slots / 16; };
     if (slabs >= 512 && !full_rounds(ks)) {
       for (int k2 = ks + 1; k2 <= 16; ++k2)
@@ -612,12 +595,9 @@ static hipError_t launch_pair_cfg(const GemmPair& pp, dim3 grid, hipStream_t st)
   return hipErrorNotSupported;
 }
 
-// A primal product and its tangent (same shape and layout) as one launch; blockIdx.z selects the
-// product.  Two cases:
-//  * not batched: 256 x 256 tiles, when the two together fill the 256 CUs evenly, in particular
-//    when one alone does not (4096 x 2048: 128 + 128 tiles).  The term counts may differ (adjoint 1, its
-//    tangent 2): the launch then lasts as long as the two-term blocks, still less than two
-//    launches of 128 x 128 tiles;
+// A primal product and its tangent (same shape and layout) as one launch; blockIdx.z selects the product.  Two cases:
+//  * not batched: 256 x 256 tiles, when the two together fill the 256 CUs evenly (products of so many tiles that the
+//    product-rule kernel, which is asked first, leaves them here);
 //  * batched causal products one attention head wide (P V and O_t, dS K and dQ_t, ...): the
 //    tiles a single launch would use; one launch instead of two short ones.
 // Returns hipErrorNotSupported otherwise; the caller then launches the two products in turn.
@@ -655,15 +635,7 @@ hipError_t launch_gemm_mfma_pair(GemmP a, GemmP b, int nb, hipStream_t st) {
     dim3 grid((unsigned)t256, 1, 2);
     return launch_pair_cfg<256, 256, 128, 128, 64, 2, 2>(pp, grid, st);
   }
-  // Products that take 128 x 128 tiles on their own (the small models' 576- and 768-tile
-  // products): the same tiles, one launch instead of two 40 us ones.
-  if (even(t256) || (a.transA && t256 >= 160) || a.N <= 128) return hipErrorNotSupported;
-  const int64_t t128 = ((int64_t)(a.M + 127) / 128) * ((a.N + 127) / 128);
-  if (t128 < 256 || t128 > 2048) return hipErrorNotSupported;
-  finish(128);
-  dim3 grid((unsigned)t128, 1, 2);
-  if (!a.transA && !a.transB && a.K < 1536) return launch_pair_cfg<128, 128, 64, 64, 32, 2, 2>(pp, grid, st);
-  return launch_pair_cfg<128, 128, 64, 64, 64, 2, 2>(pp, grid, st);
+  return hipErrorNotSupported;
 }
 
 template <int BM, int BN, int WM, int WN>
