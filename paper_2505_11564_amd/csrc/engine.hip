@@ -224,7 +224,7 @@ int hf_ctx::plan_and_alloc() {
   }
   if (bf) pl.add(vb, n * 2);
   if (desc.arch != HF_ARCH_MLP) {
-    gemm_ws_elems = bf ? GEMM_WS_ELEMS : GEMM_WS_ELEMS / 2;
+    gemm_ws_elems = GEMM_WS_ELEMS;
     pl.add(gemm_ws, gemm_ws_elems * 4);
     if (!bf) pl.add(gemm_cnt, F32_COUNTERS * 4);
   }

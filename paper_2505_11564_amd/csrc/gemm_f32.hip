@@ -3,31 +3,24 @@
 //
 //   C = alpha (A0 op B0 + A1 op B1 + A2 op B2) + bias + bias_t + Cadd        fp32 throughout
 //
-// What bounds it: the fp32 matrix pipe, 256 flops per clock and CU (157 TFLOP/s), a sixteenth of the
-// bf16 one, so operand delivery is never the limit (a 64 x 64 tile reads 128 B of operands per k for
-// 8192 flops, 13 % of what L2 delivers).  What costs time instead is a chip that is not full and a
-// wave that waits for its operands, and the design is about those two:
-//   * a launch takes up to four products (a primal product with its tangent, or the
-//     weight-gradient products of a layer), longest blocks first, so their tiles fill the CUs together;
-//   * k (over the slabs of all terms) is cut into parts where the tiles alone leave CUs idle.  Each
-//     block leaves its partial tile in the workspace and the last block of a tile to arrive adds the parts in
-//     their order, so the result does not depend on which one that was, and no second launch is needed;
+// The fp32 matrix pipe does 256 flops per clock and CU (157 TFLOP/s), a sixteenth of the bf16 one, so the larger tiles take their
+// operands apart into three bf16 numbers each and multiply those (gemm_f32_split_kernel below); products too small for
+// that to matter stay with the fp32 instructions (gemm_f32_mfma_kernel, 32 x 32 tiles), where the time goes into waits.  Both:
+//   * a launch takes up to four products (a primal product with its tangent, or the weight-gradient products of a layer), longest
+//     blocks first, so their tiles fill the CUs together;
 //   * operands are two slabs ahead in registers and one in LDS (two stages, one barrier per slab).
-// LDS layouts: a k-contiguous operand is kept [row][BK + 4], and a lane's 16-byte read holds four k of
-// its row; a row-contiguous one is kept [k][R + 8] and read one float at a time.  The k index of a
-// matrix instruction is free as long as both operands agree, so step j of a group of eight takes
-// k = j and k = 4 + j (lane halves), which is what the 16-byte reads deliver.  Both strides put the
-// lanes of a read on different banks.
-// Measured: 120 to 125 TFLOP/s from 16000 x 768 x 1024 on, 80 to 105 at 1024 tokens of a 768-wide model (a vector-FMA
-// kernel with 64 x 64 tiles before it: 13).
-#include "hf_internal.h"
-#include "gemm_params.h"
+// The split kernel also cuts k (over the slabs of all terms) into parts where the tiles alone leave CUs idle.  Each block leaves its
+// partial tile in the workspace and the last block of a tile to arrive adds the parts in their order, so the result does
+// not depend on which one that was, and no second launch is needed.
+// fp32 LDS layouts: a k-contiguous operand is kept [row][BK + 4], and a lane's 16-byte read holds four k of its row; a
+// row-contiguous one is kept [k][R + 8] and read one float at a time.  The k index of a matrix instruction is free as long as
+// both operands agree, so step j of a group of eight takes k = j and k = 4 + j (lane halves), which is what the 16-byte reads
+// deliver.  Both strides put the lanes of a read on different banks.
+#include "gemm_linear.h"
 
 #include <algorithm>
 
 namespace hf {
-
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 
 struct F32Group {
   GemmP g[F32_GROUP_MAX];
@@ -43,9 +36,9 @@ struct F32Group {
 };
 
 // One operand's slab of R rows x BK: R * BK / 1024 chunks of four elements per thread, along k (KC) or along the rows.
-template <int R, bool KC, int BK>
+template <int R, bool KC, int BK, int NTHR = 256>
 struct F32Tile {
-  static constexpr int NI = R * BK / 1024;
+  static constexpr int NI = R * BK / (4 * NTHR);
   static constexpr int LD = KC ? BK + 4 : R + 8;
   static constexpr int FLOATS = KC ? R * LD : BK * LD;
   static __device__ __forceinline__ int row(int c) { return KC ? c / (BK / 4) : (c % (R / 4)) * 4; }
@@ -57,7 +50,7 @@ struct F32Tile {
   static __device__ __forceinline__ void offsets(uint32_t (&o)[VEC ? NI : 4 * NI], int64_t ld, int r0, int rmax, int t) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int c = t + i * 256;
+      const int c = t + i * NTHR;
 #pragma unroll
       for (int q = 0; q < (VEC ? 1 : 4); ++q) {
         const int r = r0 + row(c) + (KC ? 0 : q), k = kk(c) + (KC ? q : 0);
@@ -78,7 +71,7 @@ struct F32Tile {
   static __device__ __forceinline__ void fetch_tail(float4 (&v)[NI], const float* X, int64_t ld, int r0, int rmax, int k0, int kend, int t) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int c = t + i * 256;
+      const int c = t + i * NTHR;
       float e[4];
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
@@ -92,7 +85,7 @@ struct F32Tile {
   static __device__ __forceinline__ void store(const float4 (&v)[NI], float* lds, int t) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
-      const int c = t + i * 256;
+      const int c = t + i * NTHR;
       *(float4*)(KC ? lds + row(c) * LD + kk(c) : lds + kk(c) * LD + row(c)) = v[i];
     }
   }
@@ -342,6 +335,390 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
   }
 }
 
+// ---- larger tiles: fp32 operands as three bf16 parts each ------------------------------------------------------------------
+// A float is the exact sum of three bf16 numbers x0 + x1 + x2 (8 significant bits each, each the rounding of what is left), so
+//   x y = x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) + ...
+// in exact bf16 products with fp32 accumulation; the terms left out (x1 y2, x2 y1, x2 y2) are below 2^-26 of |x y|, less than the
+// rounding of one fp32 addition.  Six bf16 matrix instructions take 3/8 of the time of the fp32 ones they replace.
+// What bounds it: a slab of 128 x 128 x 32 takes 1.3 us with all CUs busy (0.86 alone), of which its matrix instructions are 0.75
+// and the taking apart (88 vector instructions a wave, dealt out between them) 0.34: 195 TFLOP/s at 4096^3 (fp32 instructions 131),
+// 145 at 1024 x 3072 x 768 (94).  Relative error against 64 bits, fp32 instructions / this: k = 768 5.0e-7 / 3.1e-7, 3072 in parts
+// 4.5e-7 / 3.5e-7, 50257 1.8e-6 / 4.4e-7; operands over five decades 4.5e-7 / 2.6e-7, 4.0e-7 / 2.9e-7, 1.6e-6 / 4.1e-7.
+// An operand that is infinite, or rounds to infinity in bf16, makes every result that it takes part in a NaN here: blocks
+// that find one among their results compute them again with fp32 multiply-adds.
+struct F32Parts { uint2 p[3]; };
+__device__ __forceinline__ unsigned f32_round_pair(float a, float b) {
+  typedef float f32v2 __attribute__((ext_vector_type(2)));
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  unsigned u = __builtin_bit_cast(unsigned, __builtin_convertvector((f32v2){a, b}, bf16x2));
+  asm("" : "+v"(u));  // (the compiler would round again, one number at a time, where the parts are unpacked)
+  return u;
+}
+__device__ __forceinline__ F32Parts f32_split(const float4 v) {
+  float x = v.x, y = v.y, z = v.z, w = v.w;
+  F32Parts o;
+#pragma unroll
+  for (int q = 0; q < 3; ++q) {
+    o.p[q] = make_uint2(f32_round_pair(x, y), f32_round_pair(z, w));
+    if (q == 2) break;
+    x -= __uint_as_float(o.p[q].x << 16); y -= __uint_as_float(o.p[q].x & 0xffff0000u);
+    z -= __uint_as_float(o.p[q].y << 16); w -= __uint_as_float(o.p[q].y & 0xffff0000u);
+  }
+  return o;
+}
+
+// LDS: three planes of R x BK bf16 per operand and stage, in the layouts of the bf16 kernels (LinTile).
+template <int R, bool KC, int BK>
+struct SplitTile {
+  using L = LinTile<R, KC, BK>;
+  static constexpr int PLANE = R * BK;  // elements
+  // chunk of four elements number c of the slab: along k (KC) or along the rows
+  static __device__ __forceinline__ int at(int c) {
+    const int line = KC ? c / (BK / 4) : c / (R / 4), e = (KC ? c % (BK / 4) : c % (R / 4)) * 4;
+    return line * (L::CPL * 8) + L::swz(line, e >> 3) * 8 + (e & 4);
+  }
+};
+
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, bool VEC>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_kernel(F32Group gg) {
+  constexpr int BK = 32, NTHR = (BM / WM) * (BN / WN) * 64;
+  constexpr bool AKC = !TA, BKC = TB;
+  using TileA = F32Tile<BM, AKC, BK, NTHR>;
+  using TileB = F32Tile<BN, BKC, BK, NTHR>;
+  using SA = SplitTile<BM, AKC, BK>;
+  using SB = SplitTile<BN, BKC, BK>;
+  constexpr int STAGE = 3 * (SA::PLANE + SB::PLANE);  // elements
+  extern __shared__ __attribute__((aligned(1024))) unsigned char smem_raw[];
+  HF_LDS bf16* const smem = (HF_LDS bf16*)(HF_LDS void*)smem_raw;
+  __shared__ int last_block;
+  const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
+  const int col = lane & 31, half = lane >> 5;
+  int g = 0;
+  while (g + 1 < gg.n && (int)blockIdx.x >= gg.first[g + 1]) ++g;
+  const GemmP& p = gg.g[g];
+  // blocks go round-robin to the 8 XCDs: XCD x takes the x-th run of consecutive tiles, which share operand rows in
+  // its L2 (parts of k outermost: neighbours work on the same k)
+  const int nks = gg.nks[g], nblk = gg.blocks[g] * nks;
+  int b = blockIdx.x - gg.first[g];
+  b = (b & 7) * ((nblk + 7) >> 3) + (b >> 3);
+  if (b >= nblk) return;
+  const int ks = b / gg.blocks[g], zt = b - ks * gg.blocks[g];
+  const int z = zt / gg.tiles[g], tile = zt - z * gg.tiles[g];
+  const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
+  int tm, tn;
+  {  // bands of 8 tile rows
+    const int band = 8 * tiles_n, gi = tile / band, in = tile - gi * band;
+    const int rows = min(8, tiles_m - gi * 8);
+    tn = in / rows;
+    tm = gi * 8 + in - tn * rows;
+  }
+  const int m0 = tm * BM, n0 = tn * BN;
+  if (p.skip_upper && n0 > m0 + BM - 1) return;
+  const int z1 = z / p.nb2, z2 = z - z1 * p.nb2;
+  const int64_t offA = z1 * p.sA1 + z2 * p.sA2, offB = z1 * p.sB1 + (z2 / p.divB) * p.sB2, offC = z1 * p.sC1 + z2 * p.sC2;
+  int kbeg = 0, kend = p.K;
+  if (p.klimit == 1) kend = min(p.K, m0 + BM);
+  if (p.klimit == 2) kbeg = (m0 / BK) * BK;
+  // whole slabs of all terms, dealt to the parts; the ragged remainder of each term goes to the last part
+  const int nk = (kend - kbeg) / BK, total = nk * p.nterm;
+  const int it0 = (int)((int64_t)total * ks / nks), it1 = (int)((int64_t)total * (ks + 1) / nks);
+
+  const int wm0 = (wave / (BN / WN)) * WM, wn0 = (wave % (BN / WN)) * WN;
+  constexpr int TM = WM / 32, TN = WN / 32;
+  f32x16 acc[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+  float4 ra[2][TileA::NI], rb[2][TileB::NI];
+  uint32_t oa[VEC ? TileA::NI : 4 * TileA::NI], ob[VEC ? TileB::NI : 4 * TileB::NI];
+  TileA::template offsets<VEC>(oa, p.lda, m0, p.M, t);
+  TileB::template offsets<VEC>(ob, p.ldb, n0, p.N, t);
+  const int64_t stepA = TA ? BK * p.lda : BK, stepB = TB ? BK : BK * p.ldb;
+  auto base_a = [&](int term, int k0) { return (const float*)p.A[term] + offA + (TA ? (int64_t)k0 * p.lda + m0 : (int64_t)m0 * p.lda + k0); };
+  auto base_b = [&](int term, int k0) { return (const float*)p.B[term] + offB + (TB ? (int64_t)n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + n0); };
+  int f_term = nk > 0 ? it0 / nk : 0, f_slab = nk > 0 ? it0 - f_term * nk : 0;
+  const float *fa = nullptr, *fb = nullptr;
+  auto advance = [&]() {
+    if (f_slab + 1 < nk) {
+      ++f_slab;
+      fa += stepA;
+      fb += stepB;
+    } else if (f_term + 1 < p.nterm) {
+      ++f_term;
+      f_slab = 0;
+      fa = base_a(f_term, kbeg);
+      fb = base_b(f_term, kbeg);
+    }  // else the last slab again, for nobody: every iteration loads, so that none has to wait for its own loads
+  };
+  auto fetch = [&](auto& va, auto& vb) {
+    TileA::template fetch<VEC>(va, fa, oa);
+    TileB::template fetch<VEC>(vb, fb, ob);
+    advance();
+  };
+  // (chunks NTHR apart lie 4 NTHR elements apart: that many lines leave the rotation as it is)
+  static_assert(NTHR / (BK / 4) % 16 == 0 && NTHR / (BM / 4) % 16 == 0 && NTHR / (BN / 4) % 16 == 0, "lines per round of chunks");
+  const int sA0 = SA::at(t), sB0 = SB::at(t);
+  constexpr int NCH = TileA::NI + TileB::NI;  // chunks of four that a thread splits per slab
+  // chunk c of the slab in registers is split and stored into stage s; with REFILL its registers then receive the chunk of the
+  // slab at the cursor
+  auto store_one = [&](auto& va, auto& vb, int s, auto c_c, auto refill_c) {
+    constexpr int c = decltype(c_c)::value;
+    constexpr bool onA = c < TileA::NI;
+    constexpr int i = onA ? c : c - TileA::NI, PL = onA ? SA::PLANE : SB::PLANE;
+    HF_LDS bf16* d = smem + s * STAGE + (onA ? sA0 : 3 * SA::PLANE + sB0) + i * (4 * NTHR);
+    F32Parts x;
+    if constexpr (onA) x = f32_split(va[i]);
+    else x = f32_split(vb[i]);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      typedef unsigned u32x2 __attribute__((ext_vector_type(2)));
+      *(HF_LDS u32x2*)(d + q * PL) = (u32x2){x.p[q].x, x.p[q].y};
+    }
+    if constexpr (decltype(refill_c)::value) {
+      const float* const f = onA ? fa : fb;
+      const uint32_t* const o = onA ? oa : ob;
+      float4& v = onA ? va[onA ? i : 0] : vb[onA ? 0 : i];
+      if constexpr (VEC) v = *(const float4*)(f + o[i]);
+      else v = make_float4(f[o[4 * i]], f[o[4 * i + 1]], f[o[4 * i + 2]], f[o[4 * i + 3]]);
+    }
+  };
+  auto store = [&](auto& va, auto& vb, int s) {
+    static_for<NCH>([&](auto c_c) { store_one(va, vb, s, c_c, std::false_type{}); });
+  };
+  const int fA = (int)lin_frag_addr<BM, AKC, BK, 32>(wm0, 0, lane) / 2, fB = (int)lin_frag_addr<BN, BKC, BK, 32>(wn0, 0, lane) / 2;
+  // fragment i of a plane in k-step kk (row blocks of a wave differ in one bit field of the address, as do k-steps of a
+  // k-contiguous tile)
+  static_assert((TM == 1 || WM == 64) && TN == 1, "row blocks of a wave");
+  auto frag = [&](auto kc_c, auto r_c, const HF_LDS bf16* plane, int f0, int i, int kk) -> bf16x8 {
+    constexpr bool KC = decltype(kc_c)::value;
+    constexpr int R = decltype(r_c)::value;
+    if constexpr (KC) {
+      return *(const HF_LDS bf16x8*)(plane + (f0 ^ (kk * 16)) + i * 32 * BK);
+    } else {
+      const HF_LDS bf16* q0 = plane + (f0 ^ (i * 32)) + kk * 16 * R;
+      const bf16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((HF_LDS bf16x4*)q0);
+      const bf16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4bf16((HF_LDS bf16x4*)(q0 + 4 * R));
+      return __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
+    }
+  };
+  bf16x8 xa[2][3][TM], xb[2][3][TN];
+  auto read_kk = [&](int s, auto kk_c) {
+    constexpr int kk = decltype(kk_c)::value;
+    const HF_LDS bf16* As = smem + s * STAGE;
+    const HF_LDS bf16* Bs = As + 3 * SA::PLANE;
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+#pragma unroll
+      for (int i = 0; i < TM; ++i)
+        xa[kk][q][i] = frag(std::integral_constant<bool, AKC>{}, std::integral_constant<int, BM>{}, As + q * SA::PLANE, fA, i, kk);
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+        xb[kk][q][j] = frag(std::integral_constant<bool, BKC>{}, std::integral_constant<int, BN>{}, Bs + q * SB::PLANE, fB, j, kk);
+    }
+  };
+  // The matrix instructions of k-step kk, whose fragments are in registers, smallest terms first; chunks [C0, C1) of the slab in
+  // registers (va, vb) are split and stored into stage ds between them.
+  f32x16 sum[TM][TN];
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sum[i][j][r] = 0.f;
+  constexpr int MQ = 6 * TM * TN, CH = NCH / 2, NFRAG = 3 * (TM * (AKC ? 1 : 2) + TN * (BKC ? 1 : 2));
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  using IH = std::integral_constant<int, CH>;
+  using IN = std::integral_constant<int, NCH>;
+  auto multiply = [&](auto kk_c, auto c0_c, auto c1_c, int ds, auto& va, auto& vb) {
+    constexpr int kk = decltype(kk_c)::value, C0 = decltype(c0_c)::value, C1 = decltype(c1_c)::value;
+    constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
+    static_for<MQ>([&](auto q_c) {
+      constexpr int q = decltype(q_c)::value, term = q / (TM * TN), i = q % (TM * TN) / TN, j = q % TN;
+      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[kk][PA[term]][i], xb[kk][PB[term]][j], acc[i][j], 0, 0, 0);
+      constexpr int c = C0 + q * (C1 - C0) / MQ, cn = C0 + (q + 1) * (C1 - C0) / MQ;
+      static_assert(cn - c <= 1, "at most one chunk per matrix instruction");
+      if constexpr (cn > c) store_one(va, vb, ds, std::integral_constant<int, c>{}, std::true_type{});
+    });
+    // A wave issues in order: one matrix instruction (32 clocks of the pipe), then what fits into its shadow
+    if constexpr (C1 > C0) {
+      static_for<MQ>([&](auto q_c) {
+        constexpr int q = decltype(q_c)::value;
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // matrix instruction
+        __builtin_amdgcn_sched_group_barrier(0x100, (NFRAG + MQ - 1) / MQ, 0);             // LDS reads
+        __builtin_amdgcn_sched_group_barrier(0x002, (22 * (C1 - C0) + MQ - 1) / MQ, 0);    // arithmetic
+        if constexpr (q % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);       // LDS write
+        if constexpr (q % 3 == 1) __builtin_amdgcn_sched_group_barrier(0x020, VEC ? 1 : 4, 0);  // load
+      });
+    }
+    __builtin_amdgcn_sched_barrier(0);
+  };
+  // Long sums in two levels: every 16 slabs (512 k of all terms) the running sum goes to another one and starts again, which
+  // keeps the rounding of a sum of 50000 products below that of 1000 in a row.
+  auto flush = [&]() {
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) { sum[i][j][r] += acc[i][j][r]; acc[i][j][r] = 0.f; }
+  };
+  // Slab i, in LDS stage i % 2: the last k-step of the slab before it covers the reads of its first one, so that the barrier
+  // between slabs exposes no LDS latency; slab i + 1 goes from registers to the other stage (the last time it is an old one that
+  // nobody reads), and as each chunk has gone, that of slab i + 3 is loaded into its registers, two slabs before it is needed.
+  const int nit = it1 - it0;
+  auto slab = [&](int i, auto par_c) {
+    constexpr int s = decltype(par_c)::value;
+    __builtin_amdgcn_sched_barrier(0);
+    read_kk(s, I0{});
+    multiply(I1{}, I0{}, IH{}, 1 - s, ra[1 - s], rb[1 - s]);
+    if ((i & 15) == 0) flush();
+    read_kk(s, I1{});
+    multiply(I0{}, IH{}, IN{}, 1 - s, ra[1 - s], rb[1 - s]);
+    advance();
+    __syncthreads();
+  };
+  if (nit > 0) {
+    fa = base_a(f_term, kbeg + f_slab * BK);
+    fb = base_b(f_term, kbeg + f_slab * BK);
+    fetch(ra[0], rb[0]);
+    fetch(ra[1], rb[1]);
+    store(ra[0], rb[0], 0);
+    fetch(ra[0], rb[0]);
+    // the first slab has none before it: a k-step of zeros
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const bf16x8 zero = {};
+#pragma unroll
+      for (int i = 0; i < TM; ++i) xa[1][q][i] = zero;
+#pragma unroll
+      for (int j = 0; j < TN; ++j) xb[1][q][j] = zero;
+    }
+    __syncthreads();
+    int i = 0;
+    for (; i + 1 < nit; i += 2) {
+      slab(i, I0{});
+      slab(i + 1, I1{});
+    }
+    if (i < nit) slab(i, I0{});
+    multiply(I1{}, I0{}, I0{}, 0, ra[0], rb[0]);
+  }
+  const bool tail = kbeg + nk * BK < kend && ks == nks - 1;
+  if (tail) {
+    for (int term = 0; term < p.nterm; ++term) {
+      TileA::fetch_tail(ra[0], (const float*)p.A[term] + offA, p.lda, m0, p.M, kbeg + nk * BK, kend, t);
+      TileB::fetch_tail(rb[0], (const float*)p.B[term] + offB, p.ldb, n0, p.N, kbeg + nk * BK, kend, t);
+      __syncthreads();
+      store(ra[0], rb[0], 0);
+      __syncthreads();
+      read_kk(0, I0{});
+      read_kk(0, I1{});
+      multiply(I0{}, I0{}, I0{}, 0, ra[0], rb[0]);
+      multiply(I1{}, I0{}, I0{}, 0, ra[0], rb[0]);
+    }
+  }
+  flush();
+  bool bad = false;
+#pragma unroll
+  for (int i = 0; i < TM; ++i)
+#pragma unroll
+    for (int j = 0; j < TN; ++j)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        acc[i][j][r] = sum[i][j][r];
+        bad = bad || __builtin_isnan(sum[i][j][r]);
+      }
+  if (__builtin_expect(__any(bad), 0)) {
+#pragma unroll 1
+    for (int e = 0; e < TM * TN * 16; ++e) {
+      const int i = e / (TN * 16), j = e / 16 % TN, r = e % 16;
+      const int64_t gm = min(m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3), p.M - 1), gn = min(n0 + wn0 + j * 32 + col, p.N - 1);
+      float x = 0.f;
+      auto add = [&](int term, int k0, int k1) {
+        const float* A = (const float*)p.A[term] + offA + (TA ? gm : gm * p.lda);
+        const float* B = (const float*)p.B[term] + offB + (TB ? gn * p.ldb : gn);
+        for (int k = k0; k < k1; ++k) x = fmaf(A[TA ? k * p.lda : k], B[TB ? k : k * p.ldb], x);
+      };
+      for (int term = 0; term < p.nterm; ++term) {
+        const int s0 = max(it0 - term * nk, 0), s1 = min(it1 - term * nk, nk);
+        if (s0 < s1) add(term, kbeg + s0 * BK, kbeg + s1 * BK);
+        if (tail) add(term, kbeg + nk * BK, kend);
+      }
+#pragma unroll
+      for (int i2 = 0; i2 < TM; ++i2)
+#pragma unroll
+        for (int j2 = 0; j2 < TN; ++j2)
+#pragma unroll
+          for (int r2 = 0; r2 < 16; ++r2)
+            if (i2 == i && j2 == j && r2 == r) acc[i2][j2][r2] = x;
+    }
+  }
+
+  if (nks > 1) {
+    // partial tiles in accumulator order (thread t of every block of a tile owns the same elements)
+    constexpr int NACC = TM * TN * 16;
+    float* const base = gg.part + ((int64_t)gg.part0[g] + (int64_t)zt * nks) * (BM * BN);
+    float* mine = base + (int64_t)ks * (BM * BN) + t;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          __hip_atomic_store(mine + ((i * TN + j) * 16 + r) * NTHR, acc[i][j][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // The parts are stored and loaded as agent-scope atomics, which pass the XCDs' L2s on their own: once the stores
+    // are acknowledged the counter may follow.  (A fence instead would write back the whole L2 in every block: 580
+    // against 130 us for 1024 x 2304 x 768.)
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0) {
+      int* cnt = gg.counters + gg.cnt0[g] + zt;
+      const int arrived = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      last_block = arrived == nks - 1;
+      if (arrived == nks - 1) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!last_block) return;
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int j = 0; j < TN; ++j)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    for (int s = 0; s < nks; ++s) {
+      float* src = base + (int64_t)s * (BM * BN) + t;
+#pragma unroll
+      for (int e = 0; e < NACC; ++e)
+        acc[e / (TN * 16)][(e / 16) % TN][e % 16] += __hip_atomic_load(src + e * NTHR, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+  }
+
+  // accumulator tile: column lane & 31, rows 8*(r/4) + 4*(lane/32) + r%4
+#pragma unroll
+  for (int j = 0; j < TN; ++j) {
+    const int gn = n0 + wn0 + j * 32 + col;
+    if (gn >= p.N) continue;
+    float bsum = 0.f;
+    if (p.bias) bsum += ((const float*)p.bias)[gn];
+    if (p.bias_t) bsum += p.bias_t[gn];
+#pragma unroll
+    for (int i = 0; i < TM; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int gm = m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
+        if (gm >= p.M) continue;
+        const int64_t ci = offC + (int64_t)gm * p.ldc + gn;
+        float v = p.alpha * acc[i][j][r] + bsum;
+        if (p.Cadd) v += p.Cadd[ci];
+        ((float*)p.C)[ci] = v;
+      }
+  }
+}
+
 template <int BM, int BN, int BK, int WM, int WN, bool VEC>
 static hipError_t launch_f32_vec(const F32Group& gg, int grid, hipStream_t st) {
   const GemmP& p = gg.g[0];
@@ -356,23 +733,69 @@ static hipError_t launch_f32_cfg(const F32Group& gg, int grid, bool vec, hipStre
   return vec ? launch_f32_vec<BM, BN, BK, WM, WN, true>(gg, grid, st) : launch_f32_vec<BM, BN, BK, WM, WN, false>(gg, grid, st);
 }
 
-// Tiles, and the clocks a CU's matrix pipes need per slab as they run (the 64-float deep slabs of the small tile share
-// their k over the waves and pay a wait per 512 clocks).
-struct F32Cfg { int bm, bn, bk; double slab_clk; };
-static const F32Cfg kF32Cfg[] = {{64, 64, 32, 930.}, {128, 64, 32, 1720.}, {32, 32, 64, 665.}};
+template <int BM, int BN, int WM, int WN, bool TA, bool TB, bool VEC>
+static hipError_t launch_split_one(const F32Group& gg, int grid, hipStream_t st) {
+  static OncePerDevice once;
+  auto kern = gemm_f32_split_kernel<BM, BN, WM, WN, TA, TB, VEC>;
+  constexpr int smem = 2 * 3 * (BM + BN) * 32 * 2;
+  if (hipError_t e = once.lds_limit((const void*)kern, smem); e != hipSuccess) return e;
+  hipLaunchKernelGGL(kern, dim3(grid), dim3((BM / WM) * (BN / WN) * 64), smem, st, gg);
+  return hipGetLastError();
+}
+template <int BM, int BN, int WM, int WN, bool VEC>
+static hipError_t launch_split_vec(const F32Group& gg, int grid, hipStream_t st) {
+  const GemmP& p = gg.g[0];
+  if (!p.transA && !p.transB) return launch_split_one<BM, BN, WM, WN, false, false, VEC>(gg, grid, st);
+  if (!p.transA) return launch_split_one<BM, BN, WM, WN, false, true, VEC>(gg, grid, st);
+  if (!p.transB) return launch_split_one<BM, BN, WM, WN, true, false, VEC>(gg, grid, st);
+  return launch_split_one<BM, BN, WM, WN, true, true, VEC>(gg, grid, st);
+}
+template <int BM, int BN, int WM, int WN>
+static hipError_t launch_split(const F32Group& gg, int grid, bool vec, hipStream_t st) {
+  return vec ? launch_split_vec<BM, BN, WM, WN, true>(gg, grid, st) : launch_split_vec<BM, BN, WM, WN, false>(gg, grid, st);
+}
+// Tiles, the clocks a slab takes a CU that has enough blocks of them, and how much of that rate one to four resident blocks
+// reach: 64 x 64 has room for three (48 KB of LDS each; 1120 clocks a slab alone), 128 x 128 for one, 32 x 32 (64-deep slabs
+// whose k its waves share) for four.
+struct F32Cfg { int bm, bn, bk, resident; double slab_clk, busy[5]; };
+static const F32Cfg kF32Cfg[] = {{64, 64, 32, 3, 870., {1., 0.78, 0.92, 1., 1.}}, {128, 128, 32, 1, 2500., {1., 1., 1., 1., 1.}},
+                                  {32, 32, 64, 4, 665., {1., 0.68, 0.79, 0.92, 0.99}}};
 
-// Estimated clocks of a launch whose products have cnt[i] blocks of len[i] clocks, longest first.  Up to four blocks of the
-// two small tiles are resident per CU (35 and 37 KB of LDS each), dealt to the CUs in turn, and their matrix pipes are
-// busy 68, 79, 92 and 99 % of the time with one to four of them: launches of up to four blocks per CU last as
-// long as the fullest CU, others as long as the average and about two blocks more.  The 128 x 64 tile (53 to 55 KB) has room
-// for two or three: there the busy share of the last ones, and the limit of four, flatter it.
-static double f32_estimate(const int64_t* cnt, const double* len, int n) {
-  static const double kBusy[] = {1., 0.68, 0.79, 0.92, 0.99};
+// Estimated clocks of a launch whose products have cnt[i] blocks of len[i] clocks, longest first.  With one resident block a CU
+// takes the next when it has finished one.  Of the small tiles, four a CU are dealt in turn at the start: launches of no more last as long as the fullest CU, others as long as the average and a block more.
+static double f32_estimate(const int64_t* cnt, const double* len, int n, const F32Cfg& c) {
+  const double* const busy = c.busy;
   int64_t blocks = 0;
   double sum = 0.;
   for (int i = 0; i < n; ++i) { blocks += cnt[i]; sum += (double)cnt[i] * len[i]; }
   if (blocks == 0) return 0.;
-  if (blocks > 1024) return sum / 256. / kBusy[4] + 1.9 * sum / (double)blocks;
+  if (c.resident == 1) {
+    if (blocks > 16 * 256) return sum / 256. + 0.5 * len[n - 1];
+    // CUs by the time at which they are free, as groups of equal times
+    double at[64] = {0.};
+    int64_t cus[64] = {256};
+    int groups = 1;
+    double end = 0.;
+    for (int i = 0; i < n; ++i)
+      for (int64_t left = cnt[i]; left > 0;) {
+        int m = 0;
+        for (int k = 1; k < groups; ++k)
+          if (cus[k] > 0 && (cus[m] == 0 || at[k] < at[m])) m = k;
+        const int64_t take = std::min(left, cus[m]);
+        const double done = at[m] + len[i];
+        end = std::max(end, done);
+        left -= take;
+        cus[m] -= take;
+        int to = 0;
+        while (to < groups && cus[to] > 0 && at[to] != done) ++to;
+        if (to == 64) return std::max(end, sum / 256. + 0.5 * len[n - 1]);
+        if (to == groups) { ++groups; cus[to] = 0; }
+        at[to] = done;
+        cus[to] += take;
+      }
+    return end;
+  }
+  if (blocks > 1024) return sum / 256. / busy[4] + sum / (double)blocks;
   double worst = 0.;
   int64_t start = 0;
   for (int i = 0; i <= n; ++i) {  // the first CU that gets one block of product i - 1 less
@@ -385,7 +808,7 @@ static double f32_estimate(const int64_t* cnt, const double* len, int n) {
       while (b >= (e += cnt[k])) ++k;
       load += len[k];
     }
-    worst = std::max(worst, load / kBusy[held]);
+    worst = std::max(worst, load / busy[held]);
     if (i < n) start += cnt[i];
   }
   return worst;
@@ -404,30 +827,34 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   int order[F32_GROUP_MAX];
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order, order + n, [&](int a, int b) { return (int64_t)ps[a].nterm * ps[a].K > (int64_t)ps[b].nterm * ps[b].K; });
-  // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  (Under klimit the blocks
-  // are priced with the whole k, about twice their average: only the tile is chosen there, and all tiles are priced alike.)  A cut costs each block
-  // about 2000 clocks (partial tile out; twice that with the twice as large tile) and the launch 8000 (arrivals, sums).
-  // Measured (us; uncut 64 x 64, uncut 32 x 32, best and its tile / parts, chosen): primal product and tangent
-  // 1024x768x768 45.8 46.5 41.7 64/2 41.7, 1024x2304x768 118 115 106 64/3 106, 1024x3072x768 135 149 135 64/1 137,
-  // 1024x768x3072 167 161 141 64/2 148, 512x128x512 25.0 11.1 11.1 32/1 11.1, 512x384x128 10.4 7.1 7.1 32/1 7.1; A^T B
-  // 768x768x1024 43.8 37 32.3 64/3 35.3.
+  // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  (Under klimit the blocks are
+  // priced with the whole k, about twice their average: only the tile is chosen there, and all tiles are priced alike.)  A cut
+  // costs each block 1500 clocks a 64 x 64 part (partial tile out) and the launch 6000 and 1500 or 10000 a part (sums of small or large ones).
+  // Measured (us; 64 x 64 whole and in its best parts, 128 x 128 the same, 32 x 32, fp32 matrix instructions before): primal
+  // product and tangent 1024x768x768 39 37/2 58 39/3 51, 47; 1024x2304x768 82 - 76 - 123, 118; 1024x3072x768 103 - 102 - 161, 155;
+  // 1024x768x3072 143 110/3 196 94/3 166, 164; 1024x50257x768 1578 - 1263 - 2310, 1936; 1024x768x50257 1974 1578/4 2954 1326/6 -,
+  // 1985; 512x128x128 10 - 16 - 6.6, 6.7; 512x128x512 23 13/6 38 22/6 11.6, 11.5; A^T B 768x3072x1024 86 76/3 73 67/4 103, 111.
   int cfg = 0, parts = 1;
   double best = 1e300;
   for (int ci = 0; ci < 3; ++ci) {
     if (force_cfg >= 0 && ci != force_cfg) continue;
     const F32Cfg& c = kF32Cfg[ci];
     const bool cut = ci != 2 && ws && counters && !ps[0].klimit;
+    const double tile = c.bm * c.bn / 4096.;
+    int64_t all = 0;
+    for (int i = 0; i < n; ++i) all += tiles_of(ps[i], c) * nb;
     for (int k = 1; k <= (cut ? 12 : 1); ++k) {
       if (k > 1 && slabs_of(ps[order[0]], c) / k < 4) break;
+      if (k > 1 && (all * k * c.bm * c.bn > ws_elems || all > F32_COUNTERS)) break;
       int64_t cnt[F32_GROUP_MAX];
       double len[F32_GROUP_MAX];
       for (int i = 0; i < n; ++i) {
         const GemmP& p = ps[order[i]];
         const int64_t slabs = slabs_of(p, c), nks = std::min<int64_t>(k, slabs);
         cnt[i] = tiles_of(p, c) * nb * nks;
-        len[i] = c.slab_clk * (double)slabs / (double)nks + (nks > 1 ? (2000. + 60. * (double)nks) * (c.bm * c.bn) / 4096. : 0.);
+        len[i] = c.slab_clk * (double)slabs / (double)nks + (nks > 1 ? 1500. * tile : 0.);
       }
-      const double t = f32_estimate(cnt, len, n) + (k > 1 ? 8000. : 0.);
+      const double t = f32_estimate(cnt, len, n, c) + (k > 1 ? 6000. + (ci == 0 ? 1500. : 10000.) * k : 0.);
       if (t < best) { best = t; cfg = ci; parts = k; }
     }
   }
@@ -460,8 +887,8 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   gg.counters = counters;
   bool vec = true;
   for (int i = 0; i < n; ++i) vec = vec && ps[i].vecA && ps[i].vecB;
-  if (cfg == 0) return launch_f32_cfg<64, 64, 32, 32, 32>(gg, (int)first, vec, st);
-  if (cfg == 1) return launch_f32_cfg<128, 64, 32, 64, 32>(gg, (int)first, vec, st);
+  if (cfg == 0) return launch_split<64, 64, 32, 32>(gg, (int)first, vec, st);
+  if (cfg == 1) return launch_split<128, 128, 64, 32>(gg, (int)first, vec, st);
   return launch_f32_cfg<32, 32, 64, 32, 32>(gg, (int)first, vec, st);
 }
 

@@ -84,7 +84,7 @@ hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st) {
       const double full = (double)(tiles * k / 256), part = (double)(tiles * k % 256) / 256;
       const double blocks = full + (part > 0. ? 0.85 + 0.15 * part : 0.);
       const double us = k == 1 ? blocks * (slabs + 3. + out_us)
-                               : blocks * (slabs / k + 3. + lc.bm * lc.bn * 8 / 20e3) + 3. + (double)mn * (8 * k + 8) / 4.5e6;
+                               : blocks * (slabs / k + 3. + lc.bm * lc.bn * 8 / 20e3) + 6. + (double)mn * (8 * k + 8) / 4.5e6;
       if (us < best) { best = us; cfg = c; ks = k; }
     }
   }
