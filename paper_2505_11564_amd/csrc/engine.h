@@ -106,6 +106,7 @@ struct hf_ctx {
   int* gemm_cnt = nullptr;   // fp32 parameters: arrival counters of those products (F32_COUNTERS, zero between launches)
   int gemm_cnt_clear = 0;    // the first product has cleared them
   float* aux_vec = nullptr;  // n floats, allocated on first use (batch-loop partial result, unit vector)
+  bool gpt_groups_dw() const;
   int ensure_aux();
 
   // Lanczos state

@@ -375,28 +375,41 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
     CK(launch_fill_f32((float*)gemm_cnt, F32_COUNTERS, 0.f, st));
     gemm_cnt_clear = 1;
   }
-  if (accumulate) CK(launch_fill_f32((float*)(flags + 1), 1, 0.f, st));
-  else CK(launch_fill_f32((float*)flags, 2, 0.f, st));
-  // Small models: where every weight-gradient product of a layer, launched alone, would split k and add into a cleared
-  // result, the layers' whole range is cleared in one pass (the vectors between the matrices are accumulated with atomics as
-  // well), which replaces a fill per matrix and per group of vectors.  The grouped launch of a GPT layer may then still
-  // leave k whole and write every element itself; the pass over the matrices buys nothing there.
+  // Cleared up front, in one launch: the flags, and the blocks of H v that are accumulated with atomics.  Small models, where every
+  // weight-gradient product of a layer would split k and add into a cleared result: the layers' whole range in one piece (the
+  // vectors between the matrices with it), which replaces a fill per matrix, unless the launch that takes a GPT layer's products
+  // together leaves k whole and writes every element itself (clearing 340 MB of GPT-2-small for nothing was 43 us).
   dw_prezeroed = 0;
   if (!accumulate && bf && desc.arch != HF_ARCH_MLP && layers_end > layers_begin) {
     const int T = batch * seq, D = desc.d_model, F = desc.d_ff;
     const int hkv = desc.n_kv_head > 0 ? desc.n_kv_head : desc.n_head, Dkv = D / desc.n_head * hkv;
     bool all = gemm_mfma_splits_k(D, D, T, 2) && gemm_mfma_splits_k(D, F, T, 2) && gemm_mfma_splits_k(F, D, T, 2);
-    if (desc.arch == HF_ARCH_GPT) all = all && gemm_mfma_splits_k(D, 3 * D, T, 2);
-    else all = all && gemm_mfma_splits_k(D, Dkv, T, 2);
+    if (desc.arch == HF_ARCH_GPT) {
+      all = all && gemm_mfma_splits_k(D, 3 * D, T, 2);
+      if (all && gpt_groups_dw()) {
+        const int M[4] = {F, D, D, D}, N[4] = {D, F, D, 3 * D};
+        all = gemm_mfma_group_cuts_k(M, N, 4, T, 2);
+      }
+    } else {
+      all = all && gemm_mfma_splits_k(D, Dkv, T, 2);
+    }
     if (all) {
       CK(launch_fill_f32(out + layers_begin, layers_end - layers_begin, 0.f, st));
       dw_prezeroed = 1;
     }
   }
+  std::vector<float*> zp = {accumulate ? (float*)(flags + 1) : (float*)flags};
+  std::vector<int64_t> zn = {accumulate ? 1 : 2};
   if (!accumulate) for (auto& zr : zero_ranges) {
     if (dw_prezeroed && zr.first >= layers_begin && zr.first + zr.second <= layers_end) continue;
-    CK(launch_fill_f32(out + zr.first, zr.second, 0.f, st));
+    if (zr.second > (int64_t)1 << 20) {
+      CK(launch_fill_f32(out + zr.first, zr.second, 0.f, st));
+      continue;
+    }
+    zp.push_back(out + zr.first);
+    zn.push_back(zr.second);
   }
+  CK(launch_zero_ranges(zp.data(), zn.data(), (int)zp.size(), st));
   // The Lanczos update leaves the bf16 copy of q_{k+1} in vb; every other direction is converted here.
   if (bf && !(vb_of != nullptr && vb_of == v)) {
     CK(launch_f32_to_bf16(v, vb, n, st));
@@ -405,6 +418,12 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
   vb_of = nullptr;
   if (desc.arch == HF_ARCH_MLP) return hvp_mlp(params, inputs, labels, batch, v, out, st);
   return hvp_transformer(params, (const int32_t*)inputs, labels, batch, seq, v, out, st);
+}
+
+// The weight-gradient products of a bf16 GPT layer run as one launch while together they have fewer tiles than CUs.
+bool hf_ctx::gpt_groups_dw() const {
+  const int D = desc.d_model, F = desc.d_ff;
+  return gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F) < GROUP_MAX_TILES256;
 }
 
 int hf_ctx::ensure_aux() {
@@ -646,7 +665,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     // a branch are launched together before its norm.
     Gemm dw[4];
     int ndw = 0;
-    const bool group_dw = !bf || (!llama && gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F) < GROUP_MAX_TILES256);
+    const bool group_dw = !bf || (!llama && gpt_groups_dw());
     auto launch_dw = [&]() -> hipError_t {
       const int k = ndw;
       ndw = 0;

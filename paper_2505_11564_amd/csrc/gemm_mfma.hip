@@ -654,26 +654,14 @@ static hipError_t launch_group_one(const GemmGroup& gg, hipStream_t st) {
 struct GroupCfg { int bm, bn, slots; double slab_us, add_us; };
 static const GroupCfg kGroupCfg[] = {{256, 256, 256, 1.6, 23.}, {128, 128, 512, 1.08, 7.}};
 
-// The A^T B products ps[0..n) (fp32 results, no bias, operands on the fast path) as one launch.
-// zeroed: every C is zero or holds what the sum is added to, so k may be cut.
-// hipErrorNotSupported: launch them one by one.
-hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_t st) {
-  if (n < 2 || n > 4) return hipErrorNotSupported;
-  int64_t t256 = 0;
-  for (int i = 0; i < n; ++i) {
-    const GemmP& p = ps[i];
-    if (!p.transA || p.transB || p.out_bf16 || p.klimit || p.skip_upper || p.bias || p.bias_t || p.C_lo) return hipErrorNotSupported;
-    if (p.Cadd && p.Cadd != (const float*)p.C) return hipErrorNotSupported;
-    if (p.ldc != p.N) return hipErrorNotSupported;
-    t256 += gemm_tiles256(p.M, p.N);
-  }
-  if (t256 >= GROUP_MAX_TILES256) return hipErrorNotSupported;
+static void choose_group_plan(const GemmP* ps, int n, int zeroed, int& cfg, int& ks) {
   // Tile and parts of k: the shortest estimated launch, rounds of resident blocks times a block's length.  Whole
   // products of 12 / 6 layers (us; 256 x 256 in 1 or 2 parts, 128 x 128 in 1, 2 or 5; * chosen): width 768, 4096 tokens
   // 14806 14135 14006* 14357 14859; 999 tokens 6482 6560 6171* 6568 7173; 6 layers, 2048 tokens 4079 4020 3868* 4065 4305;
   // width 1024, 4096 tokens 8340* 8732 8727 8735 8974; width 256, 4096 tokens 3349 2963 2952 2665 2534* (4 parts chosen).
   // (256 x 128 tiles were slower than the better of the two everywhere.)
-  int cfg = 0, ks = 1;
+  cfg = 0;
+  ks = 1;
   double best = 1e300;
   for (int c = 0; c < 2; ++c) {
     const GroupCfg& gc = kGroupCfg[c];
@@ -689,6 +677,32 @@ hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_
       if (us < best) { best = us; cfg = c; ks = k; }
     }
   }
+}
+
+bool gemm_mfma_group_cuts_k(const int* M, const int* N, int n, int K, int nterm) {
+  GemmP ps[4] = {};
+  for (int i = 0; i < n; ++i) { ps[i].M = M[i]; ps[i].N = N[i]; ps[i].K = K; ps[i].nterm = nterm; }
+  int cfg, ks;
+  choose_group_plan(ps, n, 1, cfg, ks);
+  return ks > 1;
+}
+
+// The A^T B products ps[0..n) (fp32 results, no bias, operands on the fast path) as one launch.
+// zeroed: every C is zero or holds what the sum is added to, so k may be cut.
+// hipErrorNotSupported: launch them one by one.
+hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_t st) {
+  if (n < 2 || n > 4) return hipErrorNotSupported;
+  int64_t t256 = 0;
+  for (int i = 0; i < n; ++i) {
+    const GemmP& p = ps[i];
+    if (!p.transA || p.transB || p.out_bf16 || p.klimit || p.skip_upper || p.bias || p.bias_t || p.C_lo) return hipErrorNotSupported;
+    if (p.Cadd && p.Cadd != (const float*)p.C) return hipErrorNotSupported;
+    if (p.ldc != p.N) return hipErrorNotSupported;
+    t256 += gemm_tiles256(p.M, p.N);
+  }
+  if (t256 >= GROUP_MAX_TILES256) return hipErrorNotSupported;
+  int cfg, ks;
+  choose_group_plan(ps, n, zeroed, cfg, ks);
   const int bm = kGroupCfg[cfg].bm, bn = kGroupCfg[cfg].bn;
   GemmGroup gg = {};
   gg.n = n;

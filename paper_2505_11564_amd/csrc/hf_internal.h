@@ -120,6 +120,8 @@ hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st);  // dual output wi
 hipError_t launch_gemm_group(const Gemm* gs, int n, hipStream_t st);
 // bf16 A^T B product [M, N] over k = K with fp32 result and split-K allowed: will it accumulate with atomics?
 bool gemm_mfma_splits_k(int M, int N, int K, int nterm);
+// Will launch_gemm_group cut k of these A^T B products ([M_i, N_i], k = K, cleared results) and add with atomics?
+bool gemm_mfma_group_cuts_k(const int* M, const int* N, int n, int K, int nterm);
 // launch_gemm_group takes A^T B products whose 256 x 256 tiles together stay below this (one round of the CUs); with
 // more, each product fills the chip on its own.
 constexpr int64_t GROUP_MAX_TILES256 = 256;
@@ -130,6 +132,8 @@ inline int64_t gemm_tiles256(int M, int N) { return ((int64_t)M + 255) / 256 * (
 // Launchers take `bf` = 1 for bf16 mode (AT = PT = bf16), 0 for fp32 mode.
 
 hipError_t launch_fill_f32(float* p, int64_t n, float val, hipStream_t st);
+constexpr int ZERO_RANGES_MAX = 96;  // ranges of one launch (kernel arguments hold them)
+hipError_t launch_zero_ranges(float* const* ptr, const int64_t* len, int n, hipStream_t st);
 // Combine the per-part row statistics of the attention epilogues: forward (online softmax merge)
 // -> rstat[row] = (m, 1/l, r); backward (plain sums) -> rstat[row] = (delta, delta_t, 0).
 // Softmax-adjoint row statistics from dO and O (bf16 operands, head width 8 * 2^k); hipErrorNotSupported otherwise.
