@@ -641,7 +641,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
       auto add = [&](int term, int k0, int k1) {
         const float* A = (const float*)p.A[term] + offA + (TA ? gm : gm * p.lda);
         const float* B = (const float*)p.B[term] + offB + (TB ? gn * p.ldb : gn);
-        for (int k = k0; k < k1; ++k) x = fmaf(A[TA ? k * p.lda : k], B[TB ? k : k * p.ldb], x);
+        for (int k = k0; k < k1 && !__builtin_isnan(x); ++k) x = fmaf(A[TA ? k * p.lda : k], B[TB ? k : k * p.ldb], x);  // (a NaN stays one)
       };
       for (int term = 0; term < p.nterm; ++term) {
         const int s0 = max(it0 - term * nk, 0), s1 = min(it1 - term * nk, nk);
