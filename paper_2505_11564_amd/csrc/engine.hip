@@ -560,7 +560,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     } else {
     if (fused_att) {
       // scores without a trip through memory: the product is formed twice by the
-      // dual-output kernel, first to reduce (max, sum, tangent sum) per row over
+      // score kernel (gemm_dual.hip), first to reduce (max, sum, tangent sum) per row over
       // 64-column parts, then to write P, P_lo, P_t with the combined statistics
       Gemm g; att(g);
       g.M = S; g.N = S; g.K = dh; g.lda = W3; g.ldb = W3; g.ldc = S; g.transB = 1; g.alpha = cs; g.skip_upper = 1; g.divB = grp;
@@ -678,8 +678,8 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     if (!llama) {
       if ((rc = L.bwd_dw(b.g, b.g_t, dxa, dxa_t, T, F, D, F, D, o.wproj, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
       if ((rc = L.bwd_dx(dxa, dxa_t, T, F, D, D, o.wproj, dg, dg_t, F, bf))) return rc;
-      CK(launch_act_bwd(bf, gelu_kind, b.f, b.f_t, dg, dg_t, dg, dg_t, (int64_t)T * F, st));
-      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wfc, o.bfc, dg_t, bf, group_dw ? &dw[ndw++] : nullptr))) return rc;
+      CK(launch_act_bwd_bias(bf, gelu_kind, b.f, b.f_t, dg, dg_t, dg, dg_t, T, F, out + o.bfc, st));  // and the bias block of H v
+      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wfc, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
       if ((rc = L.bwd_dx(dg, dg_t, T, D, F, F, o.wfc, tmpd, tmpd_t, D, 0))) return rc;
     } else {
       if ((rc = L.bwd_dw(b.g, b.g_t, dxb, dxb_t, T, F, D, F, D, o.wdown, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;

@@ -94,7 +94,7 @@ struct Gemm {
   float* ws = nullptr;
   int64_t ws_elems = 0;
   int* counters = nullptr;  // fp32 products: F32_COUNTERS arrival counters, zero between launches
-  // Attention epilogues of the dual-output kernel (bf16 operands, Ct != nullptr).  With them the
+  // Attention epilogues of the score kernel, gemm_dual.hip (bf16 operands, Ct != nullptr).  With them the
   // score-shaped products never go to memory in fp32: the product is formed twice, once to reduce
   // row statistics over 64-column parts and once to apply them.
   //   EPI_FWD_STATS   : part[row][N/64][3] = (max, sum exp(s - max), sum exp(s - max) s_t) of the part
@@ -219,6 +219,9 @@ enum Act { ACT_TANH = 0, ACT_GELU = 1, ACT_GELU_TANH = 2 };
 // a_lo / y_lo (nullable): low-order halves of the primal input / output.
 hipError_t launch_act_fwd(int bf, int act, const void* a, const void* a_t, const void* a_lo, void* y, void* y_t,
                           void* y_lo, int64_t n, hipStream_t st);
+// launch_act_bwd over [T, F] with bias[F] += the column sums of da_t
+hipError_t launch_act_bwd_bias(int bf, int act, const void* a, const void* a_t, const void* dy, const void* dy_t, void* da,
+                               void* da_t, int T, int F, float* bias, hipStream_t st);
 hipError_t launch_act_bwd(int bf, int act, const void* a, const void* a_t, const void* dy, const void* dy_t, void* da,
                           void* da_t, int64_t n, hipStream_t st);
 hipError_t launch_swiglu_fwd(int bf, const void* g, const void* g_t, const void* u, const void* u_t, const void* g_lo,

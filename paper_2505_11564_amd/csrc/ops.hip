@@ -1012,6 +1012,45 @@ __global__ void act_bwd_vec_kernel(int act, const AT* a, const AT* a_t, const AT
     st8(da, i, o); st8(da_t, i, ot);
   }
 }
+// The same with the column sums of da_t, a bias block of H v: the tangent is summed where it is made, in fp32 before it is
+// rounded, instead of being read again by a launch of its own.  A block takes 256 columns and eight rows at a time (a wave: two
+// pieces of 512 bytes), keeps its columns' sums in registers and adds once per column.  Bound by the memory behind the L2 (six
+// tensors, 5.5 to 6 TB/s).  Both launches before / this one, bf16: 4096 x 3072 27.0 + 5.8 / 27.6 us, 4096 x 8192 63.6 + 11.9 / 67,
+// 999 x 3072 9.0 + 4.6 / 10.4.
+template <typename AT>
+__global__ __launch_bounds__(256) void act_bwd_bias_kernel(int act, const AT* a, const AT* a_t, const AT* dy, const AT* dy_t, AT* da, AT* da_t,
+                                                           int T, int F, int rows_per_block, float* bias) {
+  __shared__ float red[8][256 + 8];
+  const int cg = threadIdx.x & 31, rl = threadIdx.x >> 5;
+  const int c = blockIdx.x * 256 + cg * 8;
+  const int r0 = blockIdx.y * rows_per_block, r1 = min(T, r0 + rows_per_block);
+  float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+  if (c < F) {
+    for (int r = r0 + rl; r < r1; r += 8) {
+      const int64_t i = ((int64_t)r * F + c) / 8;
+      float av[8], at[8], d[8], dt[8], o[8], ot[8];
+      ld8(a, i, av); ld8(a_t, i, at); ld8(dy, i, d); ld8(dy_t, i, dt);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        float f, f1, f2;
+        act_derivs(act, av[q], f, f1, f2);
+        o[q] = f1 * d[q]; ot[q] = f1 * dt[q] + f2 * at[q] * d[q];
+        s[q] += ot[q];
+      }
+      st8(da, i, o); st8(da_t, i, ot);
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < 8; ++q) red[rl][cg * 8 + q] = s[q];
+  __syncthreads();
+  const int col = blockIdx.x * 256 + threadIdx.x;
+  if (col < F) {
+    float t = 0.f;
+#pragma unroll
+    for (int k = 0; k < 8; ++k) t += red[k][threadIdx.x];
+    atomicAdd(bias + col, t);
+  }
+}
 template <typename AT>
 __global__ void swiglu_fwd_vec_kernel(const AT* g, const AT* g_t, const AT* u, const AT* u_t, const AT* g_lo, const AT* u_lo,
                                       AT* y, AT* y_t, AT* y_lo, int64_t n8) {
@@ -1063,6 +1102,22 @@ hipError_t launch_act_fwd(int bf, int act, const void* a, const void* a_t, const
   if (bf) hipLaunchKernelGGL(act_fwd_kernel<bf16>, dim3(ew_blocks(n)), dim3(256), 0, st, act, (const bf16*)a, (const bf16*)a_t, (const bf16*)a_lo, (bf16*)y, (bf16*)y_t, (bf16*)y_lo, n);
   else hipLaunchKernelGGL(act_fwd_kernel<float>, dim3(ew_blocks(n)), dim3(256), 0, st, act, (const float*)a, (const float*)a_t, (const float*)a_lo, (float*)y, (float*)y_t, (float*)y_lo, n);
   return hipGetLastError();
+}
+hipError_t launch_act_bwd_bias(int bf, int act, const void* a, const void* a_t, const void* dy, const void* dy_t, void* da,
+                               void* da_t, int T, int F, float* bias, hipStream_t st) {
+  if (T <= 0 || F <= 0) return hipSuccess;
+  if (F % 8 == 0 && T <= 1 << 20 && all_aligned16({a, a_t, dy, dy_t, da, da_t})) {  // (grid.y stays below 65536)
+    // A block adds once per column, so more rows a block are fewer additions, but fewer loads in flight: with 16 / 32 / 64 or more
+    // rows a block 999 x 3072 takes 10.4 / 12.6 / - us, 4096 x 3072 28.9 / 27.6 / 28.1, 4096 x 8192 - / 67 / 72 to 75.
+    const int64_t cb = (F + 255) / 256;
+    const int rows = cb * ((T + 31) / 32) >= 1024 ? 32 : cb * ((T + 15) / 16) >= 512 ? 16 : 8;
+    const dim3 grid((unsigned)cb, (T + rows - 1) / rows);
+    if (bf) hipLaunchKernelGGL(act_bwd_bias_kernel<bf16>, grid, dim3(256), 0, st, act, (const bf16*)a, (const bf16*)a_t, (const bf16*)dy, (const bf16*)dy_t, (bf16*)da, (bf16*)da_t, T, F, rows, bias);
+    else hipLaunchKernelGGL(act_bwd_bias_kernel<float>, grid, dim3(256), 0, st, act, (const float*)a, (const float*)a_t, (const float*)dy, (const float*)dy_t, (float*)da, (float*)da_t, T, F, rows, bias);
+    return hipGetLastError();
+  }
+  const hipError_t e = launch_act_bwd(bf, act, a, a_t, dy, dy_t, da, da_t, (int64_t)T * F, st);
+  return e != hipSuccess ? e : launch_colsum(bf, da_t, T, F, F, bias, st);
 }
 hipError_t launch_act_bwd(int bf, int act, const void* a, const void* a_t, const void* dy, const void* dy_t, void* da,
                           void* da_t, int64_t n, hipStream_t st) {
