@@ -622,6 +622,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     }
   }
   flush();
+  // (only results that are stored count: a tile's rows and columns beyond the operand hold products of whatever lies in the
+  // padding of its rows)
   bool bad = false;
 #pragma unroll
   for (int i = 0; i < TM; ++i)
@@ -630,7 +632,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         acc[i][j][r] = sum[i][j][r];
-        bad = bad || __builtin_isnan(sum[i][j][r]);
+        bad = bad || (__builtin_isnan(sum[i][j][r]) && m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3) < p.M && n0 + wn0 + j * 32 + col < p.N);
       }
   if (__builtin_expect(__any(bad), 0)) {
 #pragma unroll 1

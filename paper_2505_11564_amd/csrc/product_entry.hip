@@ -1,0 +1,24 @@
+// One matrix product as the engine launches it, behind a C entry: what the tests of single products call.  Not part of the API.
+#include "hf_internal.h"
+
+// ptr: A[3], B[3], C, C_lo, Cadd, At, Bt, Ct, Cadd_t, ws, counters (device memory; nullptr where absent).
+// num: M, N, K, lda, ldb, ldc, transA, transB, in_bf16, out_bf16, klimit, elements of ws, force_cfg, force_ks.
+// Returns the launch's hipError_t.
+extern "C" __attribute__((visibility("default"))) int hf_internal_product(void* const* ptr, const int64_t* num, float alpha, void* stream) {
+  if (!ptr || !num) return (int)hipErrorInvalidValue;
+  for (int i = 0; i < 6; ++i)
+    if (num[i] < 1 || num[i] > (int64_t)1 << 30) return (int)hipErrorInvalidValue;
+  hf::Gemm g;
+  for (int i = 0; i < 3; ++i) { g.A[i] = ptr[i]; g.B[i] = ptr[3 + i]; }
+  g.C = ptr[6]; g.C_lo = ptr[7]; g.Cadd = (const float*)ptr[8];
+  g.At = ptr[9]; g.Bt = ptr[10]; g.Ct = ptr[11]; g.Cadd_t = (const float*)ptr[12];
+  g.ws = (float*)ptr[13]; g.counters = (int*)ptr[14];
+  g.M = (int)num[0]; g.N = (int)num[1]; g.K = (int)num[2];
+  g.lda = num[3]; g.ldb = num[4]; g.ldc = num[5];
+  g.transA = (int)num[6]; g.transB = (int)num[7];
+  g.in_bf16 = (int)num[8]; g.out_bf16 = (int)num[9]; g.klimit = (int)num[10];
+  g.ws_elems = num[11]; g.force_cfg = (int)num[12]; g.force_ks = (int)num[13];
+  g.alpha = alpha;
+  if (g.lda < (g.transA ? g.M : g.K) || g.ldb < (g.transB ? g.K : g.N) || g.ldc < g.N) return (int)hipErrorInvalidValue;
+  return (int)hf::launch_gemm(g, (hipStream_t)stream);
+}

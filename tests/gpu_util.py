@@ -80,3 +80,28 @@ def device_randn(n, seed):
         b = min(n, a + step)
         out[a:b] = torch.randn(b - a, generator=gen, device="cuda")
     return out
+
+
+def fp32_product(A, B, tile=-1, parts=0, At=None, Bt=None):
+    """C = A B of fp32 device tensors as the engine launches it; a view whose columns are contiguous is passed with its row stride, one whose
+    rows are as a transposed operand.  At, Bt: also the tangent At B + A Bt, and (C, C_t) is returned.  tile, parts: override the
+    launcher's choice (0: 64 x 64, 1: 128 x 128, 2: 32 x 32)."""
+    import ctypes
+    M, K = A.shape
+    N = B.shape[1]
+    def layout(x):
+        return (0, x.stride(0)) if x.stride(1) == 1 else (1, x.stride(1))
+    (ta, lda), (tb, ldb) = layout(A), layout(B)
+    dual = At is not None
+    C = [torch.full((M, N), float("nan"), device="cuda") for _ in range(1 + dual)]
+    ws = torch.empty(1 << 24, device="cuda")
+    cnt = torch.zeros(8192, dtype=torch.int32, device="cuda")
+    ptr = (ctypes.c_void_p * 15)()
+    ptr[0], ptr[3], ptr[6], ptr[13], ptr[14] = A.data_ptr(), B.data_ptr(), C[0].data_ptr(), ws.data_ptr(), cnt.data_ptr()
+    if dual:
+        assert layout(At) == (ta, lda) and layout(Bt) == (tb, ldb)
+        ptr[9], ptr[10], ptr[11] = At.data_ptr(), Bt.data_ptr(), C[1].data_ptr()
+    num = (ctypes.c_int64 * 14)(M, N, K, lda, ldb, N, ta, tb, 0, 0, 0, ws.numel(), tile, parts)
+    assert hf.lib().hf_internal_product(ptr, num, ctypes.c_float(1.0), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    return tuple(C) if dual else C[0]
