@@ -344,8 +344,9 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
 // and the taking apart (88 vector instructions a wave, dealt out between them) 0.34: 195 TFLOP/s at 4096^3 (fp32 instructions 131),
 // 145 at 1024 x 3072 x 768 (94).  Relative error against 64 bits, fp32 instructions / this: k = 768 5.0e-7 / 3.1e-7, 3072 in parts
 // 4.5e-7 / 3.5e-7, 50257 1.8e-6 / 4.4e-7; operands over five decades 4.5e-7 / 2.6e-7, 4.0e-7 / 2.9e-7, 1.6e-6 / 4.1e-7.
-// An operand that is infinite, or rounds to infinity in bf16, makes every result that it takes part in a NaN here: blocks
-// that find one among their results compute them again with fp32 multiply-adds.
+// An operand that is infinite, or rounds to infinity in bf16, makes every result that it takes part in a NaN here, and the product of
+// two first parts, each rounded up by as much as 2^-8 of it, can overflow where the product itself does not: blocks that find
+// a result that is not finite compute theirs again with fp32 multiply-adds.
 struct F32Parts { uint2 p[3]; };
 __device__ __forceinline__ unsigned f32_round_pair(float a, float b) {
   typedef float f32v2 __attribute__((ext_vector_type(2)));
@@ -632,7 +633,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
         acc[i][j][r] = sum[i][j][r];
-        bad = bad || (__builtin_isnan(sum[i][j][r]) && m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3) < p.M && n0 + wn0 + j * 32 + col < p.N);
+        bad = bad || (!__builtin_isfinite(sum[i][j][r]) && m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3) < p.M && n0 + wn0 + j * 32 + col < p.N);
       }
   if (__builtin_expect(__any(bad), 0)) {
 #pragma unroll 1

@@ -43,3 +43,20 @@ def test_padding_that_nobody_wrote(tile, trans):
     got = fp32_product(A, B, tile, 1)
     assert (got.double() - want).norm() <= 1e-5 * want.norm()
     assert _seconds(lambda: fp32_product(A, B, tile, 1)) <= 5 * plain
+
+
+@pytest.mark.parametrize("sign", [1.0, -1.0])
+@pytest.mark.parametrize("tile", TILES)
+def test_products_just_below_the_largest_float(tile, sign):
+    """Mantissas 1.01967 and 1.96111: their product 1.9997 fits below the largest float, that of the two rounded up to eight bits (2.007)
+    does not.  One such product is the whole sum, so the result is it, rounded once."""
+    import torch
+    from gpu_util import fp32_product
+    A, B = torch.zeros(70, 45, device="cuda"), torch.zeros(45, 66, device="cuda")
+    A[3:68:13, 40] = sign * 1.01967 * 2.0 ** 63
+    B[40, 1:66:9] = 1.96111 * 2.0 ** 64
+    want = (A.double() @ B.double()).float()
+    assert torch.isfinite(want).all() and want.abs().max() > 3.4e38
+    got = fp32_product(A, B, tile, 1)
+    assert torch.isfinite(got).all()
+    assert ((got - want).abs() <= want.abs() * 2.0 ** -23).all()
