@@ -60,3 +60,40 @@ def test_products_just_below_the_largest_float(tile, sign):
     got = fp32_product(A, B, tile, 1)
     assert torch.isfinite(got).all()
     assert ((got - want).abs() <= want.abs() * 2.0 ** -23).all()
+
+
+def _special(K, trans):
+    """Operands with an infinity, a NaN and a number that rounds to infinity in bf16, each in a row (A) or a column (B) of its own."""
+    A, B = _randn(150, K, seed=3), _randn(K, 145, seed=4)
+    A[5, K // 3], A[77, 1], A[140, K - 1] = float("inf"), float("nan"), 3.4e38
+    B[K - 2, 9], B[0, 130] = -float("inf"), float("nan")
+    B[K - 1] *= 1e-3
+    return (A.t().contiguous().t(), B.t().contiguous().t()) if trans else (A, B)
+
+
+@pytest.mark.parametrize("parts", [1, 3])
+@pytest.mark.parametrize("trans", [0, 1])
+@pytest.mark.parametrize("K", [397, 30000])
+@pytest.mark.parametrize("tile", TILES)
+def test_operands_that_are_not_finite(tile, K, trans, parts):
+    """Infinities and NaN where float64 has them (with a finite operand's 3.4e38 below the overflow), everything else within the rounding of
+    a sum one product at a time, sqrt(K / 6) 2^-24 of its size (4.2e-6 for the longest; twice that is allowed), and in at most ten times the time of
+    ordinary operands (fp32 instructions after the others: three to four times; one number at a time it was 200 times)."""
+    import torch
+    from gpu_util import fp32_product
+    plain = (_randn(150, K, seed=3), _randn(K, 145, seed=4))
+    if trans:
+        plain = tuple(x.t().contiguous().t() for x in plain)
+    A, B = _special(K, trans)
+    want = A.double() @ B.double()
+    got = fp32_product(A, B, tile, parts)
+    fin = torch.isfinite(want)
+    assert torch.equal(torch.isnan(got), torch.isnan(want))
+    assert torch.equal(got[~fin & ~torch.isnan(want)].double(), want[~fin & ~torch.isnan(want)])
+    rows = torch.ones(150, dtype=torch.bool, device="cuda")
+    rows[140] = False  # 3.4e38 times a number of its own column: the rest of that row's sums is below the last bit
+    for r in (rows, ~rows):
+        e, w = (got.double() - want)[r][fin[r]], want[r][fin[r]]
+        assert e.norm() <= 8.4e-6 * w.norm()
+    if K > 1000:
+        assert _seconds(lambda: fp32_product(A, B, tile, parts)) <= 10 * _seconds(lambda: fp32_product(*plain, tile, parts))
