@@ -336,7 +336,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
 }
 
 // ---- larger tiles: fp32 operands as three bf16 parts each ------------------------------------------------------------------
-// A float is the exact sum of three bf16 numbers x0 + x1 + x2 (8 significant bits each, each the rounding of what is left), so
+// A float times 2^24 is the exact sum of three bf16 numbers x0 + x1 + x2 (8 significant bits each, each the rounding of what is left).
+// The factor keeps the last bit of every float, the smallest subnormal one too, within bf16's normal range: without it operands lost
+// bits below 2^-110 (relative error of a product 1e-7 at any scale with the factor; without it 2.7e-6 at 1e-35 and 2.6e-4 at 1e-37).
+// It is taken out of the finished sums.  So
 //   x y = x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) + ...
 // in exact bf16 products with fp32 accumulation; the terms left out (x1 y2, x2 y1, x2 y2) are below 2^-26 of |x y|, less than the
 // rounding of one fp32 addition.  Six bf16 matrix instructions take 3/8 of the time of the fp32 ones they replace.
@@ -344,10 +347,10 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
 // and the taking apart (88 vector instructions a wave, dealt out between them) 0.34: 195 TFLOP/s at 4096^3 (fp32 instructions 131),
 // 145 at 1024 x 3072 x 768 (94).  Relative error against 64 bits, fp32 instructions / this: k = 768 5.0e-7 / 3.1e-7, 3072 in parts
 // 4.5e-7 / 3.5e-7, 50257 1.8e-6 / 4.4e-7; operands over five decades 4.5e-7 / 2.6e-7, 4.0e-7 / 2.9e-7, 1.6e-6 / 4.1e-7.
-// An operand that is infinite, or rounds to infinity in bf16, makes every result that it takes part in a NaN here, and the product of
-// two first parts, each rounded up by as much as 2^-8 of it, can overflow where the product itself does not: blocks that find
-// a result that is not finite compute theirs again with the fp32 instructions (150 x 145 x 30000 with an infinity in each block: 2.6 instead of 0.85 ms with
-// 64 x 64 tiles, 4.8 instead of 1.65 with 128 x 128; 4096^3 with one in every row 2.4 times as long).
+// An operand that is infinite or at least 2^104 makes every result that it takes part in a NaN here, and sums of 2^80 (1.2e24) and
+// more, or nearly that when the first parts are rounded up by as much as 2^-8 of them, are infinite: blocks that find a result that
+// is not finite compute theirs again with the fp32 instructions (150 x 145 x 30000 with an infinity in each block: 2.6 instead of
+// 0.85 ms with 64 x 64 tiles, 4.8 instead of 1.65 with 128 x 128; 4096^3 with one in every row 2.4 times as long).
 struct F32Parts { uint2 p[3]; };
 __device__ __forceinline__ unsigned f32_round_pair(float a, float b) {
   typedef float f32v2 __attribute__((ext_vector_type(2)));
@@ -356,8 +359,9 @@ __device__ __forceinline__ unsigned f32_round_pair(float a, float b) {
   asm("" : "+v"(u));  // (the compiler would round again, one number at a time, where the parts are unpacked)
   return u;
 }
+constexpr float F32_PARTS_SCALE = 16777216.f;  // 2^24
 __device__ __forceinline__ F32Parts f32_split(const float4 v) {
-  float x = v.x, y = v.y, z = v.z, w = v.w;
+  float x = v.x * F32_PARTS_SCALE, y = v.y * F32_PARTS_SCALE, z = v.z * F32_PARTS_SCALE, w = v.w * F32_PARTS_SCALE;
   F32Parts o;
 #pragma unroll
   for (int q = 0; q < 3; ++q) {
@@ -531,6 +535,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) sum[i][j][r] = 0.f;
+  constexpr int SPLIT_VALU = 26;  // vector instructions that take a chunk apart
   constexpr int MQ = 6 * TM * TN, CH = NCH / 2, NFRAG = 3 * (TM * (AKC ? 1 : 2) + TN * (BKC ? 1 : 2));
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -552,7 +557,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
         constexpr int q = decltype(q_c)::value;
         __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);                                // matrix instruction
         __builtin_amdgcn_sched_group_barrier(0x100, (NFRAG + MQ - 1) / MQ, 0);             // LDS reads
-        __builtin_amdgcn_sched_group_barrier(0x002, (22 * (C1 - C0) + MQ - 1) / MQ, 0);    // arithmetic
+        __builtin_amdgcn_sched_group_barrier(0x002, (SPLIT_VALU * (C1 - C0) + MQ - 1) / MQ, 0);    // arithmetic
         if constexpr (q % 2 == 1) __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);       // LDS write
         if constexpr (q % 3 == 1) __builtin_amdgcn_sched_group_barrier(0x020, VEC ? 1 : 4, 0);  // load
       });
@@ -633,7 +638,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     for (int j = 0; j < TN; ++j)
 #pragma unroll
       for (int r = 0; r < 16; ++r) {
-        acc[i][j][r] = sum[i][j][r];
+        acc[i][j][r] = sum[i][j][r] * (1.f / F32_PARTS_SCALE / F32_PARTS_SCALE);
         nans = fmaf(m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3) < p.M ? sum[i][j][r] : 0.f, 0.f, nans);
       }
   const bool bad = nans != 0.f && n0 + wn0 + col < p.N;

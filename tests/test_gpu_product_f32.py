@@ -97,3 +97,18 @@ def test_operands_that_are_not_finite(tile, K, trans, parts):
         assert e.norm() <= 8.4e-6 * w.norm()
     if K > 1000:
         assert _seconds(lambda: fp32_product(A, B, tile, parts)) <= 10 * _seconds(lambda: fp32_product(*plain, tile, parts))
+
+
+@pytest.mark.parametrize("scale", [1e-20, 1e-35, 1e-37, 1e-40, 1e12, 1e24])
+@pytest.mark.parametrize("tile", TILES)
+def test_operands_of_any_size(tile, scale):
+    """Both operands in turn: every float keeps all of its bits, so the error is that of the sum, sqrt(300 / 6) 2^-24 = 4.2e-7 (twice that is
+    allowed) whatever the scale.  The other operand is of a size that keeps the result among the normal numbers (with 1e12 and 1e24: sums on
+    both sides of 1.2e24, where a tile of parts is computed again)."""
+    import torch
+    from gpu_util import fp32_product
+    A, B = _randn(131, 300, seed=5, scale=scale), _randn(300, 133, seed=6, scale=1e6 if scale < 1 else 1e12)
+    for a, b in ((A, B), (B.t(), A.t()), (B.t().contiguous(), A.t().contiguous())):
+        want = a.double() @ b.double()
+        got = fp32_product(a, b, tile, 1)
+        assert (got.double() - want).norm() <= 8.4e-7 * want.norm()
