@@ -45,27 +45,34 @@ struct F32Tile {
   static __device__ __forceinline__ int kk(int c) { return KC ? (c % (BK / 4)) * 4 : c / (R / 4); }
   // Element offsets of the thread's chunks from the slab's (block-uniform) base.  Rows beyond the operand are replaced
   // by its last ones (they only feed results that are never stored), so the loads need no guard; without VEC the
-  // elements of a chunk are clamped one by one.
+  // elements of a chunk along the rows are clamped one by one.
+  template <bool VEC> static constexpr int PER = VEC || KC ? 1 : 4;  // offsets a chunk
   template <bool VEC>
-  static __device__ __forceinline__ void offsets(uint32_t (&o)[VEC ? NI : 4 * NI], int64_t ld, int r0, int rmax, int t) {
+  static __device__ __forceinline__ void offsets(uint32_t (&o)[PER<VEC> * NI], int64_t ld, int r0, int rmax, int t) {
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       const int c = t + i * NTHR;
 #pragma unroll
-      for (int q = 0; q < (VEC ? 1 : 4); ++q) {
-        const int r = r0 + row(c) + (KC ? 0 : q), k = kk(c) + (KC ? q : 0);
+      for (int q = 0; q < PER<VEC>; ++q) {
+        const int r = r0 + row(c) + q;
         const int rc = (VEC && !KC ? min(r, ((rmax - 1) >> 2) << 2) : min(r, rmax - 1)) - r0;
-        o[VEC ? i : 4 * i + q] = (uint32_t)(KC ? (int64_t)rc * ld + k : (int64_t)k * ld + rc);
+        o[PER<VEC> * i + q] = (uint32_t)(KC ? (int64_t)rc * ld + kk(c) : (int64_t)kk(c) * ld + rc);
       }
     }
   }
   template <bool VEC>
-  static __device__ __forceinline__ void fetch(float4 (&v)[NI], const float* base, const uint32_t (&o)[VEC ? NI : 4 * NI]) {
-#pragma unroll
-    for (int i = 0; i < NI; ++i) {
-      if constexpr (VEC) v[i] = *(const float4*)(base + o[i]);
-      else v[i] = make_float4(base[o[4 * i]], base[o[4 * i + 1]], base[o[4 * i + 2]], base[o[4 * i + 3]]);
+  static __device__ __forceinline__ float4 fetch_one(const float* base, const uint32_t* o, int i) {
+    if constexpr (VEC) return *(const float4*)(base + o[i]);
+    else if constexpr (KC) {
+      const float* const p = base + o[i];
+      return make_float4(p[0], p[1], p[2], p[3]);
     }
+    else return make_float4(base[o[4 * i]], base[o[4 * i + 1]], base[o[4 * i + 2]], base[o[4 * i + 3]]);
+  }
+  template <bool VEC>
+  static __device__ __forceinline__ void fetch(float4 (&v)[NI], const float* base, const uint32_t (&o)[PER<VEC> * NI]) {
+#pragma unroll
+    for (int i = 0; i < NI; ++i) v[i] = fetch_one<VEC>(base, o, i);
   }
   // The ragged last slab: zeros for k in [kend, k0 + BK); every load is in bounds (clamped) and none is conditional.
   static __device__ __forceinline__ void fetch_tail(float4 (&v)[NI], const float* X, int64_t ld, int r0, int rmax, int k0, int kend, int t) {
@@ -153,7 +160,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   float4 ra[2][TileA::NI], rb[2][TileB::NI];
-  uint32_t oa[VEC ? TileA::NI : 4 * TileA::NI], ob[VEC ? TileB::NI : 4 * TileB::NI];
+  uint32_t oa[TileA::template PER<VEC> * TileA::NI], ob[TileB::template PER<VEC> * TileB::NI];
   TileA::template offsets<VEC>(oa, p.lda, m0, p.M, t);
   TileB::template offsets<VEC>(ob, p.ldb, n0, p.N, t);
   const int64_t stepA = TA ? BK * p.lda : BK, stepB = TB ? BK : BK * p.ldb;
@@ -338,15 +345,17 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
 // ---- larger tiles: fp32 operands as three bf16 parts each ------------------------------------------------------------------
 // A float times 2^24 is the exact sum of three bf16 numbers x0 + x1 + x2 (8 significant bits each, each the rounding of what is left).
 // The factor keeps the last bit of every float, the smallest subnormal one too, within bf16's normal range: without it operands lost
-// bits below 2^-110 (relative error of a product 1e-7 at any scale with the factor; without it 2.7e-6 at 1e-35 and 2.6e-4 at 1e-37).
-// It is taken out of the finished sums.  So
+// bits below 2^-110 (relative error of a product 2.7e-6 at 1e-35 and 2.6e-4 at 1e-37).  It is taken out of the finished sums.  So
 //   x y = x0 y0 + (x0 y1 + x1 y0) + (x1 y1 + x0 y2 + x2 y0) + ...
-// in exact bf16 products with fp32 accumulation; the terms left out (x1 y2, x2 y1, x2 y2) are below 2^-26 of |x y|, less than the
-// rounding of one fp32 addition.  Six bf16 matrix instructions take 3/8 of the time of the fp32 ones they replace.
-// What bounds it: a slab of 128 x 128 x 32 takes 1.3 us with all CUs busy (0.86 alone), of which its matrix instructions are 0.75
-// and the taking apart (88 vector instructions a wave, dealt out between them) 0.34: 195 TFLOP/s at 4096^3 (fp32 instructions 131),
-// 145 at 1024 x 3072 x 768 (94).  Relative error against 64 bits, fp32 instructions / this: k = 768 5.0e-7 / 3.1e-7, 3072 in parts
-// 4.5e-7 / 3.5e-7, 50257 1.8e-6 / 4.4e-7; operands over five decades 4.5e-7 / 2.6e-7, 4.0e-7 / 2.9e-7, 1.6e-6 / 4.1e-7.
+// in exact bf16 products with fp32 accumulation.  The terms left out (x1 y2, x2 y1, x2 y2) are up to 2^-24 of |x y| where both mantissas
+// lie just above 1 (2^-27.5 on average), as much as one rounding of an fp32 sum.  In return the large products x0 y0 have sums of their
+// own, which round once for 16 of them; the five small ones go to others, 2^-8 of their size.
+// Relative error against 64 bits, fp32 instructions (64 x 64 tiles; 32 x 32) / this: k = 16 7.4e-8 7.4e-8 / 3.2e-8, 128 2.0e-7 1.1e-7 /
+// 6.5e-8, 512 4.1e-7 2.1e-7 / 1.3e-7, 4096 1.2e-6 5.8e-7 / 1.9e-7, 50257 4.0e-6 2.0e-6 / 2.3e-7; mantissas between 1 and 1.02 k = 512
+// 3.1e-7 9.0e-8 / 3.4e-8; every product losing most 5.9e-8 5.9e-8 / 6.0e-8 (k = 4096 1.9e-5 1.5e-5 / 6.0e-8).
+// What bounds it: six bf16 matrix instructions take 3/8 of the time of the fp32 ones they replace; a slab of 128 x 128 x 32 takes
+// 1.3 us with all CUs busy, of which they are 0.75 and the taking apart (104 vector instructions a wave, dealt out between them) 0.4:
+// 196 TFLOP/s at 4096^3 (fp32 instructions 129), with a tangent 146 at 1024 x 3072 x 768 (105).
 // An operand that is infinite or at least 2^104 makes every result that it takes part in a NaN here, and sums of 2^80 (1.2e24) and
 // more, or nearly that when the first parts are rounded up by as much as 2^-8 of them, are infinite: blocks that find a result that
 // is not finite compute theirs again with the fp32 instructions (150 x 145 x 30000 with an infinity in each block: 2.6 instead of
@@ -440,7 +449,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
       for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 
   float4 ra[2][TileA::NI], rb[2][TileB::NI];
-  uint32_t oa[VEC ? TileA::NI : 4 * TileA::NI], ob[VEC ? TileB::NI : 4 * TileB::NI];
+  uint32_t oa[TileA::template PER<VEC> * TileA::NI], ob[TileB::template PER<VEC> * TileB::NI];
   TileA::template offsets<VEC>(oa, p.lda, m0, p.M, t);
   TileB::template offsets<VEC>(ob, p.ldb, n0, p.N, t);
   const int64_t stepA = TA ? BK * p.lda : BK, stepB = TB ? BK : BK * p.ldb;
@@ -485,11 +494,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
       *(HF_LDS u32x2*)(d + q * PL) = (u32x2){x.p[q].x, x.p[q].y};
     }
     if constexpr (decltype(refill_c)::value) {
-      const float* const f = onA ? fa : fb;
-      const uint32_t* const o = onA ? oa : ob;
-      float4& v = onA ? va[onA ? i : 0] : vb[onA ? 0 : i];
-      if constexpr (VEC) v = *(const float4*)(f + o[i]);
-      else v = make_float4(f[o[4 * i]], f[o[4 * i + 1]], f[o[4 * i + 2]], f[o[4 * i + 3]]);
+      if constexpr (onA) va[i] = TileA::template fetch_one<VEC>(fa, oa, i);
+      else vb[i] = TileB::template fetch_one<VEC>(fb, ob, i);
     }
   };
   auto store = [&](auto& va, auto& vb, int s) {
@@ -526,16 +532,18 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
         xb[kk][q][j] = frag(std::integral_constant<bool, BKC>{}, std::integral_constant<int, BN>{}, Bs + q * SB::PLANE, fB, j, kk);
     }
   };
-  // The matrix instructions of k-step kk, whose fragments are in registers, smallest terms first; chunks [C0, C1) of the slab in
+  // The matrix instructions of k-step kk, whose fragments are in registers: the small terms, then the large one; chunks [C0, C1) of the slab in
   // registers (va, vb) are split and stored into stage ds between them.
-  f32x16 sum[TM][TN];
+  f32x16 low[TM][TN], sum[TM][TN];
 #pragma unroll
   for (int i = 0; i < TM; ++i)
 #pragma unroll
     for (int j = 0; j < TN; ++j)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) sum[i][j][r] = 0.f;
-  constexpr int SPLIT_VALU = 26;  // vector instructions that take a chunk apart
+      for (int r = 0; r < 16; ++r) { low[i][j][r] = 0.f; sum[i][j][r] = 0.f; }
+  // Vector instructions that take a chunk apart, and a few addresses where the B side is read row by row (us with 26 / 32: 1024 x 3072 x 768
+  // 100.6 / 98.7, 4096^3 with a tangent 2108 / 2065; A B^T 1024 x 50257 x 768 1314 / 1342).
+  constexpr int SPLIT_VALU = TB ? 26 : 32;
   constexpr int MQ = 6 * TM * TN, CH = NCH / 2, NFRAG = 3 * (TM * (AKC ? 1 : 2) + TN * (BKC ? 1 : 2));
   using I0 = std::integral_constant<int, 0>;
   using I1 = std::integral_constant<int, 1>;
@@ -546,7 +554,8 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     constexpr int PA[6] = {2, 0, 1, 1, 0, 0}, PB[6] = {0, 2, 1, 0, 1, 0};
     static_for<MQ>([&](auto q_c) {
       constexpr int q = decltype(q_c)::value, term = q / (TM * TN), i = q % (TM * TN) / TN, j = q % TN;
-      acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[kk][PA[term]][i], xb[kk][PB[term]][j], acc[i][j], 0, 0, 0);
+      f32x16& to = term == 5 ? acc[i][j] : low[i][j];
+      to = __builtin_amdgcn_mfma_f32_32x32x16_bf16(xa[kk][PA[term]][i], xb[kk][PB[term]][j], to, 0, 0, 0);
       constexpr int c = C0 + q * (C1 - C0) / MQ, cn = C0 + (q + 1) * (C1 - C0) / MQ;
       static_assert(cn - c <= 1, "at most one chunk per matrix instruction");
       if constexpr (cn > c) store_one(va, vb, ds, std::integral_constant<int, c>{}, std::true_type{});
@@ -564,15 +573,15 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     }
     __builtin_amdgcn_sched_barrier(0);
   };
-  // Long sums in two levels: every 16 slabs (512 k of all terms) the running sum goes to another one and starts again, which
-  // keeps the rounding of a sum of 50000 products below that of 1000 in a row.
+  // Long sums in two levels: every 32 slabs (1024 k of all terms) the running sums go to another one and start again, which
+  // keeps the rounding of a sum of 50000 products near that of 1000 in a row.
   auto flush = [&]() {
 #pragma unroll
     for (int i = 0; i < TM; ++i)
 #pragma unroll
       for (int j = 0; j < TN; ++j)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) { sum[i][j][r] += acc[i][j][r]; acc[i][j][r] = 0.f; }
+        for (int r = 0; r < 16; ++r) { sum[i][j][r] += acc[i][j][r] + low[i][j][r]; acc[i][j][r] = 0.f; low[i][j][r] = 0.f; }
   };
   // Slab i, in LDS stage i % 2: the last k-step of the slab before it covers the reads of its first one, so that the barrier
   // between slabs exposes no LDS latency; slab i + 1 goes from registers to the other stage (the last time it is an old one that
@@ -583,7 +592,7 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
     __builtin_amdgcn_sched_barrier(0);
     read_kk(s, I0{});
     multiply(I1{}, I0{}, IH{}, 1 - s, ra[1 - s], rb[1 - s]);
-    if ((i & 15) == 0) flush();
+    if ((i & 31) == 0) flush();
     read_kk(s, I1{});
     multiply(I0{}, IH{}, IN{}, 1 - s, ra[1 - s], rb[1 - s]);
     advance();
@@ -859,10 +868,10 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  (Under klimit the blocks are
   // priced with the whole k, about twice their average: only the tile is chosen there, and all tiles are priced alike.)  A cut
   // costs each block 1500 clocks a 64 x 64 part (partial tile out) and the launch 6000 and 1500 or 10000 a part (sums of small or large ones).
-  // Measured (us; 64 x 64 whole and in its best parts, 128 x 128 the same, 32 x 32, fp32 matrix instructions before): primal
-  // product and tangent 1024x768x768 39 37/2 58 39/3 51, 47; 1024x2304x768 82 - 76 - 123, 118; 1024x3072x768 103 - 102 - 161, 155;
-  // 1024x768x3072 143 110/3 196 94/3 166, 164; 1024x50257x768 1578 - 1263 - 2310, 1936; 1024x768x50257 1974 1578/4 2954 1326/6 -,
-  // 1985; 512x128x128 10 - 16 - 6.6, 6.7; 512x128x512 23 13/6 38 22/6 11.6, 11.5; A^T B 768x3072x1024 86 76/3 73 67/4 103, 111.
+  // Measured (us; 64 x 64 whole and in its best parts, 128 x 128 the same, 32 x 32, chosen): primal product and tangent
+  // 1024x768x768 41 37/2 55 39/2 47, 39; 1024x2304x768 85 - 73 - 114, 73; 1024x3072x768 106 - 101 - 150, 99; 1024x768x3072 124
+  // 109/3 190 94/3 162, 95; 1024x50257x768 1636 - 1291 - 2323, 1305; 1024x768x50257 1996 1638/4 3041 1311/3 3000, 1267; 512x128x128
+  // 11 - 17 - 6.5, 6.4; 512x128x512 25 14/6 39 23/6 11.1, 11.2; A^T B 768x3072x1024 92 83/3 74 73/3 103, 78.
   int cfg = 0, parts = 1;
   double best = 1e300;
   for (int ci = 0; ci < 3; ++ci) {

@@ -1,10 +1,10 @@
 """fp32 products whose operands are taken apart into three bf16 numbers: the edges of their two tiles, aligned and not, against
 the float64 oracle; sums of many products; numbers that round to infinity in bf16.
 
-Tolerance: the parts carry all 24 bits of an operand and the terms left out are below 2^-26 of a product, so what remains is the
-rounding of the sums: runs of at most 16 slabs of six 16-term instructions for 32 of k, added up over the runs: sqrt(192 / 6) 2^-24 of a
-run and sqrt(runs / 6) 2^-24 of their sum, below 5e-7 for a product of 50000; a dozen products between input and result add up in
-quadrature to 2e-6 (the bar of 1e-5 of the other fp32 tests is twenty times what these measure, 2e-6 is four times)."""
+Tolerance: the parts carry all 24 bits of an operand and the terms left out are at most 2^-24 of a product (both mantissas just above 1;
+2^-27.5 on average), so what remains is the rounding of the sums: runs of at most 1024 k in 16-term instructions, added up over the
+runs: sqrt(64 / 6) 2^-24 of a run and sqrt(runs / 6) 2^-24 of their sum, below 3e-7 for a product of 50000; a dozen products between input
+and result, the elementwise passes between them as well, add up in quadrature to less than 2e-6."""
 import numpy as np
 import pytest
 

@@ -112,3 +112,38 @@ def test_operands_of_any_size(tile, scale):
         want = a.double() @ b.double()
         got = fp32_product(a, b, tile, 1)
         assert (got.double() - want).norm() <= 8.4e-7 * want.norm()
+
+
+def _mantissas_that_lose_most():
+    """A number near 1 whose square loses most when the products of a second with a third part are left out: about 2^-24 of it."""
+    import torch
+    x = (1 + 0.02 * torch.rand(1 << 20, dtype=torch.float64, generator=torch.Generator().manual_seed(7))).float()
+    x0 = x.bfloat16().float()
+    x1 = (x - x0).bfloat16().float()
+    lost = (2 * x1 * (x - x0 - x1)).double() / x.double() ** 2
+    assert 0.9 * 2.0 ** -24 < lost.max() < 1.1 * 2.0 ** -24
+    return float(x[lost.argmax()])
+
+
+@pytest.mark.parametrize("kind", ["normal", "near one", "near one, signs", "most lost", "most lost, signs"])
+@pytest.mark.parametrize("K", [16, 64, 128, 512, 1024, 4096])
+@pytest.mark.parametrize("tile", [0, 1])
+def test_parts_add_up_to_no_more_error_than_the_sum(tile, K, kind):
+    """The large products are added 16 at a time, in runs of 1024 k: sqrt(min(K, 1024) / 16 / 6) 2^-24 of rounding in a run (each
+    addition rounds a partial sum that grows like a random walk), sqrt(K / 1024 / 6) 2^-24 where the runs are added, 0.7 2^-24 for the last
+    rounding and the small products, and up to 2^-24 for those left out where every mantissa loses most (2^-27.5 on average)."""
+    import numpy as np
+    import torch
+    from gpu_util import fp32_product
+    g = torch.Generator(device="cuda").manual_seed(K)
+    sign = lambda *s: (torch.randint(0, 2, s, generator=g, device="cuda") * 2 - 1).float()
+    def draw(*s):
+        if kind == "normal":
+            return torch.randn(*s, generator=g, device="cuda")
+        x = 1 + 0.02 * torch.rand(*s, generator=g, device="cuda") if "near" in kind else torch.full(s, _mantissas_that_lose_most(), device="cuda")
+        return x * sign(*s) if "signs" in kind else x
+    A, B = draw(192, K), draw(K, 192)
+    want = A.double() @ B.double()
+    got = fp32_product(A, B, tile, 1)
+    bound = np.sqrt(min(K, 1024) / 96 + K / 6144) + 0.7 + (1.0 if "lost" in kind else 0.0)
+    assert (got.double() - want).norm() <= bound * 2.0 ** -24 * want.norm()
