@@ -36,7 +36,7 @@ struct F32Group {
 };
 
 // One operand's slab of R rows x BK: R * BK / 1024 chunks of four elements per thread, along k (KC) or along the rows.
-template <int R, bool KC, int BK, int NTHR = 256>
+template <int R, bool KC, int BK, int NTHR>
 struct F32Tile {
   static constexpr int NI = R * BK / (4 * NTHR);
   static constexpr int LD = KC ? BK + 4 : R + 8;
@@ -104,31 +104,26 @@ struct F32Tile {
   }
 };
 
-// Four waves of WM x WN; where that covers the tile WK times over, each set of waves multiplies its share of a slab's k
-// and the sums meet in LDS.  VEC: both operands' rows are 16-byte aligned.
-template <int BM, int BN, int BK, int WM, int WN, bool TA, bool TB, bool VEC>
+// 32 x 32 tiles: each of the four waves multiplies its share of a slab's k for the whole tile, and the sums meet in LDS.
+// VEC: both operands' rows are 16-byte aligned.
+template <bool TA, bool TB, bool VEC>
 __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
-  constexpr int WK = 4 / ((BM / WM) * (BN / WN));
-  static_assert((BM / WM) * (BN / WN) * WK == 4 && BK % (16 * WK) == 0, "four waves, pairs of groups of eight k");
-  static_assert(WK == 1 || (WK == 4 && WM == 32 && WN == 32), "k shared by all four waves or by none");
-  using TileA = F32Tile<BM, !TA, BK>;
-  using TileB = F32Tile<BN, TB, BK>;
+  constexpr int BM = 32, BN = 32, BK = 64, WAVES = 4;
+  using TileA = F32Tile<BM, !TA, BK, 256>;
+  using TileB = F32Tile<BN, TB, BK, 256>;
   constexpr int STAGE = TileA::FLOATS + TileB::FLOATS;
   __shared__ __attribute__((aligned(16))) float smem[2 * STAGE];
-  __shared__ int last_block;
   const int t = threadIdx.x, lane = t & 63, wave = t >> 6;
   const int col = lane & 31, half = lane >> 5;
   int g = 0;
   while (g + 1 < gg.n && (int)blockIdx.x >= gg.first[g + 1]) ++g;
   const GemmP& p = gg.g[g];
-  // blocks go round-robin to the 8 XCDs: XCD x takes the x-th run of consecutive tiles, which share operand rows in
-  // its L2 (parts of k outermost: neighbours work on the same k)
-  const int nks = gg.nks[g], nblk = gg.blocks[g] * nks;
+  // blocks go round-robin to the 8 XCDs: XCD x takes the x-th run of consecutive tiles, which share operand rows in its L2
+  const int nblk = gg.blocks[g];
   int b = blockIdx.x - gg.first[g];
   b = (b & 7) * ((nblk + 7) >> 3) + (b >> 3);
   if (b >= nblk) return;
-  const int ks = b / gg.blocks[g], zt = b - ks * gg.blocks[g];
-  const int z = zt / gg.tiles[g], tile = zt - z * gg.tiles[g];
+  const int z = b / gg.tiles[g], tile = b - z * gg.tiles[g];
   const int tiles_m = (p.M + BM - 1) / BM, tiles_n = (p.N + BN - 1) / BN;
   int tm, tn;
   {  // bands of 8 tile rows
@@ -144,20 +139,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
   int kbeg = 0, kend = p.K;
   if (p.klimit == 1) kend = min(p.K, m0 + BM);
   if (p.klimit == 2) kbeg = (m0 / BK) * BK;
-  // whole slabs of all terms, dealt to the parts; the ragged remainder of each term goes to the last part
-  const int nk = (kend - kbeg) / BK, total = nk * p.nterm;
-  const int it0 = (int)((int64_t)total * ks / nks), it1 = (int)((int64_t)total * (ks + 1) / nks);
+  const int nk = (kend - kbeg) / BK, nit = nk * p.nterm;  // whole slabs of a term and of all
 
-  const int wm0 = WK > 1 ? 0 : (wave / (BN / WN)) * WM, wn0 = WK > 1 ? 0 : (wave % (BN / WN)) * WN;
-  constexpr int TM = WM / 32, TN = WN / 32, NG = BK / 8 / WK;
-  const int g0 = WK > 1 ? wave * NG : 0;  // first group of eight k of this wave
-  f32x16 acc[TM][TN];
+  constexpr int NG = BK / 8 / WAVES;
+  const int g0 = wave * NG;  // first group of eight k of this wave
+  f32x16 acc;
 #pragma unroll
-  for (int i = 0; i < TM; ++i)
-#pragma unroll
-    for (int j = 0; j < TN; ++j)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 
   float4 ra[2][TileA::NI], rb[2][TileB::NI];
   uint32_t oa[TileA::template PER<VEC> * TileA::NI], ob[TileB::template PER<VEC> * TileB::NI];
@@ -166,7 +154,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
   const int64_t stepA = TA ? BK * p.lda : BK, stepB = TB ? BK : BK * p.ldb;
   auto base_a = [&](int term, int k0) { return (const float*)p.A[term] + offA + (TA ? (int64_t)k0 * p.lda + m0 : (int64_t)m0 * p.lda + k0); };
   auto base_b = [&](int term, int k0) { return (const float*)p.B[term] + offB + (TB ? (int64_t)n0 * p.ldb + k0 : (int64_t)k0 * p.ldb + n0); };
-  int f_term = nk > 0 ? it0 / nk : 0, f_slab = nk > 0 ? it0 - f_term * nk : 0;
+  int f_term = 0, f_slab = 0;
   const float *fa = nullptr, *fb = nullptr;
   auto fetch = [&](auto& va, auto& vb) {
     TileA::template fetch<VEC>(va, fa, oa);
@@ -184,14 +172,12 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
     TileB::store(vb, smem + s * STAGE + TileA::FLOATS, t);
   };
   // The matrix instructions of the slab in stage s; a group's fragments are read while the group before it is multiplied.
-  float4 xa[2][TM], xb[2][TN];
+  float4 xa[2], xb[2];
   auto read_group = [&](int s, int gk) {
     const float* As = smem + s * STAGE;
     const float* Bs = As + TileA::FLOATS;
-#pragma unroll
-    for (int i = 0; i < TM; ++i) xa[gk & 1][i] = TileA::read(As, wm0 + i * 32 + col, g0 + gk, half);
-#pragma unroll
-    for (int j = 0; j < TN; ++j) xb[gk & 1][j] = TileB::read(Bs, wn0 + j * 32 + col, g0 + gk, half);
+    xa[gk & 1] = TileA::read(As, col, g0 + gk, half);
+    xb[gk & 1] = TileB::read(Bs, col, g0 + gk, half);
   };
   auto multiply = [&](int s) {
     read_group(s, 0);
@@ -201,19 +187,13 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
       __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
       for (int q = 0; q < 4; ++q)
-#pragma unroll
-        for (int i = 0; i < TM; ++i)
-#pragma unroll
-          for (int j = 0; j < TN; ++j)
-            acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(((const float*)&xa[gk & 1][i])[q], ((const float*)&xb[gk & 1][j])[q],
-                                                             acc[i][j], 0, 0, 0);
+        acc = __builtin_amdgcn_mfma_f32_32x32x2f32(((const float*)&xa[gk & 1])[q], ((const float*)&xb[gk & 1])[q], acc, 0, 0, 0);
       __builtin_amdgcn_sched_barrier(0);
     }
   };
-  const int nit = it1 - it0;
   if (nit > 0) {
-    fa = base_a(f_term, kbeg + f_slab * BK);
-    fb = base_b(f_term, kbeg + f_slab * BK);
+    fa = base_a(0, kbeg);
+    fb = base_b(0, kbeg);
     fetch(ra[0], rb[0]);
     if (nit > 1) fetch(ra[1], rb[1]);
     store(ra[0], rb[0], 0);
@@ -244,7 +224,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
       }
     }
   }
-  if (kbeg + nk * BK < kend && ks == nks - 1) {
+  if (kbeg + nk * BK < kend) {
     for (int term = 0; term < p.nterm; ++term) {
       TileA::fetch_tail(ra[0], (const float*)p.A[term] + offA, p.lda, m0, p.M, kbeg + nk * BK, kend, t);
       TileB::fetch_tail(rb[0], (const float*)p.B[term] + offB, p.ldb, n0, p.N, kbeg + nk * BK, kend, t);
@@ -255,90 +235,27 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
     }
   }
 
-  if constexpr (WK > 1) {  // (k is not cut over blocks as well)
-    __syncthreads();
+  __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 16; ++r) smem[(wave * 16 + r) * 64 + lane] = acc[0][0][r];
-    __syncthreads();
-    const int gn = n0 + col;
-    float bsum = 0.f;
-    if (gn < p.N) {
-      if (p.bias) bsum += ((const float*)p.bias)[gn];
-      if (p.bias_t) bsum += p.bias_t[gn];
-    }
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {  // wave w finishes rows 8w + 0..7
-      const int r = wave * 4 + q, gm = m0 + wave * 8 + half * 4 + q;
-      float v = 0.f;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) v += smem[(w * 16 + r) * 64 + lane];
-      if (gm >= p.M || gn >= p.N) continue;
-      const int64_t ci = offC + (int64_t)gm * p.ldc + gn;
-      v = p.alpha * v + bsum;
-      if (p.Cadd) v += p.Cadd[ci];
-      ((float*)p.C)[ci] = v;
-    }
-    return;
-  }
-
-  if (nks > 1) {
-    // partial tiles in accumulator order (thread t of every block of a tile owns the same elements)
-    constexpr int NACC = TM * TN * 16;
-    float* const base = gg.part + ((int64_t)gg.part0[g] + (int64_t)zt * nks) * (BM * BN);
-    float* mine = base + (int64_t)ks * (BM * BN) + t;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r)
-          __hip_atomic_store(mine + ((i * TN + j) * 16 + r) * 256, acc[i][j][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    // The parts are stored and loaded as agent-scope atomics, which pass the XCDs' L2s on their own: once the stores
-    // are acknowledged the counter may follow.  (A fence instead would write back the whole L2 in every block: 580
-    // against 130 us for 1024 x 2304 x 768.)
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    __syncthreads();
-    if (t == 0) {
-      int* cnt = gg.counters + gg.cnt0[g] + zt;
-      const int arrived = __hip_atomic_fetch_add(cnt, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      last_block = arrived == nks - 1;
-      if (arrived == nks - 1) __hip_atomic_store(cnt, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    __syncthreads();
-    if (!last_block) return;
-#pragma unroll
-    for (int i = 0; i < TM; ++i)
-#pragma unroll
-      for (int j = 0; j < TN; ++j)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-    for (int s = 0; s < nks; ++s) {
-      float* src = base + (int64_t)s * (BM * BN) + t;
-#pragma unroll
-      for (int e = 0; e < NACC; ++e)
-        acc[e / (TN * 16)][(e / 16) % TN][e % 16] += __hip_atomic_load(src + e * 256, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-  }
-
-  // accumulator tile: column lane & 31, rows 8*(r/4) + 4*(lane/32) + r%4
-#pragma unroll
-  for (int j = 0; j < TN; ++j) {
-    const int gn = n0 + wn0 + j * 32 + col;
-    if (gn >= p.N) continue;
-    float bsum = 0.f;
+  for (int r = 0; r < 16; ++r) smem[(wave * 16 + r) * 64 + lane] = acc[r];
+  __syncthreads();
+  const int gn = n0 + col;
+  float bsum = 0.f;
+  if (gn < p.N) {
     if (p.bias) bsum += ((const float*)p.bias)[gn];
     if (p.bias_t) bsum += p.bias_t[gn];
+  }
 #pragma unroll
-    for (int i = 0; i < TM; ++i)
+  for (int q = 0; q < 4; ++q) {  // wave w finishes rows 8w + 0..7
+    const int r = wave * 4 + q, gm = m0 + wave * 8 + half * 4 + q;
+    float v = 0.f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int gm = m0 + wm0 + i * 32 + (r >> 2) * 8 + half * 4 + (r & 3);
-        if (gm >= p.M) continue;
-        const int64_t ci = offC + (int64_t)gm * p.ldc + gn;
-        float v = p.alpha * acc[i][j][r] + bsum;
-        if (p.Cadd) v += p.Cadd[ci];
-        ((float*)p.C)[ci] = v;
-      }
+    for (int w = 0; w < WAVES; ++w) v += smem[(w * 16 + r) * 64 + lane];
+    if (gm >= p.M || gn >= p.N) continue;
+    const int64_t ci = offC + (int64_t)gm * p.ldc + gn;
+    v = p.alpha * v + bsum;
+    if (p.Cadd) v += p.Cadd[ci];
+    ((float*)p.C)[ci] = v;
   }
 }
 
@@ -757,18 +674,14 @@ __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2) void gemm_f32_split_
   }
 }
 
-template <int BM, int BN, int BK, int WM, int WN, bool VEC>
-static hipError_t launch_f32_vec(const F32Group& gg, int grid, hipStream_t st) {
+template <bool VEC>
+static hipError_t launch_mfma(const F32Group& gg, int grid, hipStream_t st) {
   const GemmP& p = gg.g[0];
-  if (!p.transA && !p.transB) hipLaunchKernelGGL((gemm_f32_mfma_kernel<BM, BN, BK, WM, WN, false, false, VEC>), dim3(grid), dim3(256), 0, st, gg);
-  else if (!p.transA) hipLaunchKernelGGL((gemm_f32_mfma_kernel<BM, BN, BK, WM, WN, false, true, VEC>), dim3(grid), dim3(256), 0, st, gg);
-  else if (!p.transB) hipLaunchKernelGGL((gemm_f32_mfma_kernel<BM, BN, BK, WM, WN, true, false, VEC>), dim3(grid), dim3(256), 0, st, gg);
-  else hipLaunchKernelGGL((gemm_f32_mfma_kernel<BM, BN, BK, WM, WN, true, true, VEC>), dim3(grid), dim3(256), 0, st, gg);
+  if (!p.transA && !p.transB) hipLaunchKernelGGL((gemm_f32_mfma_kernel<false, false, VEC>), dim3(grid), dim3(256), 0, st, gg);
+  else if (!p.transA) hipLaunchKernelGGL((gemm_f32_mfma_kernel<false, true, VEC>), dim3(grid), dim3(256), 0, st, gg);
+  else if (!p.transB) hipLaunchKernelGGL((gemm_f32_mfma_kernel<true, false, VEC>), dim3(grid), dim3(256), 0, st, gg);
+  else hipLaunchKernelGGL((gemm_f32_mfma_kernel<true, true, VEC>), dim3(grid), dim3(256), 0, st, gg);
   return hipGetLastError();
-}
-template <int BM, int BN, int BK, int WM, int WN>
-static hipError_t launch_f32_cfg(const F32Group& gg, int grid, bool vec, hipStream_t st) {
-  return vec ? launch_f32_vec<BM, BN, BK, WM, WN, true>(gg, grid, st) : launch_f32_vec<BM, BN, BK, WM, WN, false>(gg, grid, st);
 }
 
 template <int BM, int BN, int WM, int WN, bool TA, bool TB, bool VEC>
@@ -927,7 +840,7 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   for (int i = 0; i < n; ++i) vec = vec && ps[i].vecA && ps[i].vecB;
   if (cfg == 0) return launch_split<64, 64, 32, 32>(gg, (int)first, vec, st);
   if (cfg == 1) return launch_split<128, 128, 64, 32>(gg, (int)first, vec, st);
-  return launch_f32_cfg<32, 32, 64, 32, 32>(gg, (int)first, vec, st);
+  return vec ? launch_mfma<true>(gg, (int)first, st) : launch_mfma<false>(gg, (int)first, st);
 }
 
 }  // namespace hf
