@@ -765,17 +765,16 @@ static double f32_estimate(const int64_t* cnt, const double* len, int n, const F
   return worst;
 }
 
-// All products have the same transposes and nb batch entries.  ws / counters nullptr: k is never cut.
-hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int64_t ws_elems, int* counters, int force_cfg,
-                                 int force_ks, hipStream_t st) {
-  if (n < 1 || n > F32_GROUP_MAX) return hipErrorInvalidValue;
+// The choice of tile and parts: fills gg but for its pointers, with products in launch order (order[k]: position in ps).  Returns the tile's
+// index, -1 for products that no launch takes.  scratch: there is a workspace (ws_elems floats) and counters, so k may be cut.
+static int plan_group(const GemmP* ps, int n, int nb, bool scratch, int64_t ws_elems, int force_cfg, int force_ks, F32Group& gg, int* order) {
+  if (n < 1 || n > F32_GROUP_MAX) return -1;
   for (int i = 1; i < n; ++i)
-    if (ps[i].transA != ps[0].transA || ps[i].transB != ps[0].transB) return hipErrorInvalidValue;
+    if (ps[i].transA != ps[0].transA || ps[i].transB != ps[0].transB) return -1;
   auto tiles_of = [&](const GemmP& p, const F32Cfg& c) {
     return ((int64_t)p.M + c.bm - 1) / c.bm * (((int64_t)p.N + c.bn - 1) / c.bn);
   };
   auto slabs_of = [&](const GemmP& p, const F32Cfg& c) { return (int64_t)p.nterm * ((p.K + c.bk - 1) / c.bk); };
-  int order[F32_GROUP_MAX];
   for (int i = 0; i < n; ++i) order[i] = i;
   std::stable_sort(order, order + n, [&](int a, int b) { return (int64_t)ps[a].nterm * ps[a].K > (int64_t)ps[b].nterm * ps[b].K; });
   // Tile and parts of k (the same for all products): the pair with the shortest estimated launch.  (Under klimit the blocks are
@@ -790,7 +789,7 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
   for (int ci = 0; ci < 3; ++ci) {
     if (force_cfg >= 0 && ci != force_cfg) continue;
     const F32Cfg& c = kF32Cfg[ci];
-    const bool cut = ci != 2 && ws && counters && !ps[0].klimit;
+    const bool cut = ci != 2 && scratch && !ps[0].klimit;
     const double tile = c.bm * c.bn / 4096.;
     int64_t all = 0;
     for (int i = 0; i < n; ++i) all += tiles_of(ps[i], c) * nb;
@@ -810,7 +809,7 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
     }
   }
   const F32Cfg& c = kF32Cfg[cfg];
-  F32Group gg = {};
+  gg = {};
   gg.n = n;
   int64_t first = 0, part = 0, cnt = 0;
   for (int k = 0; k < n; ++k) {
@@ -818,7 +817,7 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
     const GemmP& p = gg.g[k];
     const int64_t tiles = tiles_of(p, c), blocks = tiles * nb;
     int64_t nks = 1;
-    if (cfg != 2 && ws && counters && !p.klimit) {
+    if (cfg != 2 && scratch && !p.klimit) {
       nks = force_ks > 0 ? force_ks : parts;
       nks = std::max<int64_t>(1, std::min<int64_t>(nks, p.nterm * (p.K / c.bk)));
       while (nks > 1 && ((part + blocks * nks) * c.bm * c.bn > ws_elems || cnt + blocks > F32_COUNTERS)) --nks;
@@ -831,16 +830,35 @@ hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int6
     if (nks > 1) { part += blocks * nks; cnt += blocks; }
     gg.first[k] = (int)first;
     first += (blocks * nks + 7) / 8 * 8;
-    if (first > (int64_t)1 << 30) return hipErrorInvalidValue;
+    if (first > (int64_t)1 << 30) return -1;
   }
   gg.first[n] = (int)first;
+  return cfg;
+}
+
+int f32_plan(const GemmP* ps, int n, int nb, int64_t ws_elems, int* parts) {
+  F32Group gg;
+  int order[F32_GROUP_MAX];
+  const int cfg = plan_group(ps, n, nb, ws_elems > 0, ws_elems, -1, 0, gg, order);
+  for (int k = 0; cfg >= 0 && k < n; ++k) parts[order[k]] = gg.nks[k];
+  return cfg;
+}
+
+// All products have the same transposes and nb batch entries.  ws / counters nullptr: k is never cut.
+hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int64_t ws_elems, int* counters, int force_cfg,
+                                 int force_ks, hipStream_t st) {
+  F32Group gg;
+  int order[F32_GROUP_MAX];
+  const int cfg = plan_group(ps, n, nb, ws && counters, ws_elems, force_cfg, force_ks, gg, order);
+  if (cfg < 0) return hipErrorInvalidValue;
   gg.part = ws;
   gg.counters = counters;
+  const int grid = gg.first[n];
   bool vec = true;
   for (int i = 0; i < n; ++i) vec = vec && ps[i].vecA && ps[i].vecB;
-  if (cfg == 0) return launch_split<64, 64, 32, 32>(gg, (int)first, vec, st);
-  if (cfg == 1) return launch_split<128, 128, 64, 32>(gg, (int)first, vec, st);
-  return vec ? launch_mfma<true>(gg, (int)first, st) : launch_mfma<false>(gg, (int)first, st);
+  if (cfg == 0) return launch_split<64, 64, 32, 32>(gg, grid, vec, st);
+  if (cfg == 1) return launch_split<128, 128, 64, 32>(gg, grid, vec, st);
+  return vec ? launch_mfma<true>(gg, grid, st) : launch_mfma<false>(gg, grid, st);
 }
 
 }  // namespace hf

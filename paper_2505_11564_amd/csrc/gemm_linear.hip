@@ -35,6 +35,51 @@ static hipError_t launch_linear_tn(int cfg, const LinP& p, int nb, int ks, hipSt
   }
 }
 
+// Tile (index of the table) and parts of k for a product with its tangent; -1: two products in one launch are the better choice.
+int linear_plan(const Gemm& g, int* parts) {
+  const int nb = g.nb1 * g.nb2;
+  const int64_t mn = (int64_t)g.M * g.N;
+  const int nt = 4 + (g.A[1] != nullptr) + (g.A[2] != nullptr);  // operand tiles
+  // Tile and k-split: the shortest estimate, rounds of one block per CU times a block's length (blocks of a round that leaves
+  // CUs idle run up to 15 % faster).  A block's length is its slabs, 3 us of start and its results (with addends) at 20 bytes a
+  // ns, a CU's share of the memory rate; the parts of a cut k are then added by another launch at 4.5 TB/s.  Measured / estimated
+  // (us): 512 x 4096 x 11008 64 x 128 whole 167 / 126, 128 x 128 in two parts 138 / 124, 128 x 256 in four 142 / 141;
+  // 4096 x 2048 x 2048 128 x 256 98 / 106, 128 x 128 105 / 107; 4096 x 3072 x 768 128 x 192 54 / 55, 128 x 128 60 / 61;
+  // 4096 x 768 x 3072 128 x 96 62 / 62; 2048 x 768 x 3072 64 x 128 35 / 40, 128 x 96 in two parts 44 / 44;
+  // 999 x 768 x 3072 64 x 64 24 / 29, 128 x 64 34 / 43.
+  int cfg = -1;
+  int& ks = *parts;
+  ks = 1;
+  double best = 1e300;
+  for (int c = 0; c < LIN_CFGS; ++c) {
+    if (kLin[c].slab_us[nt - 4] == 0.) continue;
+    if (g.transA && c > LIN_64x128) continue;
+    if (g.force_cfg >= 0 && c != g.force_cfg) continue;
+    const LinCfg& lc = kLin[c];
+    const int64_t tiles = ((int64_t)g.M + lc.bm - 1) / lc.bm * (((int64_t)g.N + lc.bn - 1) / lc.bn) * nb;
+    const double slabs = (g.K + 63) / 64 * (g.klimit ? 0.5 : 1.) * lc.slab_us[nt - 4];
+    const double out_us = (double)lc.bm * lc.bn * ((g.out_bf16 ? 4 : 8) + (g.Cadd ? 4 : 0) + (g.Cadd_t ? 4 : 0)) / 20e3;
+    const int max_ks = g.ws && nb == 1 && !g.klimit && !g.skip_upper && ((uintptr_t)g.ws % 16) == 0 ? std::min(8, g.K / 512) : 1;
+    for (int k = 1; k == 1 || (k <= max_ks && 2 * k * mn <= g.ws_elems); ++k) {
+      if (g.force_ks > 0 && k != std::min(g.force_ks, max_ks)) continue;
+      const double full = (double)(tiles * k / 256), part = (double)(tiles * k % 256) / 256;
+      const double blocks = full + (part > 0. ? 0.85 + 0.15 * part : 0.);
+      const double us = k == 1 ? blocks * (slabs + 3. + out_us)
+                               : blocks * (slabs / k + 3. + lc.bm * lc.bn * 8 / 20e3) + 6. + (double)mn * (8 * k + 8) / 4.5e6;
+      if (us < best) { best = us; cfg = c; ks = k; }
+    }
+  }
+  // Many rounds: 256 x 256 tiles of the two products in one launch load as little per product and spend their epilogues on
+  // fewer, larger tiles.  Measured (us, this kernel / those): 4096 x 50257 x 768 1117 / 1080, 4096 x 8192 x 2048 346 / 341,
+  // 4096 x 6144 x 2048 254 / 273, 4096 x 2048 x 8192 346 / 381, 4096 x 2048 x 2048 100 / 118; with A_lo both products have
+  // two terms, so that two rounds come out even: 512 x 32000 x 4096 480 / 447.
+  const int64_t pair_blocks = 2 * gemm_tiles256(g.M, g.N);
+  if (g.force_cfg < 0 && nb == 1 && !g.klimit && !g.skip_upper && !g.transA && ks == 1 && g.K >= 512 && pair_blocks >= (nt > 4 ? 450 : 1024) &&
+      pair_blocks * 100 >= (pair_blocks + 255) / 256 * 256 * 85)
+    return -1;
+  return cfg;
+}
+
 // g.Ct != nullptr, operands on the fast path.  hipErrorNotSupported: the description does not fit, or two single-output
 // products are the better choice; the caller then issues those.
 hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st) {
@@ -50,6 +95,11 @@ hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st) {
   if (p.Blo && !p.Alo) return hipErrorNotSupported;
   const int nt = p.Blo ? 6 : p.Alo ? 5 : 4;
   if (g.transA && nt != 4) return hipErrorNotSupported;
+  int ks;
+  const int cfg = linear_plan(g, &ks);
+  if (cfg < 0) return hipErrorNotSupported;
+  const int nb = g.nb1 * g.nb2;
+  const int64_t mn = (int64_t)g.M * g.N;
   p.C = g.C; p.Ct = g.Ct; p.Clo = g.C_lo; p.Cadd = g.Cadd; p.Cadd_t = g.Cadd_t; p.bias = g.bias; p.bias_t = g.bias_t;
   p.M = g.M; p.N = g.N; p.K = g.K; p.lda = g.lda; p.ldb = g.ldb; p.ldc = g.ldc; p.nb2 = g.nb2; p.divB = g.divB > 0 ? g.divB : 1;
   p.sA1 = g.sA1; p.sA2 = g.sA2; p.sB1 = g.sB1; p.sB2 = g.sB2; p.sC1 = g.sC1; p.sC2 = g.sC2;
@@ -59,44 +109,6 @@ hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st) {
     auto al = [&](const void* x) { return x == nullptr || ((uintptr_t)x % 16) == 0; };
     p.vec = al(g.C) && al(g.Ct) && al(g.C_lo) && al(g.Cadd) && al(g.Cadd_t) && g.ldc % q == 0 && g.sC1 % q == 0 && g.sC2 % q == 0;
   }
-  const int nb = g.nb1 * g.nb2;
-  const int64_t mn = (int64_t)g.M * g.N;
-  // Tile and k-split: the shortest estimate, rounds of one block per CU times a block's length (blocks of a round that leaves
-  // CUs idle run up to 15 % faster).  A block's length is its slabs, 3 us of start and its results (with addends) at 20 bytes a
-  // ns, a CU's share of the memory rate; the parts of a cut k are then added by another launch at 4.5 TB/s.  Measured / estimated
-  // (us): 512 x 4096 x 11008 64 x 128 whole 167 / 126, 128 x 128 in two parts 138 / 124, 128 x 256 in four 142 / 141;
-  // 4096 x 2048 x 2048 128 x 256 98 / 106, 128 x 128 105 / 107; 4096 x 3072 x 768 128 x 192 54 / 55, 128 x 128 60 / 61;
-  // 4096 x 768 x 3072 128 x 96 62 / 62; 2048 x 768 x 3072 64 x 128 35 / 40, 128 x 96 in two parts 44 / 44;
-  // 999 x 768 x 3072 64 x 64 24 / 29, 128 x 64 34 / 43.
-  int cfg = -1, ks = 1;
-  double best = 1e300;
-  for (int c = 0; c < LIN_CFGS; ++c) {
-    if (kLin[c].slab_us[nt - 4] == 0.) continue;
-    if (g.transA && c > LIN_64x128) continue;
-    if (g.force_cfg >= 0 && c != g.force_cfg) continue;
-    const LinCfg& lc = kLin[c];
-    const int64_t tiles = ((int64_t)g.M + lc.bm - 1) / lc.bm * (((int64_t)g.N + lc.bn - 1) / lc.bn) * nb;
-    const double slabs = (g.K + 63) / 64 * (g.klimit ? 0.5 : 1.) * lc.slab_us[nt - 4];
-    const double out_us = (double)lc.bm * lc.bn * ((g.out_bf16 ? 4 : 8) + (g.Cadd ? 4 : 0) + (g.Cadd_t ? 4 : 0)) / 20e3;
-    const int max_ks = g.ws && nb == 1 && !g.klimit && !g.skip_upper && ((uintptr_t)g.ws % 16) == 0 ? std::min(8, g.K / 512) : 1;
-    for (int k = 1; k == 1 || (k <= max_ks && 2 * k * mn <= g.ws_elems); ++k) {
-      if (g.force_ks > 0 && k != g.force_ks && k < max_ks) continue;
-      const double full = (double)(tiles * k / 256), part = (double)(tiles * k % 256) / 256;
-      const double blocks = full + (part > 0. ? 0.85 + 0.15 * part : 0.);
-      const double us = k == 1 ? blocks * (slabs + 3. + out_us)
-                               : blocks * (slabs / k + 3. + lc.bm * lc.bn * 8 / 20e3) + 6. + (double)mn * (8 * k + 8) / 4.5e6;
-      if (us < best) { best = us; cfg = c; ks = k; }
-    }
-  }
-  if (cfg < 0) return hipErrorNotSupported;
-  // Many rounds: 256 x 256 tiles of the two products in one launch load as little per product and spend their epilogues on
-  // fewer, larger tiles.  Measured (us, this kernel / those): 4096 x 50257 x 768 1117 / 1080, 4096 x 8192 x 2048 346 / 341,
-  // 4096 x 6144 x 2048 254 / 273, 4096 x 2048 x 8192 346 / 381, 4096 x 2048 x 2048 100 / 118; with A_lo both products have
-  // two terms, so that two rounds come out even: 512 x 32000 x 4096 480 / 447.
-  const int64_t pair_blocks = 2 * gemm_tiles256(g.M, g.N);
-  if (g.force_cfg < 0 && nb == 1 && !g.klimit && !g.skip_upper && !g.transA && ks == 1 && g.K >= 512 && pair_blocks >= (nt > 4 ? 450 : 1024) &&
-      pair_blocks * 100 >= (pair_blocks + 255) / 256 * 256 * 85)
-    return hipErrorNotSupported;
   if (ks > 1) {
     p.C = g.ws; p.Ct = g.ws + ks * mn; p.Clo = nullptr; p.Cadd = nullptr; p.Cadd_t = nullptr; p.bias = nullptr; p.bias_t = nullptr;
     p.out_bf16 = 0; p.ldc = g.N; p.sCk = mn; p.vec = g.N % 4 == 0 ? 1 : 0;

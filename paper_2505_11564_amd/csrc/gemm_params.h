@@ -44,5 +44,7 @@ hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_
 constexpr int F32_GROUP_MAX = 4;
 hipError_t launch_gemm_f32_group(const GemmP* ps, int n, int nb, float* ws, int64_t ws_elems, int* counters, int force_cfg,
                                  int force_ks, hipStream_t st);
+// Its choice for these products (no device call): tile 0: 64 x 64, 1: 128 x 128, 2: 32 x 32, and each one's parts of k.
+int f32_plan(const GemmP* ps, int n, int nb, int64_t ws_elems, int* parts);
 
 }  // namespace hf

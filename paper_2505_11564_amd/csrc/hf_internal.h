@@ -115,6 +115,7 @@ enum { EPI_NONE = 0, EPI_FWD_STATS = 1, EPI_FWD_SOFTMAX = 2, EPI_BWD_STATS = 3, 
 hipError_t launch_gemm(const Gemm& g, hipStream_t st);
 hipError_t launch_gemm_dual(const Gemm& g, hipStream_t st);    // attention epilogues; bf16, aligned operands only
 hipError_t launch_gemm_linear(const Gemm& g, hipStream_t st);  // dual output without epilogue; bf16, aligned operands only
+int linear_plan(const Gemm& g, int* parts);                    // its tile and parts of k (no device call)
 // gs[0..n): single-output products whose results are already zero (c_zeroed) or are added to
 // (Cadd == C); launched as one grid where that is faster, else in turn.
 hipError_t launch_gemm_group(const Gemm* gs, int n, hipStream_t st);

@@ -1,4 +1,6 @@
-// One matrix product as the engine launches it, behind a C entry: what the tests of single products call.  Not part of the API.
+// One matrix product as the engine launches it, and the launchers' choices, behind C entries: what the tests of single products call.
+// Not part of the API.
+#include "gemm_params.h"
 #include "hf_internal.h"
 
 // ptr: A[3], B[3], C, C_lo, Cadd, At, Bt, Ct, Cadd_t, ws, counters (device memory; nullptr where absent).
@@ -21,4 +23,32 @@ extern "C" __attribute__((visibility("default"))) int hf_internal_product(void* 
   g.alpha = alpha;
   if (g.lda < (g.transA ? g.M : g.K) || g.ldb < (g.transB ? g.K : g.N) || g.ldc < g.N) return (int)hipErrorInvalidValue;
   return (int)hf::launch_gemm(g, (hipStream_t)stream);
+}
+
+// Tile and parts of k of a bf16 product with its tangent: M, N, K, transA, transB, low-order terms (0, 1, 2), out_bf16, addends (0, 1),
+// elements of ws.  Returns tile + 16 parts, -1 for two products of 256 x 256 tiles in one launch.
+extern "C" __attribute__((visibility("default"))) int hf_internal_linear_plan(const int64_t* num) {
+  static float none;
+  hf::Gemm g;
+  g.M = (int)num[0]; g.N = (int)num[1]; g.K = (int)num[2];
+  g.transA = (int)num[3]; g.transB = (int)num[4];
+  g.A[0] = &none;
+  for (int i = 0; i < num[5] && i < 2; ++i) g.A[1 + i] = &none;
+  g.in_bf16 = 1; g.out_bf16 = (int)num[6];
+  if (num[7]) g.Cadd = g.Cadd_t = &none;
+  g.ws_elems = num[8];
+  if (num[8] > 0) g.ws = (float*)(uintptr_t)4096;  // (aligned; only looked at)
+  int parts;
+  const int tile = hf::linear_plan(g, &parts);
+  return tile < 0 ? -1 : tile + 16 * parts;
+}
+
+// Tile of n fp32 products launched together (M, N, K, terms of each in num), and the parts of each one's k.
+extern "C" __attribute__((visibility("default"))) int hf_internal_f32_plan(const int64_t* num, int n, int64_t ws_elems, int* parts) {
+  if (n < 1 || n > hf::F32_GROUP_MAX) return -1;
+  hf::GemmP ps[hf::F32_GROUP_MAX] = {};
+  for (int i = 0; i < n; ++i) {
+    ps[i].M = (int)num[4 * i]; ps[i].N = (int)num[4 * i + 1]; ps[i].K = (int)num[4 * i + 2]; ps[i].nterm = (int)num[4 * i + 3];
+  }
+  return hf::f32_plan(ps, n, 1, ws_elems, parts);
 }

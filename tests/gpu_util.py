@@ -105,3 +105,36 @@ def fp32_product(A, B, tile=-1, parts=0, At=None, Bt=None):
     assert hf.lib().hf_internal_product(ptr, num, ctypes.c_float(1.0), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
     torch.cuda.synchronize()
     return tuple(C) if dual else C[0]
+
+
+def bf16_product(A, B, At, Bt, A_lo=None, B_lo=None, add=None, add_t=None, bf16_out=False, tile=-1, parts=0):
+    """C = A B + A_lo B + A B_lo + add and C_t = At B + A Bt + add_t of bf16 device tensors as the engine launches them, layouts as in
+    fp32_product; bf16_out: (C, C_lo, C_t) in bf16, else (C, C_t) in fp32.  tile: index in the launcher's table."""
+    import ctypes
+    M, K = A.shape
+    N = B.shape[1]
+    def layout(x):
+        return (0, x.stride(0)) if x.stride(1) == 1 else (1, x.stride(1))
+    (ta, lda), (tb, ldb) = layout(A), layout(B)
+    for x, l in ((At, (ta, lda)), (A_lo, (ta, lda)), (Bt, (tb, ldb)), (B_lo, (tb, ldb))):
+        assert x is None or layout(x) == l
+    ldc = (N + 7) // 8 * 8
+    dt = torch.bfloat16 if bf16_out else torch.float32
+    C = [torch.full((M, ldc), float("nan"), dtype=dt, device="cuda") for _ in range(3 if bf16_out else 2)]
+    ws = torch.empty(1 << 24, device="cuda")
+    ptr = (ctypes.c_void_p * 15)()
+    ptr[0], ptr[3], ptr[9], ptr[10] = A.data_ptr(), B.data_ptr(), At.data_ptr(), Bt.data_ptr()
+    lo = [(a, b) for a, b in ((A_lo, B), (A, B_lo)) if a is not None and b is not None]
+    for i, (a, b) in enumerate(lo):
+        ptr[1 + i], ptr[4 + i] = a.data_ptr(), b.data_ptr()
+    ptr[6], ptr[11] = C[0].data_ptr(), C[-1].data_ptr()
+    if bf16_out:
+        ptr[7] = C[1].data_ptr()
+    elif add is not None:
+        assert add.stride(0) == add_t.stride(0) == ldc
+        ptr[8], ptr[12] = add.data_ptr(), add_t.data_ptr()
+    ptr[13] = ws.data_ptr()
+    num = (ctypes.c_int64 * 14)(M, N, K, lda, ldb, ldc, ta, tb, 1, int(bf16_out), 0, ws.numel(), tile, parts)
+    assert hf.lib().hf_internal_product(ptr, num, ctypes.c_float(1.0), ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)) == 0
+    torch.cuda.synchronize()
+    return tuple(c[:, :N] for c in C)

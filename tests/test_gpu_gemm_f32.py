@@ -14,11 +14,11 @@ from oracle import models as om
 pytestmark = pytest.mark.gpu
 
 SHAPES = {
-    # ragged last rows and columns: k is cut into parts, also with a ragged last slab
+    # ragged last rows and columns: k is cut into parts on both larger tiles, also with a ragged last slab
     "cut": dict(model=si._gpt(1, 520, 4, 2084, 101, 500), batch=2, tokens="zipf"),
     # no row of any operand is 16-byte aligned
     "unaligned": dict(model=si._gpt(1, 261, 9, 1031, 103, 333), batch=3, tokens="zipf"),
-    # thousands of 64 x 64 tiles, and 128 x 128 tiles with k in parts, ragged in both directions
+    # thousands of 64 x 64 tiles, and 128 x 128 tiles with k whole, ragged in both directions
     "large": dict(model=si._gpt(1, 260, 4, 4100, 97, 515), batch=4, tokens="zipf"),
     # so many tiles that the 128 x 128 one is taken with k whole, ragged in both directions: neither and B transposed,
     "whole": dict(model=si._gpt(1, 132, 3, 10260, 97, 515), batch=4, tokens="zipf"),

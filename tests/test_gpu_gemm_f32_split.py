@@ -20,6 +20,7 @@ SHAPES = {
     "large_unaligned": (si._gpt(1, 517, 11, 2071, 1003, 261), 4),
     # 64 x 64 tiles whole and in parts
     "middle": (si._gpt(2, 324, 3, 1300, 515, 131), 3),
+    # in parts, no row aligned
     "middle_unaligned": (si._llama(1, 330, 3, 1309, 513, 131, n_kv=1), 3),
 }
 

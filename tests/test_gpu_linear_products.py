@@ -1,5 +1,6 @@
 """bf16 product-rule products (a product and its tangent in one launch) at each tile the launcher chooses from, with k whole and
-in parts, ragged in rows, columns and k, through whole Hessian-vector products against the float64 oracle.
+in parts, ragged in rows, columns and k, through whole Hessian-vector products against the float64 oracle.  (test_product_plans_cpu.py
+holds the launcher to the tiles named here.)
 
 Tolerance 2e-2, the bound of bf16 products everywhere (operands rounded to 2^-9), also for every parameter tensor's block on its
 own where it carries more than 1e-6 of the whole: a wrong tile of one product is a tenth of some block."""
@@ -13,7 +14,7 @@ pytestmark = pytest.mark.gpu
 
 # model, batch: tiles (and parts of k) of its layers' products
 SHAPES = {
-    # 128 x 96, 64 x 64 whole and in two parts, 128 x 256, 64 x 128 in two parts
+    # 128 x 96, 64 x 64, 128 x 256, 64 x 128 in two parts
     "wide": (si._gpt(1, 1024, 16, 8200, 97, 385), 2),
     # 64 x 128, 128 x 128, 128 x 64 in four parts
     "middle": (si._gpt(1, 392, 7, 3080, 515, 515), 2),
