@@ -42,10 +42,11 @@ int linear_plan(const Gemm& g, int* parts) {
   const int nt = 4 + (g.A[1] != nullptr) + (g.A[2] != nullptr);  // operand tiles
   // Tile and k-split: the shortest estimate, rounds of one block per CU times a block's length (blocks of a round that leaves
   // CUs idle run up to 15 % faster).  A block's length is its slabs, 3 us of start and its results (with addends) at 20 bytes a
-  // ns, a CU's share of the memory rate; the parts of a cut k are then added by another launch at 4.5 TB/s.  Measured / estimated
-  // (us): 512 x 4096 x 11008 64 x 128 whole 167 / 126, 128 x 128 in two parts 138 / 124, 128 x 256 in four 142 / 141;
+  // ns, a CU's share of the memory rate; the parts of a cut k are then added by another launch, 6 us and 4.5 TB/s.  (The 6 us decide
+  // for 92 of 690 shapes of 256 to 4096 tokens and widths 256 to 4096: with 3 us those take 5.5 % longer, with 9 us 1.8 %.)  Measured /
+  // estimated (us): 512 x 4096 x 11008 64 x 128 whole 164 / 126, 128 x 128 in two parts 140 / 127, 128 x 256 in four 142 / 144;
   // 4096 x 2048 x 2048 128 x 256 98 / 106, 128 x 128 105 / 107; 4096 x 3072 x 768 128 x 192 54 / 55, 128 x 128 60 / 61;
-  // 4096 x 768 x 3072 128 x 96 62 / 62; 2048 x 768 x 3072 64 x 128 35 / 40, 128 x 96 in two parts 44 / 44;
+  // 4096 x 768 x 3072 128 x 96 62 / 62; 2048 x 768 x 3072 64 x 128 35 / 40, 128 x 96 in two parts 44 / 47;
   // 999 x 768 x 3072 64 x 64 24 / 29, 128 x 64 34 / 43.
   int cfg = -1;
   int& ks = *parts;
@@ -71,10 +72,13 @@ int linear_plan(const Gemm& g, int* parts) {
   }
   // Many rounds: 256 x 256 tiles of the two products in one launch load as little per product and spend their epilogues on
   // fewer, larger tiles.  Measured (us, this kernel / those): 4096 x 50257 x 768 1117 / 1080, 4096 x 8192 x 2048 346 / 341,
-  // 4096 x 6144 x 2048 254 / 273, 4096 x 2048 x 8192 346 / 381, 4096 x 2048 x 2048 100 / 118; with A_lo both products have
-  // two terms, so that two rounds come out even: 512 x 32000 x 4096 480 / 447.
+  // 4096 x 6144 x 2048 254 / 273, 4096 x 2048 x 8192 346 / 381, 4096 x 2048 x 2048 100 / 118.  With A_lo both products have two
+  // terms, so that rounds come out even, from the first full one on: one round (256 blocks) 2048 x 4096 x 768 60 / 53, x 1024 64 / 65,
+  // x 4096 232 / 217, x 11008 615 / 573, 4096 x 2048 x 2048 120 / 117, 512 x 16384 x 1024 68 / 65; two rounds (from 448 blocks) 512 x 28672
+  // x 768 124 / 100, x 4096 483 / 410, 1024 x 14336 x 2048 242 / 206, 4096 x 3584 x 512 80 / 73, 512 x 32000 x 4096 491 / 432; three
+  // (688) 2048 x 11008 x 4096 604 / 591; unevenly filled rounds lose (512 x 25600 x 4096 425 / 514, 2048 x 6144 x 2048 172 / 243).
   const int64_t pair_blocks = 2 * gemm_tiles256(g.M, g.N);
-  if (g.force_cfg < 0 && nb == 1 && !g.klimit && !g.skip_upper && !g.transA && ks == 1 && g.K >= 512 && pair_blocks >= (nt > 4 ? 450 : 1024) &&
+  if (g.force_cfg < 0 && nb == 1 && !g.klimit && !g.skip_upper && !g.transA && ks == 1 && g.K >= 512 && pair_blocks >= (nt > 4 ? 256 : 1024) &&
       pair_blocks * 100 >= (pair_blocks + 255) / 256 * 256 * 85)
     return -1;
   return cfg;

@@ -48,3 +48,19 @@ def test_product_and_tangent(tile, nt, trans, K, parts, bf16_out):
         pairs = [(d(got[0]), want + d(add[:, :N]), 2e-6), (d(got[1]), want_t + d(add_t[:, :N]), 2e-6)]
     for g, w, tol in pairs:
         assert (g - w).norm() <= tol * w.norm()
+
+
+@pytest.mark.parametrize("M,N", [(512, 16384), (500, 16300), (1900, 3960), (512, 28672)])
+def test_low_order_halves_in_even_rounds_of_large_tiles(M, N):
+    """One and two rounds of 256 x 256 tiles: the product with its low-order half and the tangent as two products of one launch."""
+    import torch
+    from gpu_util import bf16_product
+    from test_product_plans_cpu import _linear
+    K = 520
+    assert _linear(M, N, K, 0, lo=1) == ("pair", 1)
+    A, At, A_lo = (_operand(M, K, False, s, c) for s, c in ((1, 1.0), (2, 1.0), (3, 2.0 ** -9)))
+    B, Bt = (_operand(K, N, False, s) for s in (4, 5))
+    got = bf16_product(A, B, At, Bt, A_lo)
+    d = lambda x: x.double()
+    for g, w in zip(got, ((d(A) + d(A_lo)) @ d(B), d(At) @ d(B) + d(A) @ d(Bt))):
+        assert (d(g) - w).norm() <= 2e-6 * w.norm()
