@@ -175,7 +175,9 @@ hipError_t launch_attn_bwd(const AttnP& p, hipStream_t st);  // dQ, dK, dV with 
 // probe.hip: Hessian-column statistics
 constexpr int CS_MAX_THRESHOLDS = 16, CS_MAX_BINS = 256, CS_STATS_WORDS = 32 + CS_MAX_BINS, CS_COPIES = 8, CS_ARRAY_WORDS = CS_STATS_WORDS * (CS_COPIES + 1);  // the copies, then room for their sums
 struct ColThresholds { float t[CS_MAX_THRESHOLDS]; };
-constexpr int64_t GEMM_WS_ELEMS = 16ll << 20;  // 64 MiB of fp32: two results x up to 8 splits of a 512 x 2048 product, 2 x 2 of 512 x 4096
+// Scratch of every transformer context, 64 MiB: two results x up to 8 splits of a 512 x 2048 product, 2 x 2 of 512 x 4096; in fp32 the partial
+// tiles of a cut k (a head of 1024 x 768 in 10 parts; half of it had kept such products at 5).
+constexpr int64_t GEMM_WS_ELEMS = 16ll << 20;
 // One result of a k-split dual-output product: C = sum over the splits' partial sums (each
 // M x N, row stride N, consecutive splits M*N apart) + bias + Cadd, written as fp32 or as bf16
 // with an optional low-order half; rows of C / Cadd / C_lo have stride ldc.
