@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256, 2) void gemm_f32_mfma_kernel(F32Group gg) {
 // 3.1e-7 9.0e-8 / 3.4e-8; every product losing most 5.9e-8 5.9e-8 / 6.0e-8 (k = 4096 1.9e-5 1.5e-5 / 6.0e-8).
 // What bounds it: six bf16 matrix instructions take 3/8 of the time of the fp32 ones they replace; a slab of 128 x 128 x 32 takes
 // 1.3 us with all CUs busy, of which they are 0.75 and the taking apart (104 vector instructions a wave, dealt out between them) 0.4:
-// 196 TFLOP/s at 4096^3 (fp32 instructions 129), with a tangent 146 at 1024 x 3072 x 768 (105).
+// 199 TFLOP/s at 4096^3 (fp32 instructions 129), with a tangent 150 at 1024 x 3072 x 768 (106).
 // An operand that is infinite or at least 2^104 makes every result that it takes part in a NaN here, and sums of 2^80 (1.2e24) and
 // more, or nearly that when the first parts are rounded up by as much as 2^-8 of them, are infinite: blocks that find a result that
 // is not finite compute theirs again with the fp32 instructions (150 x 145 x 30000 with an infinity in each block: 2.6 instead of
@@ -797,9 +797,9 @@ static int plan_group(const GemmP* ps, int n, int nb, bool scratch, int64_t ws_e
   // priced with the whole k, about twice their average: only the tile is chosen there, and all tiles are priced alike.)  A cut
   // costs each block 1500 clocks a 64 x 64 part (partial tile out) and the launch 6000 and 1500 or 10000 a part (sums of small or large ones).
   // Measured (us; 64 x 64 whole and in its best parts, 128 x 128 the same, 32 x 32, chosen): primal product and tangent
-  // 1024x768x768 41 37/2 55 39/2 47, 39; 1024x2304x768 85 - 73 - 114, 73; 1024x3072x768 106 - 101 - 150, 99; 1024x768x3072 124
-  // 109/3 190 94/3 162, 95; 1024x50257x768 1636 - 1291 - 2323, 1305; 1024x768x50257 1996 1638/4 3041 1311/3 3000, 1267; 512x128x128
-  // 11 - 17 - 6.5, 6.4; 512x128x512 25 14/6 39 23/6 11.1, 11.2; A^T B 768x3072x1024 92 83/3 74 73/3 103, 78.
+  // 1024x768x768 41 36/2 53 37/2 45, 37; 1024x2304x768 81 - 68 - 114, 68; 1024x3072x768 104 - 96 - 149, 97; 1024x768x3072 122
+  // 108/3 188 92/3 163, 92; 1024x50257x768 1624 - 1261 - 2313, 1293; 1024x768x50257 1980 1641/4 3031 1305/8 3107, 1270; 512x128x128
+  // 9.8 - 14 - 6.1, 6.1; 512x128x512 23 13/6 36 20/6 10.9, 11.0; A^T B 768x3072x1024 92 82/3 72 70/3 102, 75.
   int cfg = 0, parts = 1;
   double best = 1e300;
   for (int ci = 0; ci < 3; ++ci) {
