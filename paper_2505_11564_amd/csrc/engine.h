@@ -39,6 +39,13 @@ struct LayerBuf {
   float* att_stat;
 };
 
+// Adjoints (with tangents) that the weight-gradient products of a layer read: of its output (x) and between its two branches
+// (m; operand-type copies), of the activation's input(s), of the packed q | k | v, and of v apart from them (stored attention, grouped
+// heads).  The products of several layers may run as one launch, so there are several of these (dw_layers).
+struct AdjBuf {
+  void *x, *x_t, *m, *m_t, *g, *g_t, *up, *up_t, *qkv, *qkv_t, *v, *v_t;
+};
+
 // mlp.hip: MLP products whose weights fit LDS run in one kernel of at most MLP_BLOCKS blocks, each of which leaves a
 // partial result.
 constexpr int MLP_BLOCKS = 256, MLP_FUSED_MAX_BATCH = 65536;
@@ -78,7 +85,6 @@ struct hf_ctx {
   void *a_lo = nullptr, *qkv_lo = nullptr, *P_lo = nullptr, *o_lo = nullptr, *f_lo = nullptr, *up_lo = nullptr, *g_lo = nullptr;
   float *rq = nullptr, *rq_t = nullptr;  // LLAMA: fp32 q|k (or their adjoints) before the rotation
   float *rv = nullptr, *rv_t = nullptr;  // grouped-query attention: fp32 dV summed over the heads of a group
-  void *dvb = nullptr, *dvb_t = nullptr; //   and its operand-type copy (bf16 mode)
   float *z = nullptr, *z_t = nullptr;
   void *dz = nullptr, *dz_t = nullptr;
   int64_t ldz = 0;
@@ -90,10 +96,8 @@ struct hf_ctx {
   int att_zero_B = -1, att_zero_S = -1;               // shape for which the never-written score tiles were last cleared
   void *dS = nullptr, *dS_t = nullptr;
   float *dx = nullptr, *dx_t = nullptr, *tmpd = nullptr, *tmpd_t = nullptr;
-  void *dxb = nullptr, *dxb_t = nullptr, *dob = nullptr, *dob_t = nullptr;
-  void *dxb2 = nullptr, *dxb2_t = nullptr;  // second pair of bf16 adjoint copies (grouped weight-gradient launches)
-  void *dqkv = nullptr, *dqkv_t = nullptr;
-  void *dg = nullptr, *dg_t = nullptr, *dup = nullptr, *dup_t = nullptr, *dy = nullptr, *dy_t = nullptr;
+  void *dob = nullptr, *dob_t = nullptr, *dy = nullptr, *dy_t = nullptr;
+  std::vector<hf::AdjBuf> adj;  // layer l's are adj[l % adj.size()]
   float* mlp_part = nullptr;  // MLP products in one kernel: the blocks' shares of H v and of the loss; nullptr = not that size
   double* mlp_part_loss = nullptr;
   void* xin = nullptr;  // MLP input in operand type (bf16 mode)
@@ -106,7 +110,7 @@ struct hf_ctx {
   int* gemm_cnt = nullptr;   // fp32 parameters: arrival counters of those products (F32_COUNTERS, zero between launches)
   int gemm_cnt_clear = 0;    // the first product has cleared them
   float* aux_vec = nullptr;  // n floats, allocated on first use (batch-loop partial result, unit vector)
-  bool gpt_groups_dw() const;
+  int dw_layers() const;  // layers whose weight-gradient products may wait for a common launch
   int ensure_aux();
 
   // Lanczos state
@@ -138,7 +142,7 @@ struct hf_ctx {
   float* prev_q() const;        // q_{k-1} (meaningful for k >= 1)
 
   int fail(int code, const std::string& m) { err = m; return code; }
-  int plan_and_alloc();
+  int plan_and_alloc(bool may_wait = true);  // false: weight-gradient products never wait beyond their layer (least memory)
   // out = seed_scale * H v, or out += seed_scale * H v when accumulate (the batch loop of Algorithm 1:
   // the weight of a batch multiplies the adjoint seeds, in which the backward sweep is linear)
   int hvp_enqueue(const void* params, const void* inputs, const int32_t* labels, int batch, int seq, const float* v,

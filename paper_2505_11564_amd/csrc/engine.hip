@@ -138,7 +138,7 @@ void hf_ctx::release_host() {
   host_scal = host_hvp = nullptr;
 }
 
-int hf_ctx::plan_and_alloc() {
+int hf_ctx::plan_and_alloc(bool may_wait) {
   Planner pl;
   const int64_t e = bf ? 2 : 4;
   if (desc.arch == HF_ARCH_MLP) {
@@ -148,7 +148,8 @@ int hf_ctx::plan_and_alloc() {
     b = LayerBuf{};
     pl.add(b.f, B * Hd * e); pl.add(b.f_t, B * Hd * e);
     pl.add(b.g, B * Hd * e); pl.add(b.g_t, B * Hd * e);
-    pl.add(dg, B * Hd * e); pl.add(dg_t, B * Hd * e);
+    adj.assign(1, AdjBuf{});
+    pl.add(adj[0].g, B * Hd * e); pl.add(adj[0].g_t, B * Hd * e);
     ldz = round_up(O, 8);
     pl.add(z, B * ldz * 4); pl.add(z_t, B * ldz * 4);
     pl.add(dz, B * ldz * e); pl.add(dz_t, B * ldz * e);
@@ -198,7 +199,6 @@ int hf_ctx::plan_and_alloc() {
     if (llama) { pl.add(rq, T * (D + Dkv) * 4); pl.add(rq_t, T * (D + Dkv) * 4); }
     if (llama && Dkv != D) {  // grouped heads: dV is summed over a group in fp32, then rounded once
       pl.add(rv, T * Dkv * 4); pl.add(rv_t, T * Dkv * 4);
-      if (bf) { pl.add(dvb, T * Dkv * e); pl.add(dvb_t, T * Dkv * e); }
     }
     ldz = round_up(desc.vocab, 64);
     pl.add(z, T * ldz * 4); pl.add(z_t, T * ldz * 4);
@@ -213,14 +213,16 @@ int hf_ctx::plan_and_alloc() {
     }
     pl.add(dS, SSa * e); pl.add(dS_t, SSa * e);
     pl.add(dx, T * D * 4); pl.add(dx_t, T * D * 4); pl.add(tmpd, T * D * 4); pl.add(tmpd_t, T * D * 4);
-    if (bf) { pl.add(dxb, T * D * e); pl.add(dxb_t, T * D * e); pl.add(dxb2, T * D * e); pl.add(dxb2_t, T * D * e); }
     pl.add(dob, T * D * e); pl.add(dob_t, T * D * e);
-    pl.add(dqkv, T * W3 * e); pl.add(dqkv_t, T * W3 * e);
-    pl.add(dg, T * F * e); pl.add(dg_t, T * F * e);
-    if (llama) {
-      pl.add(dup, T * F * e); pl.add(dup_t, T * F * e);
-      pl.add(dy, T * F * e); pl.add(dy_t, T * F * e);
+    adj.assign(may_wait ? dw_layers() : 1, AdjBuf{});
+    for (AdjBuf& a : adj) {
+      if (bf) { pl.add(a.x, T * D * e); pl.add(a.x_t, T * D * e); pl.add(a.m, T * D * e); pl.add(a.m_t, T * D * e); }
+      pl.add(a.qkv, T * W3 * e); pl.add(a.qkv_t, T * W3 * e);
+      pl.add(a.g, T * F * e); pl.add(a.g_t, T * F * e);
+      if (llama) { pl.add(a.up, T * F * e); pl.add(a.up_t, T * F * e); }
+      if (llama && Dkv != D && bf && !flash) { pl.add(a.v, T * Dkv * e); pl.add(a.v_t, T * Dkv * e); }
     }
+    if (llama) { pl.add(dy, T * F * e); pl.add(dy_t, T * F * e); }
   }
   if (bf) pl.add(vb, n * 2);
   if (desc.arch != HF_ARCH_MLP) {
@@ -247,6 +249,7 @@ int hf_ctx::plan_and_alloc() {
   if (e1 != hipSuccess) {
     arena = nullptr;
     (void)hipGetLastError();
+    if (adj.size() > 1) return plan_and_alloc(false);
     return fail(HF_ENOMEM, "hipMalloc of " + std::to_string(arena_bytes) + " bytes failed: " + hipGetErrorString(e1));
   }
   for (auto& f : pl.fix) *f.first = arena + f.second;
@@ -257,7 +260,7 @@ int hf_ctx::plan_and_alloc() {
   }
   host_hvp = host_scal + LZ_AHEAD * S_COUNT;
   host_stats = (unsigned long long*)(host_hvp + 3);
-  if (!bf) { dxb = dx; dxb_t = dx_t; dxb2 = dx; dxb2_t = dx_t; }
+  if (!bf) for (AdjBuf& a : adj) { a.x = a.m = dx; a.x_t = a.m_t = dx_t; }
   return HF_OK;
 }
 
@@ -375,25 +378,23 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
     CK(launch_fill_f32((float*)gemm_cnt, F32_COUNTERS, 0.f, st));
     gemm_cnt_clear = 1;
   }
-  // Cleared up front, in one launch: the flags, and the blocks of H v that are accumulated with atomics.  Small models, where every
-  // weight-gradient product of a layer would split k and add into a cleared result: the layers' whole range in one piece (the
-  // vectors between the matrices with it), which replaces a fill per matrix, unless the launch that takes a GPT layer's products
-  // together leaves k whole and writes every element itself (clearing 340 MB of GPT-2-small for nothing was 43 us).
+  // Cleared up front, in one launch: the flags, and the blocks of H v that are accumulated with atomics.  Small models, where the
+  // launch of a few layers' weight-gradient products would cut k and add into cleared results: the layers' whole range in one piece
+  // (the vectors between the matrices with it).  Where it leaves k whole it writes every element itself (clearing 340 MB of
+  // GPT-2-small for nothing was 43 us).
   dw_prezeroed = 0;
   if (!accumulate && bf && desc.arch != HF_ARCH_MLP && layers_end > layers_begin) {
     const int T = batch * seq, D = desc.d_model, F = desc.d_ff;
     const int hkv = desc.n_kv_head > 0 ? desc.n_kv_head : desc.n_head, Dkv = D / desc.n_head * hkv;
-    bool all = gemm_mfma_splits_k(D, D, T, 2) && gemm_mfma_splits_k(D, F, T, 2) && gemm_mfma_splits_k(F, D, T, 2);
-    if (desc.arch == HF_ARCH_GPT) {
-      all = all && gemm_mfma_splits_k(D, 3 * D, T, 2);
-      if (all && gpt_groups_dw()) {
-        const int M[4] = {F, D, D, D}, N[4] = {D, F, D, 3 * D};
-        all = gemm_mfma_group_cuts_k(M, N, 4, T, 2);
+    const int Mg[4] = {F, D, D, D}, Ng[4] = {D, F, D, 3 * D}, Ml[7] = {F, D, D, D, D, D, D}, Nl[7] = {D, F, F, D, D, Dkv, Dkv};
+    const bool gpt = desc.arch == HF_ARCH_GPT;
+    int M[GEMM_GROUP_MAX], N[GEMM_GROUP_MAX], k = 0;
+    for (size_t i = 0; i < adj.size(); ++i)
+      for (int j = 0; j < (gpt ? 4 : 7) && k < GEMM_GROUP_MAX; ++j, ++k) {
+        M[k] = gpt ? Mg[j] : Ml[j];
+        N[k] = gpt ? Ng[j] : Nl[j];
       }
-    } else {
-      all = all && gemm_mfma_splits_k(D, Dkv, T, 2);
-    }
-    if (all) {
+    if (gemm_mfma_group_cuts_k(M, N, k, T, 2)) {
       CK(launch_fill_f32(out + layers_begin, layers_end - layers_begin, 0.f, st));
       dw_prezeroed = 1;
     }
@@ -420,10 +421,22 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
   return hvp_transformer(params, (const int32_t*)inputs, labels, batch, seq, v, out, st);
 }
 
-// The weight-gradient products of a bf16 GPT layer run as one launch while together they have fewer tiles than CUs.
-bool hf_ctx::gpt_groups_dw() const {
-  const int D = desc.d_model, F = desc.d_ff;
-  return gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F) < GROUP_MAX_TILES256;
+// Whether so many tiles of 256 x 256 leave at most a twentieth of their rounds of the CUs idle.
+static bool fills_rounds(int64_t tiles) { return tiles * 100 >= (tiles + 255) / 256 * 256 * 95; }
+
+// bf16 weight-gradient products (A^T B over all tokens, few tiles each) wait until together they fill whole rounds of the CUs with
+// 256 x 256 tiles, which do a third more per us than the 128 x 128 ones that a layer's 108 tiles (width 768) would need to fill the
+// chip alone.  That takes the adjoints of as many layers as make a round and one, up to four; none where a layer's own fill rounds
+// (width 2048: 768).  The memory is a hundredth to a tenth of a context's.  Measured, a launch a layer / this (ms): GPT-2-small
+// 4096 tokens 12.15 / 11.79 (735 tiles in three rounds with the head's, then 252 a round), 999 tokens 5.19 / 5.11; 1.3B 87.4 / 85.9 (W_o's 64
+// tiles next to W_qkv's 192); LLAMA-7B widths, two layers, 512 tokens 6.70 / 6.61.
+int hf_ctx::dw_layers() const {
+  if (!bf) return 1;
+  const int D = desc.d_model, F = desc.d_ff, Dkv = D / desc.n_head * (desc.n_kv_head > 0 ? desc.n_kv_head : desc.n_head);
+  const int64_t t = desc.arch == HF_ARCH_GPT ? gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F)
+                                             : 2 * gemm_tiles256(D, D) + 2 * gemm_tiles256(D, Dkv) + 3 * gemm_tiles256(D, F);
+  if (fills_rounds(t)) return 1;
+  return (int)std::min<int64_t>(desc.n_layer, std::min<int64_t>(4, (255 + t) / t + 1));
 }
 
 int hf_ctx::ensure_aux() {
@@ -456,6 +469,7 @@ int hf_ctx::hvp_mlp(const void* params, const void* inputs, const int32_t* label
   const int I = desc.mlp_in, Hd = desc.mlp_hidden, O = desc.mlp_out;
   Lin L{this, params, v, out, st, bf};
   LayerBuf& b = lb[0];
+  void *const dg = adj[0].g, *const dg_t = adj[0].g_t;
   const void* X = inputs;
   if (bf) { CK(launch_f32_to_bf16((const float*)inputs, (bf16*)xin, (int64_t)B * I, st)); X = xin; }
   int rc;
@@ -634,6 +648,32 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
   CK(launch_sum_rows_f64(loss_rows, T, flags + 1, loss_dev, (double)seed, acc_mode, flags, host_hvp, st));
 
   // ------------------------------ backward with tangents ----------------------
+  // Weight-gradient products are only described as they come up and wait until together they fill whole rounds of the CUs
+  // (dw_layers), until the next layer to be entered needs the adjoints' memory, or the end.  fp32 parameters: the norm
+  // adjoints work in place, so the products of a branch are launched together before its norm.
+  std::vector<Gemm> dw;
+  int64_t dw_tiles = 0;
+  int dw_oldest = -1;  // layer of the first one that waits, -1: none that reads a layer's adjoints
+  auto launch_dw = [&]() -> hipError_t {
+    const hipError_t er = dw.empty() ? hipSuccess : launch_gemm_group(dw.data(), (int)dw.size(), st);
+    dw.clear();
+    dw_tiles = 0;
+    dw_oldest = -1;
+    return er;
+  };
+  auto queue_dw = [&](const Gemm& g, int layer) -> hipError_t {
+    dw.push_back(g);
+    if (dw_oldest < 0) dw_oldest = layer;
+    dw_tiles += gemm_tiles256(g.M, g.N);
+    return bf && ((int)dw.size() == GEMM_GROUP_MAX || fills_rounds(dw_tiles)) ? launch_dw() : hipSuccess;
+  };
+  auto adj_of = [&](int l) -> const AdjBuf& { return adj[l % adj.size()]; };
+  // the head's: not in cleared memory, so it does not join launches that cut k
+  auto head_dw = [&](Gemm& g) -> hipError_t {
+    if (!bf || dw_prezeroed) return launch_gemm(g, st);
+    g.allow_splitk = 1;
+    return queue_dw(g, -1);
+  };
   if (tied) {
     // z = xf wte^T:  (Hv)_wte = dz_t^T xf + dz^T xf_t  [V, D];  dxf = dz wte
     Gemm g;
@@ -641,62 +681,56 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     g.A[0] = dz_t; g.B[0] = xf; g.A[1] = dz; g.B[1] = xf_t; g.C = out + off_wte;
     if (acc_mode) g.Cadd = out + off_wte;
     L.scratch(g);
-    CK(launch_gemm(g, st));
+    CK(head_dw(g));
     if ((rc = L.bwd_dx(dz, dz_t, T, D, V, ldz, off_wte, tmpd, tmpd_t, D, 0, nullptr, nullptr, 1, D))) return rc;
   } else {
-    if ((rc = L.bwd_dw(xf, xf_t, dz, dz_t, T, D, V, D, ldz, off_head, -1, nullptr, 0))) return rc;
+    Gemm g;
+    if ((rc = L.bwd_dw(xf, xf_t, dz, dz_t, T, D, V, D, ldz, off_head, -1, nullptr, 0, &g))) return rc;
+    CK(head_dw(g));
     if ((rc = L.bwd_dx(dz, dz_t, T, D, V, ldz, off_head, tmpd, tmpd_t, D, 0))) return rc;
   }
-  // each norm adjoint also leaves the bf16 copies (dxb, dxb_t) that the next products read, and adds
+  // each norm adjoint also leaves the bf16 copies that the next products read, and adds
   // the column sums of its dx_t to the H v block of the bias that this adjoint belongs to (the output
   // bias of the linear layer applied just before, in forward order)
   CK(launch_norm_bwd(bf, rms, tmpd, tmpd_t, xL, xL_t, stf, L.Wp(off_nfg), v + off_nfg, T, D, 0, dx, dx_t,
-                     out + off_nfg, rms ? nullptr : out + off_nfb, norm_part, st, bf ? dxb : nullptr, bf ? dxb_t : nullptr,
+                     out + off_nfg, rms ? nullptr : out + off_nfb, norm_part, st, bf ? adj_of(NL - 1).x : nullptr, bf ? adj_of(NL - 1).x_t : nullptr,
                      loff[NL - 1].bproj >= 0 ? out + loff[NL - 1].bproj : nullptr));
 
   for (int l = NL - 1; l >= 0; --l) {
     LayerBuf& b = lb[l];
     const LayerOff& o = loff[l];
+    const AdjBuf& ad = adj_of(l);
+    void *const dg = ad.g, *const dg_t = ad.g_t, *const dup = ad.up, *const dup_t = ad.up_t, *const dqkv = ad.qkv, *const dqkv_t = ad.qkv_t;
+    Gemm g_dw;
     // ---- MLP branch
-    // GPT: the four weight-gradient products of a layer that do not fill the chip on their own are
-    // only described here and launched together once the last of their operands exists; the two norm
-    // adjoints of a layer then write their bf16 copies to different buffers, so that the first is still
-    // there when the group runs.  fp32 parameters: the norm adjoints work in place, so the products of
-    // a branch are launched together before its norm.
-    Gemm dw[4];
-    int ndw = 0;
-    const bool group_dw = !bf || (!llama && gpt_groups_dw());
-    auto launch_dw = [&]() -> hipError_t {
-      const int k = ndw;
-      ndw = 0;
-      return k > 0 ? launch_gemm_group(dw, k, st) : hipSuccess;
-    };
-    void* const dxa = dxb;                        // adjoint entering the layer (bf16 copy) and its tangent
-    void* const dxa_t = dxb_t;
-    void* const dxm = group_dw ? dxb2 : dxb;      // adjoint between the two branches (fp32: dx again)
-    void* const dxm_t = group_dw ? dxb2_t : dxb_t;
     if (!llama) {
-      if ((rc = L.bwd_dw(b.g, b.g_t, dxa, dxa_t, T, F, D, F, D, o.wproj, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
-      if ((rc = L.bwd_dx(dxa, dxa_t, T, F, D, D, o.wproj, dg, dg_t, F, bf))) return rc;
+      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, T, F, D, F, D, o.wproj, -1, nullptr, 0, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
+      if ((rc = L.bwd_dx(ad.x, ad.x_t, T, F, D, D, o.wproj, dg, dg_t, F, bf))) return rc;
       CK(launch_act_bwd_bias(bf, gelu_kind, b.f, b.f_t, dg, dg_t, dg, dg_t, T, F, out + o.bfc, st));  // and the bias block of H v
-      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wfc, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
+      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wfc, -1, nullptr, 0, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dg, dg_t, T, D, F, F, o.wfc, tmpd, tmpd_t, D, 0))) return rc;
     } else {
-      if ((rc = L.bwd_dw(b.g, b.g_t, dxb, dxb_t, T, F, D, F, D, o.wdown, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
-      if ((rc = L.bwd_dx(dxb, dxb_t, T, F, D, D, o.wdown, dy, dy_t, F, bf))) return rc;
+      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, T, F, D, F, D, o.wdown, -1, nullptr, 0, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
+      if ((rc = L.bwd_dx(ad.x, ad.x_t, T, F, D, D, o.wdown, dy, dy_t, F, bf))) return rc;
       CK(launch_swiglu_bwd(bf, b.f, b.f_t, b.up, b.up_t, dy, dy_t, dg, dg_t, dup, dup_t, (int64_t)T * F, st));
-      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wgate, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
-      if ((rc = L.bwd_dw(b.m, b.m_t, dup, dup_t, T, D, F, D, F, o.wup, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
+      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wgate, -1, nullptr, 0, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
+      if ((rc = L.bwd_dw(b.m, b.m_t, dup, dup_t, T, D, F, D, F, o.wup, -1, nullptr, 0, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dg, dg_t, T, D, F, F, o.wgate, tmpd, tmpd_t, D, 0))) return rc;
       if ((rc = L.bwd_dx(dup, dup_t, T, D, F, F, o.wup, tmpd, tmpd_t, D, 0, tmpd, tmpd_t))) return rc;
     }
     if (!bf) CK(launch_dw());
     CK(launch_norm_bwd(bf, rms, tmpd, tmpd_t, b.x2, b.x2_t, b.st2, L.Wp(o.n2g), v + o.n2g, T, D, 1, dx, dx_t,
-                       out + o.n2g, rms ? nullptr : out + o.n2b, norm_part, st, bf ? dxm : nullptr, bf ? dxm_t : nullptr,
+                       out + o.n2g, rms ? nullptr : out + o.n2b, norm_part, st, bf ? ad.m : nullptr, bf ? ad.m_t : nullptr,
                        o.bo >= 0 ? out + o.bo : nullptr));
     // ---- attention branch
-    if ((rc = L.bwd_dw(b.o, b.o_t, dxm, dxm_t, T, D, D, D, D, o.wo, -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
-    if ((rc = L.bwd_dx(dxm, dxm_t, T, D, D, D, o.wo, dob, dob_t, D, bf))) return rc;
+    if ((rc = L.bwd_dw(b.o, b.o_t, ad.m, ad.m_t, T, D, D, D, D, o.wo, -1, nullptr, 0, &g_dw))) return rc;
+    CK(queue_dw(g_dw, l));
+    if ((rc = L.bwd_dx(ad.m, ad.m_t, T, D, D, D, o.wo, dob, dob_t, D, bf))) return rc;
     // Products whose result belongs to a key/value head sum over the grp query heads that share
     // it: one launch per member j of the groups (batch = key/value heads, query head kv * grp + j),
     // the first writing and the others adding to an fp32 result.
@@ -739,7 +773,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
       } else {  // fp32 [T, Dkv], rounded once below
         g.ldc = Dkv; g.sC1 = (int64_t)S * Dkv; g.sC2 = dh;
         CK(grouped(g, SS, dh, rv, rv_t));
-        if (bf) CK(launch_cast_pair(1, rv, rv_t, dvb, dvb_t, (int64_t)T * Dkv, st));
+        if (bf) CK(launch_cast_pair(1, rv, rv_t, ad.v, ad.v_t, (int64_t)T * Dkv, st));
       }
     }
     if (fused_att) {
@@ -796,8 +830,8 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     }
     }
     if (!llama) {
-      if ((rc = L.bwd_dw(b.a, b.a_t, dqkv, dqkv_t, T, D, 3 * D, D, W3, o.wqkv, o.bqkv, dqkv_t, bf, group_dw ? &dw[ndw++] : nullptr))) return rc;
-      CK(launch_dw());
+      if ((rc = L.bwd_dw(b.a, b.a_t, dqkv, dqkv_t, T, D, 3 * D, D, W3, o.wqkv, o.bqkv, dqkv_t, bf, &g_dw))) return rc;
+      CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dqkv, dqkv_t, T, D, 3 * D, W3, o.wqkv, tmpd, tmpd_t, D, 0))) return rc;
     } else {
       CK(launch_rope(bf, rq, rq_t, RQ, dqkv, dqkv_t, nullptr, W3, T, S, H + Hkv, dh, desc.rope_theta, 1, st));
@@ -809,19 +843,23 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
         int64_t ldy = W3;
         const int Ni = i ? Dkv : D;
         if (i == 2 && grp > 1 && !flash) {  // dV of grouped heads lives in its own [T, Dkv] buffer
-          dyi = bf ? (const void*)dvb : (const void*)rv;
-          dyi_t = bf ? (const void*)dvb_t : (const void*)rv_t;
+          dyi = bf ? (const void*)ad.v : (const void*)rv;
+          dyi_t = bf ? (const void*)ad.v_t : (const void*)rv_t;
           ldy = Dkv;
         }
-        if ((rc = L.bwd_dw(b.a, b.a_t, dyi, dyi_t, T, D, Ni, D, ldy, w3[i], -1, nullptr, 0, group_dw ? &dw[ndw++] : nullptr))) return rc;
+        if ((rc = L.bwd_dw(b.a, b.a_t, dyi, dyi_t, T, D, Ni, D, ldy, w3[i], -1, nullptr, 0, &g_dw))) return rc;
+        CK(queue_dw(g_dw, l));
         if ((rc = L.bwd_dx(dyi, dyi_t, T, D, Ni, ldy, w3[i], tmpd, tmpd_t, D, 0, i ? tmpd : nullptr, i ? tmpd_t : nullptr))) return rc;
       }
     }
-    CK(launch_dw());
+    // the adjoint that enters the next layer goes where layer l - 1 + (number of buffers) had its own
+    if (!bf || dw_oldest >= l - 1 + (int)adj.size()) CK(launch_dw());
+    const AdjBuf* const next = bf && l > 0 ? &adj_of(l - 1) : nullptr;
     CK(launch_norm_bwd(bf, rms, tmpd, tmpd_t, b.x1, b.x1_t, b.st1, L.Wp(o.n1g), v + o.n1g, T, D, 1, dx, dx_t,
-                       out + o.n1g, rms ? nullptr : out + o.n1b, norm_part, st, bf ? dxb : nullptr, bf ? dxb_t : nullptr,
+                       out + o.n1g, rms ? nullptr : out + o.n1b, norm_part, st, next ? next->x : nullptr, next ? next->x_t : nullptr,
                        (l > 0 && loff[l - 1].bproj >= 0) ? out + loff[l - 1].bproj : nullptr));
   }
+  CK(launch_dw());
   CK(launch_embed_bwd(dx_t, tok, T, S, D, V, out + off_wte, llama ? nullptr : out + off_wpe, st));
   return HF_OK;
 }

@@ -318,7 +318,7 @@ static hipError_t launch_prepared(int kind, const Gemm& g, GemmP& p, hipStream_t
 }
 
 // Several single-output products in one launch where that pays (fp32 products; bf16 A^T B products with few
-// output tiles each: the weight-gradient products of a layer of a small model); otherwise one by one.
+// output tiles each: the weight-gradient products of a few layers); otherwise one by one.
 hipError_t launch_gemm_group(const Gemm* gs, int n, hipStream_t st) {
   if (n >= 2 && n <= F32_GROUP_MAX && !gs[0].in_bf16) {
     GemmP ps[F32_GROUP_MAX];
@@ -328,8 +328,8 @@ hipError_t launch_gemm_group(const Gemm* gs, int n, hipStream_t st) {
            gs[i].transB == gs[0].transB && prepare_single(gs[i], ps[i]) == 1;
     if (ok) return launch_gemm_f32_group(ps, n, 1, gs[0].ws, gs[0].ws_elems, gs[0].counters, -1, 0, st);
   }
-  if (n >= 2 && n <= 4) {
-    GemmP ps[4];
+  if (n >= 2 && n <= GEMM_GROUP_MAX) {
+    GemmP ps[GEMM_GROUP_MAX];
     bool ok = true, zeroed = true;
     for (int i = 0; i < n && ok; ++i) {
       const Gemm& g = gs[i];

@@ -430,19 +430,20 @@ __global__ __launch_bounds__(256, (min_blocks<BM, BN, KT, NS>())) void gemm_mfma
   gemm_mfma_body<BM, BN, WM, WN, KT, NS, TA, TB, FL>(pp.g[blockIdx.z], 0, 1);
 }
 
-// Up to four A^T B products (the weight-gradient products of one layer: few output tiles each, a
+// Up to GEMM_GROUP_MAX A^T B products (the weight-gradient products of a few layers: few output tiles each, a
 // long contraction over the tokens) as one launch.  Block b works on part (b - first[g]) / tiles[g]
 // of the k-split of tile (b - first[g]) % tiles[g] of product g.  With k cut, the parts are added
 // with atomics, so C must hold zeros (or what the sum is added to) beforehand.
 // Blocks go round-robin to the 8 XCDs: XCD x takes the x-th run of consecutive tiles, which share
 // operand rows in its L2.
 struct GemmGroup {
-  GemmP g[4];
-  int first[5];   // first block of each product; first[n] = number of blocks
-  int tiles[4];
-  int nks[4];
+  GemmP g[GEMM_GROUP_MAX];
+  int first[GEMM_GROUP_MAX + 1];   // first block of each product; first[n] = number of blocks
+  int tiles[GEMM_GROUP_MAX];
+  int nks[GEMM_GROUP_MAX];
   int n;
 };
+static_assert(sizeof(GemmGroup) <= 4096, "kernel arguments");
 template <int BM, int BN, int WM, int WN, int KT, int NS, bool TA, bool TB, int FL = 1>
 __global__ __launch_bounds__(256, 1) void gemm_mfma_group_kernel(GemmGroup gg) {
   const int x = blockIdx.x & 7, per = gridDim.x >> 3, rem = gridDim.x & 7;
@@ -525,16 +526,6 @@ static void choose_tile_and_split(const GemmP& p, int nb, int allow_splitk, int 
     }
   }
   cfg_out = cfg; ks_out = ks;
-}
-
-// Whether launch_gemm_mfma would split k (and so add into C with atomics, which needs C zeroed) for an
-// fp32-output A^T B product of this shape: lets a caller clear several results with one fill.
-bool gemm_mfma_splits_k(int M, int N, int K, int nterm) {
-  GemmP p = {};
-  p.M = M; p.N = N; p.K = K; p.nterm = nterm; p.transA = 1; p.transB = 0; p.out_bf16 = 0; p.klimit = 0;
-  int cfg, ks;
-  choose_tile_and_split(p, 1, 1, -1, -1, cfg, ks);
-  return ks > 1;
 }
 
 // c_zeroed: the caller has already cleared C (a split product then skips its own fill).
@@ -680,7 +671,7 @@ static void choose_group_plan(const GemmP* ps, int n, int zeroed, int& cfg, int&
 }
 
 bool gemm_mfma_group_cuts_k(const int* M, const int* N, int n, int K, int nterm) {
-  GemmP ps[4] = {};
+  GemmP ps[GEMM_GROUP_MAX] = {};
   for (int i = 0; i < n; ++i) { ps[i].M = M[i]; ps[i].N = N[i]; ps[i].K = K; ps[i].nterm = nterm; }
   int cfg, ks;
   choose_group_plan(ps, n, 1, cfg, ks);
@@ -691,16 +682,13 @@ bool gemm_mfma_group_cuts_k(const int* M, const int* N, int n, int K, int nterm)
 // zeroed: every C is zero or holds what the sum is added to, so k may be cut.
 // hipErrorNotSupported: launch them one by one.
 hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_t st) {
-  if (n < 2 || n > 4) return hipErrorNotSupported;
-  int64_t t256 = 0;
+  if (n < 2 || n > GEMM_GROUP_MAX) return hipErrorNotSupported;
   for (int i = 0; i < n; ++i) {
     const GemmP& p = ps[i];
     if (!p.transA || p.transB || p.out_bf16 || p.klimit || p.skip_upper || p.bias || p.bias_t || p.C_lo) return hipErrorNotSupported;
     if (p.Cadd && p.Cadd != (const float*)p.C) return hipErrorNotSupported;
     if (p.ldc != p.N) return hipErrorNotSupported;
-    t256 += gemm_tiles256(p.M, p.N);
   }
-  if (t256 >= GROUP_MAX_TILES256) return hipErrorNotSupported;
   int cfg, ks;
   choose_group_plan(ps, n, zeroed, cfg, ks);
   const int bm = kGroupCfg[cfg].bm, bn = kGroupCfg[cfg].bn;

@@ -34,7 +34,7 @@ hipError_t launch_gemm_mfma(GemmP p, int nb, int allow_splitk, int force_cfg, in
 // Two products of one shape (primal and tangent) in one launch; hipErrorNotSupported = launch them separately.
 hipError_t launch_gemm_mfma_pair(GemmP a, GemmP b, int nb, hipStream_t st);
 
-// Several A^T B products with fp32 results as one launch; zeroed: the results are zero or hold the addend, so k may be cut
+// Several (up to GEMM_GROUP_MAX) A^T B products with fp32 results as one launch; zeroed: the results are zero or hold the addend, so k may be cut
 // (atomic accumulation).  hipErrorNotSupported = launch them separately.
 hipError_t launch_gemm_mfma_group(const GemmP* ps, int n, int zeroed, hipStream_t st);
 

@@ -119,13 +119,9 @@ int linear_plan(const Gemm& g, int* parts);                    // its tile and p
 // gs[0..n): single-output products whose results are already zero (c_zeroed) or are added to
 // (Cadd == C); launched as one grid where that is faster, else in turn.
 hipError_t launch_gemm_group(const Gemm* gs, int n, hipStream_t st);
-// bf16 A^T B product [M, N] over k = K with fp32 result and split-K allowed: will it accumulate with atomics?
-bool gemm_mfma_splits_k(int M, int N, int K, int nterm);
 // Will launch_gemm_group cut k of these A^T B products ([M_i, N_i], k = K, cleared results) and add with atomics?
 bool gemm_mfma_group_cuts_k(const int* M, const int* N, int n, int K, int nterm);
-// launch_gemm_group takes A^T B products whose 256 x 256 tiles together stay below this (one round of the CUs); with
-// more, each product fills the chip on its own.
-constexpr int64_t GROUP_MAX_TILES256 = 256;
+constexpr int GEMM_GROUP_MAX = 16;  // products of one launch (its kernel arguments hold them)
 inline int64_t gemm_tiles256(int M, int N) { return ((int64_t)M + 255) / 256 * (((int64_t)N + 255) / 256); }
 
 // -------------------------------------------------------- row / pointwise ----
