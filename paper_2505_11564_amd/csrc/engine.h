@@ -160,8 +160,9 @@ struct hf_ctx {
   // iterations finished.  HF_EBREAKDOWN as lanczos_update.
   int run_small(const void* params, const void* inputs, const int32_t* labels, int batch, int seq, int m, double tol, double* alpha,
                 double* beta, int* done, hipStream_t st);
-  // the small update of iteration lz_k (hq = H q_k, the residual into r) into slot `host`; hipErrorNotSupported: vectors too long
-  hipError_t enqueue_small_update(const float* hq, float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st);
+  // the small update of iteration lz_k (the residual, or without a basis H q_k itself, into r), scalars into slot `host`; false: vectors too long
+  bool small_update(float* r, double tol, double* host, int chained, hf::LzSmall& u);
+  const hf::LzSmall* then_update = nullptr;  // the update that follows the product being enqueued; taken (NULL again) by one that includes it
   // what a finished iteration k with norm bt leaves: true if the run goes on
   bool advance(int k, double bt, double tol);
   int flag_error(const double* host);

@@ -884,18 +884,24 @@ int hf_ctx::flag_error(const double* host) {  // the product's input checks; q_{
   return HF_OK;
 }
 
-hipError_t hf_ctx::enqueue_small_update(const float* hq, float* r, double tol, const int* hvp_flags, double* host, int chained, hipStream_t st) {
+bool hf_ctx::small_update(float* r, double tol, double* host, int chained, LzSmall& u) {
   const int k = lz_k;
+  u = {};
+  u.n = (int)n; u.tol = tol; u.scal = scal; u.host = host; u.chained = chained; u.r = r;
   if (lz_reorth == HF_REORTH_FULL) {
-    if (!lz_rows_are_vectors() || !lz_small(n, k + 1)) return hipErrorNotSupported;
-    float* row = k + 1 < max_m ? (float*)basis + (int64_t)(k + 1) * ldq : nullptr;
-    bf16* vdst = !bf ? nullptr : ((basis_bf && row) ? basis_bf + (int64_t)(k + 1) * ldq : vb);
-    next_vb = vdst;
-    return lz_small_full((const float*)basis, ldq, hq, r, n, k + 1, row, row ? nullptr : lz_vec[iq], vdst, tol, hvp_flags, scal, host, chained, st);
+    if (!lz_rows_are_vectors() || !lz_small(n, k + 1)) return false;
+    u.full = 1;
+    u.Q = (const float*)basis; u.ldq = ldq; u.nq = k + 1;
+    u.row = k + 1 < max_m ? (float*)basis + (int64_t)(k + 1) * ldq : nullptr;
+    u.spill = u.row ? nullptr : lz_vec[iq];
+    u.vb = !bf ? nullptr : ((basis_bf && u.row) ? basis_bf + (int64_t)(k + 1) * ldq : vb);
+  } else {
+    if (!lz_small(n, 0)) return false;
+    u.q = cur_q(); u.qp = prev_q(); u.use_prev = k > 0; u.bprev = (float)lz_beta_prev;
+    u.vb = bf ? vb : nullptr;
   }
-  if (!lz_small(n, 0)) return hipErrorNotSupported;
-  next_vb = bf ? vb : nullptr;
-  return lz_small_three(hq, hq == r ? nullptr : r, cur_q(), prev_q(), bf ? vb : nullptr, n, k > 0, lz_beta_prev, tol, hvp_flags, scal, host, chained, st);
+  next_vb = u.vb;
+  return true;
 }
 
 bool hf_ctx::advance(int k, double bt, double tol) {
@@ -918,9 +924,11 @@ int hf_ctx::lanczos_update(float* r, double tol, double* alpha_k, double* beta_k
   const bool rows = lz_rows_are_vectors();
   float* q = cur_q();
   float* qp = prev_q();
-  const hipError_t es = enqueue_small_update(r, r, tol, hvp_flags, host_scal, 0, st);  // scalars on the host included
-  if (es != hipErrorNotSupported) {
-    CK(es);
+  LzSmall u;
+  const bool small = small_update(r, tol, host_scal, 0, u);
+  if (small) {  // scalars on the host included
+    if (!u.full) u.r = nullptr;  // (r is H q_k itself)
+    CK(lz_small_update(u, r, hvp_flags, st));
   } else if (lz_reorth == HF_REORTH_FULL) {
     // Gram-Schmidt of H q_k against q_0 .. q_k is the three-term subtraction and the
     // orthogonalisation in one.  An fp32 basis holds q_k and q_{k-1} as its rows k and k - 1; a
@@ -941,7 +949,7 @@ int hf_ctx::lanczos_update(float* r, double tol, double* alpha_k, double* beta_k
     CK(lz3_update(r, q, qp, bf ? vb : nullptr, n, k > 0, lz_beta_prev, tol, hvp_flags, scal, partials, st));
     next_vb = bf ? vb : nullptr;
   }
-  if (es != hipSuccess) CK(hipMemcpyAsync(host_scal, scal, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, st));
+  if (!small) CK(hipMemcpyAsync(host_scal, scal, S_COUNT * sizeof(double), hipMemcpyDeviceToHost, st));
   CK(hipStreamSynchronize(st));
   if (hvp_flags) {
     const int rc = flag_error(host_scal);
@@ -972,12 +980,16 @@ int hf_ctx::run_small(const void* params, const void* inputs, const int32_t* lab
   *done = 0;
   while (seen < m) {
     if (k < m && k - seen < LZ_AHEAD) {
+      LzSmall u;
+      const bool small = small_update(lz_vec[ir], tol, host_scal + (k % LZ_AHEAD) * S_COUNT, 1, u);
+      then_update = small ? &u : nullptr;
       int rc = hvp_enqueue(params, inputs, labels, batch, seq, cur_q(), lz_hq, st);
       if (rc == HF_OK) {
-        hipError_t e = enqueue_small_update(lz_hq, lz_vec[ir], tol, flags, host_scal + (k % LZ_AHEAD) * S_COUNT, 1, st);
+        hipError_t e = !small ? hipErrorNotSupported : then_update ? lz_small_update(u, lz_hq, flags, st) : hipSuccess;
         if (e == hipSuccess) e = hipEventRecord(ahead_ev[k % LZ_AHEAD], st);
         if (e != hipSuccess) rc = fail(HF_EDEVICE, std::string("run_small: ") + hipGetErrorString(e));
       }
+      then_update = nullptr;
       if (rc != HF_OK) {
         (void)hipStreamSynchronize(st);
         drop(seen);

@@ -3,6 +3,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "hf_internal.h"
+
 namespace hf {
 
 // Slots of the device-resident scalar array.
@@ -49,14 +51,27 @@ hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, 
 // Vectors so short that one block does the whole update of an iteration (see lanczos.hip): full orthogonalisation against an
 // fp32 basis, and the three-term recurrence.  `host`: S_COUNT doubles of pinned host memory that also receive the scalars.
 // chained: return at once after an iteration that could not advance; the three-term kernel takes beta_{k-1} from scal.
-// hq / w = H q_k; the residual goes to r (may be hq), and without a basis, where it is never stored, w itself to keep if given.
 constexpr int LZ_AHEAD = 3;  // iterations of such a run the host may be ahead of
 constexpr int64_t LZ_SMALL_N = 8192, LZ_SMALL_WORK = 256 * 1024;
 bool lz_small(int64_t n, int64_t rows);
-hipError_t lz_small_full(const float* Q, int64_t ldq, const float* hq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
-                         const int* flags, double* scal, double* host, int chained, hipStream_t st);
-hipError_t lz_small_three(const float* w, float* keep, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
-                          const int* flags, double* scal, double* host, int chained, hipStream_t st);
+// What such an update works on.
+struct LzSmall {
+  int full;                        // orthogonalise against Q, else three terms
+  const float* Q; int64_t ldq;     // full: the basis, its row stride,
+  int nq;                          //   its rows (k + 1),
+  float *row, *spill;              //   and where q_{k+1} goes (either may be NULL)
+  const float* q; float* qp;       // three terms: q_k, and q_{k-1}, which q_{k+1} replaces
+  int use_prev; float bprev;       //   with beta_{k-1}
+  float* r;                        // the residual; three terms: a copy of H q_k (may be NULL)
+  bf16* vb;                        // bf16 copy of q_{k+1} (may be NULL)
+  int n;
+  double tol;
+  double *scal, *host;
+  int chained;
+  int64_t lds() const { return (full ? (int64_t)(nq + 1) * 8 : 0) + (int64_t)n * 4; }  // bytes; below 64 KB: n <= 8192, nq <= 2000
+};
+// hq: H q_k (may be u.r), flags: error bits and valid labels of the product that made it, or NULL.
+hipError_t lz_small_update(const LzSmall& u, const float* hq, const int* flags, hipStream_t st);
 hipError_t lz_widen(const void* src, int is_bf16, float* dst, int64_t n, hipStream_t st);
 
 }  // namespace hf

@@ -24,15 +24,9 @@
 // accumulators, one partial per block, summed in a fixed order by a small second
 // kernel, so results are bitwise reproducible.
 #include "hf_internal.h"
-#include "lanczos.h"
+#include "lanczos_small.h"
 
 namespace hf {
-
-__device__ __forceinline__ double wave_sum_d(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
-  return v;
-}
 
 __device__ __forceinline__ double block_sum_d(double v, double* red) {
   v = wave_sum_d(v);
@@ -554,123 +548,16 @@ __global__ __launch_bounds__(256) void lz_sub_qc_kernel(const BT* __restrict__ Q
 // bandwidth, up to about LZ_SMALL_WORK vector elements (one CU streams about 100 GB/s).  The iteration's scalars also go
 // straight to the host's pinned array.
 
-__device__ __forceinline__ double block16_sum_d(double v, double* red /* [16] */) {
-  v = wave_sum_d(v);
-  __syncthreads();
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = v;
-  __syncthreads();
-  double s = 0.0;
-#pragma unroll
-  for (int i = 0; i < 16; ++i) s += red[i];
-  return s;
-}
-
-// <a, b> over n elements by one wave
-__device__ __forceinline__ double wave_dot(const float* a, const float* b, int n) {
-  double s = 0.0;
-#pragma unroll 4
-  for (int i = threadIdx.x & 63; i < n; i += 64) s += (double)a[i] * (double)b[i];
-  return wave_sum_d(s);
-}
-
-// The iteration's scalars, on the device and in the host's array.  chained: the host enqueues iterations ahead of their
-// results, so one that may not advance stops those behind it.
-__device__ __forceinline__ void small_scalars(double* scal, double* host, double alpha, double beta, const int* flags, bool ok, int chained) {
-  const double f0 = flags ? (double)flags[0] : 0.0, f1 = flags ? (double)flags[1] : 1.0;
-  scal[S_ALPHA] = alpha; scal[S_BETA] = beta; scal[S_REDO] = 0.0; scal[S_FLAG0] = f0; scal[S_FLAG1] = f1;
-  host[S_ALPHA] = alpha; host[S_BETA] = beta; host[S_FLAG0] = f0; host[S_FLAG1] = f1;
-  if (chained && !ok) scal[S_STOP] = 1.0;
-}
-
-// Full orthogonalisation against an fp32 basis of nq = k + 1 rows: the first Gram-Schmidt pass on w = H q_k itself, a
-// second one where it shrank the norm below 1/sqrt(2), q_{k+1} = r / beta_k into any of row, spill, vb.  r may be hq (= H q_k).
-__global__ __launch_bounds__(1024) void lz_small_full_kernel(const float* __restrict__ Q, int64_t ldq, const float* hq, float* r, int n, int nq,
-                                                             float* row, float* spill, bf16* vb, double tol, const int* flags,
-                                                             double* scal, double* host, int chained) {
-  extern __shared__ double sm_c[];  // [nq + 1] coefficients, then w
-  float* w = (float*)(sm_c + nq + 1);
+__global__ __launch_bounds__(1024) void lz_small_kernel(LzSmall u, const float* hq, const int* flags) {
+  extern __shared__ double sm_c[];  // [nq + 1] coefficients (full), then w
+  float* const w = (float*)(sm_c + (u.full ? u.nq + 1 : 0));
   __shared__ double red[16];
-  const int t = threadIdx.x, wave = t >> 6;
-  if (chained && scal[S_STOP] != 0.0) return;
-  for (int i = t; i < n; i += 1024) w[i] = hq[i];
+  if (u.chained && u.scal[S_STOP] != 0.0) return;
+  for (int i = threadIdx.x; i < u.n; i += 1024) w[i] = hq[i];
+  const int f0 = flags ? flags[0] : 0, f1 = flags ? flags[1] : 1;
   __syncthreads();
-  double alpha = 0.0, before = 0.0, beta = 0.0;
-  for (int pass = 0; pass < 2; ++pass) {
-    for (int j = wave; j <= nq; j += 16) {
-      const double d = wave_dot(j < nq ? Q + (int64_t)j * ldq : w, w, n);
-      if ((t & 63) == 0) sm_c[j] = d;
-    }
-    __syncthreads();
-    if (pass == 0) {  // as lz_direct_scal_kernel
-      alpha = sm_c[nq - 1];
-      const double p = nq >= 2 ? sm_c[nq - 2] : 0.0, ww = sm_c[nq], rest = ww - alpha * alpha - p * p;
-      before = rest > 1e-5 * ww ? sqrt(rest) : INFINITY;
-    }
-    double s = 0.0;
-    for (int i = t; i < n; i += 1024) {
-      float x = w[i];
-#pragma unroll 8
-      for (int j = 0; j < nq; ++j) x = fmaf(-(float)sm_c[j], Q[(int64_t)j * ldq + i], x);
-      w[i] = x;
-      s += (double)x * (double)x;
-    }
-    beta = sqrt(block16_sum_d(s, red));
-    if (pass == 1 || !(beta < before * 0.70710678118654752)) break;
-  }
-  bool ok = beta >= tol && beta > 0.0;
-  if (flags) ok = ok && flags[0] == 0 && flags[1] != 0;
-  const float inv = (float)(1.0 / beta);
-  for (int i = t; i < n; i += 1024) {
-    const float x = w[i];
-    r[i] = x;
-    if (!ok) continue;
-    const float q = x * inv;
-    if (row) row[i] = q;
-    if (spill) spill[i] = q;
-    if (vb) vb[i] = (bf16)q;
-  }
-  if (t == 0) small_scalars(scal, host, alpha, beta, flags, ok, chained);
-}
-
-// Three-term recurrence: alpha_k, beta_k, and q_{k+1} over qp; keep (may be NULL) takes a copy of wv = H q_k.
-__global__ __launch_bounds__(1024) void lz_small_three_kernel(const float* __restrict__ wv, float* __restrict__ keep, const float* __restrict__ q,
-                                                              float* qp, bf16* vb, int n, int use_prev, float bprev, double tol, const int* flags,
-                                                              double* scal, double* host, int chained) {
-  extern __shared__ float sm_w[];
-  __shared__ double red[16];
-  const int t = threadIdx.x;
-  if (chained) {
-    if (scal[S_STOP] != 0.0) return;
-    bprev = (float)scal[S_BETA];  // of the iteration before, whose result the host has not seen
-  }
-  double s = 0.0;
-  for (int i = t; i < n; i += 1024) {
-    float x = wv[i];
-    if (keep) keep[i] = x;
-    if (use_prev) x = fmaf(-bprev, qp[i], x);
-    sm_w[i] = x;
-    s += (double)x * (double)q[i];
-  }
-  const double alpha = block16_sum_d(s, red);
-  const float al = (float)alpha;
-  s = 0.0;
-  for (int i = t; i < n; i += 1024) {
-    const float x = fmaf(-al, q[i], sm_w[i]);
-    sm_w[i] = x;
-    s += (double)x * (double)x;
-  }
-  const double beta = sqrt(block16_sum_d(s, red));
-  bool ok = beta >= tol && beta > 0.0;
-  if (flags) ok = ok && flags[0] == 0 && flags[1] != 0;
-  if (ok) {
-    const float inv = (float)(1.0 / beta);
-    for (int i = t; i < n; i += 1024) {
-      const float x = sm_w[i] * inv;
-      qp[i] = x;
-      if (vb) vb[i] = (bf16)x;
-    }
-  }
-  if (t == 0) small_scalars(scal, host, alpha, beta, flags, ok, chained);
+  if (u.full) lz_small_full_block(u, w, sm_c, red, f0, f1);
+  else lz_small_three_block(u, w, red, f0, f1);
 }
 
 template <typename BT>
@@ -790,17 +677,8 @@ hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, 
 
 bool lz_small(int64_t n, int64_t rows) { return n <= LZ_SMALL_N && n * (rows + 2) <= LZ_SMALL_WORK; }
 
-hipError_t lz_small_full(const float* Q, int64_t ldq, const float* hq, float* r, int64_t n, int nq, float* row, float* spill, bf16* vb, double tol,
-                         const int* flags, double* scal, double* host, int chained, hipStream_t st) {
-  const size_t lds = (size_t)(nq + 1) * 8 + (size_t)n * 4;  // below 64 KB: n <= 8192, nq <= 2000
-  hipLaunchKernelGGL(lz_small_full_kernel, dim3(1), dim3(1024), lds, st, Q, ldq, hq, r, (int)n, nq, row, spill, vb, tol, flags, scal, host, chained);
-  return hipGetLastError();
-}
-
-hipError_t lz_small_three(const float* w, float* keep, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev, double tol,
-                          const int* flags, double* scal, double* host, int chained, hipStream_t st) {
-  hipLaunchKernelGGL(lz_small_three_kernel, dim3(1), dim3(1024), (size_t)n * 4, st, w, keep, q, qp, vb, (int)n, use_prev, (float)beta_prev, tol,
-                     flags, scal, host, chained);
+hipError_t lz_small_update(const LzSmall& u, const float* hq, const int* flags, hipStream_t st) {
+  hipLaunchKernelGGL(lz_small_kernel, dim3(1), dim3(1024), (size_t)u.lds(), st, u, hq, flags);
   return hipGetLastError();
 }
 

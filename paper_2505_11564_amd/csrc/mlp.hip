@@ -4,26 +4,31 @@
 // chain of products and pointwise kernels it was 15 launches of 1.5 to 13 us, each waiting for the one before.  The samples
 // are independent, so a block takes its own through the forward, loss and backward sweeps with their tangents in LDS and
 // leaves its share of H v (n floats) in the workspace; a second kernel adds the blocks' shares in a fixed order.
-// Measured at that shape: 13 + 4 us for the two, against 62 us of kernels in 15 launches (with the products of
-// gemm_f32.hip); an iteration of a run 33 us, 136 before.
+// In a run of few samples that sum is part of the Lanczos update behind it (mlp_sum_update_kernel), one launch less.
+// Measured at that shape: 62 us of kernels in 15 launches (with the products of gemm_f32.hip); 13 + 4 us with 256 threads a block and
+// the update, 6.5, behind them; 11.7 + 8 us now, at n = 4204 (16-200-4) 19 us (27).  Of the 11.7 most is the same at n = 90 (9): what a launch
+// takes to fetch 10 KB of instructions and go through a dozen barriers.
 // Blocks: one per eight samples up to one per CU (the largest weights take a CU's LDS), then several turns each.  With at most
 // 64 blocks, whatever the batch, a large one lost to the chain of products.  hf_hvp, us (chain / 64 blocks / 256 blocks and the
 // sum spread over eight groups of lanes): 128-64-10 at 256 samples 97 / 55 / 54, 2048 138 / 134 / 62, 16384 451 / 839 / 250, 65536
 // 1553 / - / 917; 32-32-10 88 / 34 / 33, 124 / 58 / 34, 428 / 269 / 94, 1493 / - / 292; 100-70-31 118 / 64 / 62, 202 / 159 /
-// 68, 852 / 1029 / 297, 3093 / - / 1102.  Larger batches (MLP_FUSED_MAX_BATCH) have not been measured and take the chain.
+// 68, 852 / 1029 / 297, 3093 / - / 1102.  256 threads and 32 lanes a sample / sixteen waves: 32-32-10 at 3000 samples 41 / 36, 16384 89 / 68;
+// 64-64-10 62 / 44, 165 / 94; 16-200-4 85 / 49, 250 / 114; 8-8-2 32 / 32, 57 / 58.  Larger batches (MLP_FUSED_MAX_BATCH) have not been measured and take the chain.
 //   f = x W1 + b1, g = tanh f, z = g W2 + b2, p = softmax z, and along v:
 //   f_t = x W1_t + b1_t, g_t = g' f_t, z_t = g_t W2 + g W2_t + b2_t
 //   dz = (p - onehot) s, dz_t = p (z_t - <p, z_t>) s;  dg = dz W2^T, dg_t = dz_t W2^T + dz W2_t^T
 //   da_t = g' dg_t + g'' f_t dg,  g' = 1 - g^2, g'' = -2 g g'
 //   (Hv)_W2 = g_t^T dz + g^T dz_t, (Hv)_b2 = sum dz_t, (Hv)_W1 = x^T da_t, (Hv)_b1 = sum da_t
 #include "engine.h"
+#include "lanczos_small.h"
 
 #include <algorithm>
 #include <cmath>
 
 namespace hf {
 
-constexpr int MLP_ROWS = 8;  // samples a block works on at a time: 32 lanes each
+constexpr int MLP_ROWS = 8, MLP_THREADS = 1024;  // samples a block works on at a time: two waves each
+constexpr int64_t MLP_ADD_IN_UPDATE = 65536;      // most floats of shares that the one block of an update adds
 
 struct MlpP {
   const float *params, *v, *x;
@@ -38,23 +43,29 @@ struct MlpP {
 
 // LDS floats: W1, W1_t, b1, b1_t; W2, W2_t with rows of LO = O | 1 floats (lanes that walk down a column then
 // hit different banks); b2, b2_t; the block's share of H v; the rows' buffers.
-__host__ __device__ inline int64_t mlp_lds_floats(int64_t I, int64_t H, int64_t O) {
+__host__ __device__ inline int64_t mlp_lds_floats(int64_t I, int64_t H, int64_t O, int rows) {
   const int64_t LO = O | 1;
-  return 2 * (I * H + H + H * LO + O) + (I * H + H + H * O + O) + MLP_ROWS * (I + 4 * H + 4 * LO);
+  return 2 * (I * H + H + H * LO + O) + (I * H + H + H * O + O) + rows * (I + 4 * H + 4 * LO);
 }
 
-__device__ __forceinline__ float half_sum(float v) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v += __shfl_xor(v, o, 32);
-  return v;
-}
-__device__ __forceinline__ float half_max(float v) {
-#pragma unroll
-  for (int o = 16; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 32));
-  return v;
+// Sum over k = k0, k0 + step, .. < K of a[k] u[k st], and of b[k] w[k st] if there is a b.
+__device__ __forceinline__ float lds_dot(const float* a, const float* u, const float* b, const float* w, int st, int k0, int step, int K) {
+  float s = 0.f;
+  if (!b) {
+#pragma unroll 4
+    for (int k = k0; k < K; k += step) s = fmaf(a[k], u[k * st], s);
+  } else {
+#pragma unroll 4
+    for (int k = k0; k < K; k += step) s = fmaf(b[k], w[k * st], fmaf(a[k], u[k * st], s));
+  }
+  return s;
 }
 
-__global__ __launch_bounds__(256) void mlp_hvp_kernel(MlpP p) {
+// Two waves a sample (WPS), one for the primal of each sum and one for the tangent, or one for both.  The three matrix-vector products share their code, as do
+// the blocks of H v: a launch fetches its instructions anew and runs through them once, so that a kernel waits for its own size.
+template <int WPS>
+__global__ __launch_bounds__(MLP_THREADS) void mlp_hvp_kernel(MlpP p) {
+  constexpr int MLP_ROWS = MLP_THREADS / 64 / WPS;
   extern __shared__ float sm[];
   const int t = threadIdx.x, I = p.I, H = p.H, O = p.O, LO = O | 1, IH = I * H, HO = H * O, n = IH + H + HO + O;
   float* w1 = sm;        float* w1t = w1 + IH;
@@ -63,149 +74,173 @@ __global__ __launch_bounds__(256) void mlp_hvp_kernel(MlpP p) {
   float* b2 = w2t + H * LO; float* b2t = b2 + O;
   float* acc = b2t + O;
   float* X = acc + n;                                              // [rows][I]
-  float* G = X + MLP_ROWS * I;    float* Gt = G + MLP_ROWS * H;    // g, g_t
-  float* Ft = Gt + MLP_ROWS * H;  float* At = Ft + MLP_ROWS * H;   // f_t, da_t
-  float* Z = At + MLP_ROWS * H;   float* Zt = Z + MLP_ROWS * LO;   // z, z_t
+  float* G = X + MLP_ROWS * I;    float* Ft = G + MLP_ROWS * H;    // g, f_t
+  float* E = Ft + MLP_ROWS * H;   float* Et = E + MLP_ROWS * H;    // g_t, then dg, then g_t again; dg_t, then da_t
+  float* Z = Et + MLP_ROWS * H;   float* Zt = Z + MLP_ROWS * LO;   // z, z_t
   float* D = Zt + MLP_ROWS * LO;  float* Dt = D + MLP_ROWS * LO;   // dz, dz_t
-  __shared__ int cnt[4], bad[4];
+  __shared__ int cnt[MLP_THREADS / 64], bad[MLP_THREADS / 64];
   __shared__ double rowloss[MLP_ROWS];
+  __shared__ float one;
 
-  const int row = t >> 5, lane = t & 31;  // each half wave owns one sample
+  const int wave = t >> 6, lane = t & 63, row = wave / WPS, lane_r = t % (64 * WPS);
+  const bool first_wave = wave % WPS == 0;
   // all loads of the start are independent and in flight together: weights, direction, labels, the first samples
   const int r_first = blockIdx.x * MLP_ROWS;
-  for (int i = lane; i < I; i += 32) X[row * I + i] = r_first + row < p.B ? p.x[(int64_t)(r_first + row) * I + i] : 0.f;
-#pragma unroll 8
-  for (int j = t; j < n; j += 256) {
+  for (int i = lane_r; i < I; i += 64 * WPS) X[row * I + i] = r_first + row < p.B ? p.x[(int64_t)(r_first + row) * I + i] : 0.f;
+#pragma unroll 4
+  for (int j = t; j < n; j += MLP_THREADS) {
     const float w = p.params[j], d = p.v[j];
-    float *dst = w1 + j, *dst_t = w1t + j;
+    int at = j, gap = IH;  // the weight's place, and how far behind it its tangent lies
     if (j >= IH) {
-      if (j < IH + H) { dst = b1 + (j - IH); dst_t = b1t + (j - IH); }
-      else if (j < IH + H + HO) {
-        const int q = j - IH - H, h = q / O, at = h * LO + q - h * O;
-        dst = w2 + at; dst_t = w2t + at;
-      } else { dst = b2 + (j - IH - H - HO); dst_t = b2t + (j - IH - H - HO); }
+      const int q = j - IH - H;
+      at = j + IH;
+      gap = H;
+      if (q >= HO) { at += H + 2 * H * LO - HO; gap = O; }
+      else if (q >= 0) { at += H + q / O * (LO - O); gap = H * LO; }
     }
-    *dst = w;
-    *dst_t = d;
+    sm[at] = w;
+    sm[at + gap] = d;
     acc[j] = 0.f;
   }
   // every block counts the valid labels of the whole batch itself
   int c = 0, b = 0;
-  for (int i = t; i < p.B; i += 256) {
+  for (int i = t; i < p.B; i += MLP_THREADS) {
     const int y = p.labels[i];
     c += (y >= 0);
     b |= (y >= O);
   }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) { c += __shfl_xor(c, o, 64); b |= __shfl_xor(b, o, 64); }
-  if ((t & 63) == 0) { cnt[t >> 6] = c; bad[t >> 6] = b; }
+  c = (int)lanes_sum<1>((float)c);  // (at most MLP_FUSED_MAX_BATCH: exact)
+  b = __any(b);
+  if (lane == 0) { cnt[wave] = c; bad[wave] = b; }
+  if (t == 0) one = 1.f;
   __syncthreads();
-  const int nv = cnt[0] + cnt[1] + cnt[2] + cnt[3];
+  int nv = 0, any_bad = 0;
+  for (int w = 0; w < MLP_THREADS / 64; ++w) { nv += cnt[w]; any_bad |= bad[w]; }
   if (blockIdx.x == 0 && t == 0) {
-    const int bits = ((bad[0] | bad[1] | bad[2] | bad[3]) ? 2 : 0) | (nv == 0 ? 4 : 0);
+    const int bits = (any_bad ? 2 : 0) | (nv == 0 ? 4 : 0);
     p.flags[0] = p.accumulate ? (p.flags[0] | bits) : bits;
     p.flags[1] = nv;
   }
   const float invN = p.seed / (float)max(1, nv);
   double loss = 0.0;
+#pragma unroll 1
   for (int r0 = r_first; r0 < p.B; r0 += gridDim.x * MLP_ROWS) {
     const int gr = r0 + row;
     const bool in = gr < p.B;
     if (r0 != r_first) {
       __syncthreads();  // the products of the previous samples are done with the row buffers
-      for (int i = lane; i < I; i += 32) X[row * I + i] = in ? p.x[(int64_t)gr * I + i] : 0.f;
+      for (int i = lane_r; i < I; i += 64 * WPS) X[row * I + i] = in ? p.x[(int64_t)gr * I + i] : 0.f;
       __syncthreads();
     }
-    for (int h = lane; h < H; h += 32) {
-      float f = b1[h], ft = b1t[h];
-#pragma unroll 8
-      for (int i = 0; i < I; ++i) {
-        const float xv = X[row * I + i];
-        f = fmaf(xv, w1[i * H + h], f);
-        ft = fmaf(xv, w1t[i * H + h], ft);
+    // ph 0: f, f_t; 1: z, z_t and from them dz, dz_t; 2: dg, dg_t
+#pragma unroll 1
+    for (int ph = 0; ph < 3; ++ph) {
+      const int J = ph == 1 ? O : H, K = ph == 0 ? I : ph == 1 ? H : O;
+      const int sk = ph == 0 ? H : ph == 1 ? LO : 1, sj = ph == 2 ? LO : 1;
+      const float* const a = ph == 0 ? X + row * I : ph == 1 ? G + row * H : D + row * LO;
+      int per = 8;  // lanes of different j; where J leaves lanes over, several share the k of one
+      while (per < J && per < 64) per <<= 1;
+#pragma unroll 1
+      for (int tang = WPS == 2 ? wave & 1 : 0; tang < (WPS == 2 ? (wave & 1) + 1 : 2); ++tang) {
+        const float* const u = ph == 0 ? (tang ? w1t : w1) : (tang ? w2t : w2);
+        const float* const a2 = !tang || ph == 0 ? nullptr : ph == 1 ? E + row * H : Dt + row * LO;
+        const float* const bias = ph == 0 ? (tang ? b1t : b1) : (tang ? b2t : b2);
+        float* const dst = ph == 0 ? (tang ? Ft : G) + row * H : ph == 1 ? (tang ? Zt : Z) + row * LO : (tang ? Et : E) + row * H;
+        for (int j = lane & (per - 1); j < ((J + per - 1) & -per); j += per) {
+          float s = 0.f;
+          if (j < J) s = lds_dot(a, u + j * sj, a2, w2 + j * sj, sk, lane / per, 64 / per, K);
+          if (per <= 32) s += lane_across<32>(s);
+          if (per <= 16) s += lane_across<16>(s);
+          if (per <= 8) s += lane_across<8>(s);
+          if (lane < per && j < J) {
+            if (ph < 2) s += bias[j];
+            if (ph == 0 && !tang) s = tanhf(s);
+            dst[j] = s;
+          }
+        }
       }
-      const float g = tanhf(f);
-      G[row * H + h] = g;
-      Ft[row * H + h] = ft;
-      Gt[row * H + h] = (1.f - g * g) * ft;
-    }
-    __syncthreads();
-    const int y = in ? p.labels[gr] : -1;
-    const bool valid = y >= 0 && y < O;
-    float m = -INFINITY;
-    for (int o = lane; o < O; o += 32) {
-      float z = b2[o], zt = b2t[o];
-#pragma unroll 8
-      for (int h = 0; h < H; ++h) {
-        const float g = G[row * H + h], w = w2[h * LO + o];
-        z = fmaf(g, w, z);
-        zt = fmaf(Gt[row * H + h], w, zt);
-        zt = fmaf(g, w2t[h * LO + o], zt);
-      }
-      Z[row * LO + o] = z;
-      Zt[row * LO + o] = zt;
-      m = fmaxf(m, z);
-    }
-    m = half_max(m);
-    float se = 0.f, sd = 0.f;
-    for (int o = lane; o < O; o += 32) {
-      const float e = __expf(Z[row * LO + o] - m);
-      se += e;
-      sd = fmaf(e, Zt[row * LO + o], sd);
-    }
-    se = half_sum(se);
-    sd = half_sum(sd);
-    const float inv = 1.f / se, pz = sd * inv;
-    for (int o = lane; o < O; o += 32) {
-      const float pv = __expf(Z[row * LO + o] - m) * inv;
-      D[row * LO + o] = valid ? (pv - (o == y ? 1.f : 0.f)) * invN : 0.f;
-      Dt[row * LO + o] = valid ? pv * (Zt[row * LO + o] - pz) * invN : 0.f;
-    }
-    __syncthreads();
-    if (valid && lane == 0) loss += (double)(logf(se) + m - Z[row * LO + y]);
-    for (int h = lane; h < H; h += 32) {
-      float dg = 0.f, dgt = 0.f;
-#pragma unroll 8
-      for (int o = 0; o < O; ++o) {
-        const float d = D[row * LO + o], w = w2[h * LO + o];
-        dg = fmaf(d, w, dg);
-        dgt = fmaf(Dt[row * LO + o], w, dgt);
-        dgt = fmaf(d, w2t[h * LO + o], dgt);
-      }
-      const float g = G[row * H + h], g1 = 1.f - g * g;
-      At[row * H + h] = g1 * dgt - 2.f * g * g1 * Ft[row * H + h] * dg;
-    }
-    __syncthreads();
-    for (int j = t; j < n; j += 256) {
-      float s = acc[j];
-      if (j < IH) {
-        const int i = j / H, h = j - i * H;
-#pragma unroll
-        for (int r = 0; r < MLP_ROWS; ++r) s = fmaf(X[r * I + i], At[r * H + h], s);
-      } else if (j < IH + H) {
-#pragma unroll
-        for (int r = 0; r < MLP_ROWS; ++r) s += At[r * H + j - IH];
-      } else if (j < IH + H + HO) {
-        const int q = j - IH - H, h = q / O, o = q - h * O;
-#pragma unroll
-        for (int r = 0; r < MLP_ROWS; ++r) {
-          s = fmaf(Gt[r * H + h], D[r * LO + o], s);
-          s = fmaf(G[r * H + h], Dt[r * LO + o], s);
+      __syncthreads();
+      if (ph == 1) {
+        if (first_wave) {
+          const int y = in ? p.labels[gr] : -1;
+          const bool valid = y >= 0 && y < O;
+          const float *z = Z + row * LO, *zt = Zt + row * LO;
+          float m = -INFINITY;
+          for (int o = lane; o < O; o += 64) m = fmaxf(m, z[o]);
+          m = wave_max_f(m);
+          float se = 0.f, sd = 0.f;
+          for (int o = lane; o < O; o += 64) {
+            const float e = __expf(z[o] - m);
+            se += e;
+            sd = fmaf(e, zt[o], sd);
+          }
+          se = lanes_sum<1>(se);
+          sd = lanes_sum<1>(sd);
+          const float inv = 1.f / se, pz = sd * inv;
+          for (int o = lane; o < O; o += 64) {
+            const float pv = __expf(z[o] - m) * inv;
+            D[row * LO + o] = valid ? (pv - (o == y ? 1.f : 0.f)) * invN : 0.f;
+            Dt[row * LO + o] = valid ? pv * (zt[o] - pz) * invN : 0.f;
+          }
+          if (valid && lane == 0) loss += (double)(logf(se) + m - z[y]);
         }
       } else {
+        for (int j = t; j < MLP_ROWS * H; j += MLP_THREADS) {
+          const float g = G[j], g1 = 1.f - g * g, ft = Ft[j];
+          if (ph == 2) Et[j] = g1 * Et[j] - 2.f * g * g1 * ft * E[j];
+          E[j] = g1 * ft;
+        }
+      }
+      __syncthreads();
+    }
+    // the blocks of H v as sums over the rows of x y (+ x' y')
+#pragma unroll 1
+    for (int j = t; j < n; j += MLP_THREADS) {
+      const float *x = &one, *y, *x2 = nullptr, *y2 = nullptr;
+      int sx = 0, sy = H;
+      if (j < IH) {
+        const int i = j / H;
+        x = X + i; sx = I;
+        y = Et + (j - i * H);
+      } else if (j < IH + H) {
+        y = Et + (j - IH);
+      } else if (j < IH + H + HO) {
+        const int q = j - IH - H, h = q / O, o = q - h * O;
+        x = E + h; sx = H; y = D + o; sy = LO;
+        x2 = G + h; y2 = Dt + o;
+      } else {
+        y = Dt + (j - IH - H - HO); sy = LO;
+      }
+      float s = acc[j];
 #pragma unroll
-        for (int r = 0; r < MLP_ROWS; ++r) s += Dt[r * LO + j - IH - H - HO];
+      for (int r = 0; r < MLP_ROWS; ++r) s = fmaf(x[r * sx], y[r * sy], s);
+      if (x2) {
+#pragma unroll
+        for (int r = 0; r < MLP_ROWS; ++r) s = fmaf(x2[r * H], y2[r * LO], s);
       }
       acc[j] = s;
     }
   }
-  if (lane == 0) rowloss[row] = loss;
-  for (int j = t; j < n; j += 256) p.part[(int64_t)blockIdx.x * n + j] = acc[j];
+  if (first_wave && lane == 0) rowloss[row] = loss;
+  for (int j = t; j < n; j += MLP_THREADS) p.part[(int64_t)blockIdx.x * n + j] = acc[j];
   __syncthreads();
   if (t == 0) {
     double s = 0.0;
     for (int r = 0; r < MLP_ROWS; ++r) s += rowloss[r];
     p.part_loss[blockIdx.x] = s;
+  }
+}
+
+// The loss of a product, by one wave: the blocks' shares of it, and what the host reads.
+__device__ __forceinline__ void mlp_loss(const double* part_loss, int nblk, const int* flags, double weight, int accumulate, double* loss, double* host) {
+  const int lane = threadIdx.x & 63;
+  double l = 0.0;
+  for (int b = lane; b < nblk; b += 64) l += part_loss[b];
+  l = wave_sum_d(l);
+  if (lane == 0) {
+    l = (accumulate ? loss[0] : 0.0) + weight * l / (double)max(1, flags[1]);
+    loss[0] = l;
+    host[0] = (double)flags[0]; host[1] = (double)flags[1]; host[2] = l;
   }
 }
 
@@ -230,24 +265,43 @@ __global__ __launch_bounds__(256) void mlp_sum_kernel(const float* __restrict__ 
     for (int g = 0; g < 8; ++g) s += red[g][lane];
     out[j] = (float)s;
   }
-  if (blockIdx.x == 0 && t >= 64 && t < 128) {
-    double l = 0.0;
-    for (int b = t - 64; b < nblk; b += 64) l += part_loss[b];
+  if (blockIdx.x == 0 && t >= 64 && t < 128) mlp_loss(part_loss, nblk, flags, weight, accumulate, loss, host);
+}
+
+// The sum of few shares and the Lanczos update behind it, by one block.
+__global__ __launch_bounds__(1024) void mlp_sum_update_kernel(const float* __restrict__ part, const double* __restrict__ part_loss, int nblk,
+                                                              const int* __restrict__ flags, double weight, double* __restrict__ loss,
+                                                              double* __restrict__ host, LzSmall u) {
+  extern __shared__ double sm_c[];  // [nq + 1] coefficients (full), then w
+  float* const w = (float*)(sm_c + (u.full ? u.nq + 1 : 0));
+  __shared__ double red[16];
+  if (u.chained && u.scal[S_STOP] != 0.0) return;
+  const int t = threadIdx.x, n = u.n, f0 = flags[0], f1 = flags[1];
+  for (int j = t; j < n; j += 1024) {
+    double g[8] = {}, s = 0.0;  // in the order of mlp_sum_kernel: runs and single steps agree bit for bit
+    int b = 0;
+#pragma unroll 2
+    for (; b + 8 <= nblk; b += 8)
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
-    if (t == 64) {
-      l = (accumulate ? loss[0] : 0.0) + weight * l / (double)max(1, flags[1]);
-      loss[0] = l;
-      host[0] = (double)flags[0]; host[1] = (double)flags[1]; host[2] = l;
-    }
+      for (int q = 0; q < 8; ++q) g[q] += (double)part[(int64_t)(b + q) * n + j];
+#pragma unroll
+    for (int q = 0; q < 7; ++q)
+      if (b + q < nblk) g[q] += (double)part[(int64_t)(b + q) * n + j];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += g[q];
+    w[j] = (float)s;
   }
+  if (t >= 960) mlp_loss(part_loss, nblk, flags, weight, 0, loss, host);
+  __syncthreads();
+  if (u.full) lz_small_full_block(u, w, sm_c, red, f0, f1);
+  else lz_small_three_block(u, w, red, f0, f1);
 }
 
 int mlp_blocks(int B) { return std::min(MLP_BLOCKS, (B + MLP_ROWS - 1) / MLP_ROWS); }
 
 // 150 of the 160 KB of LDS.
 bool mlp_fused_fits(const hf_model_desc& d) {
-  return d.param_dtype == HF_F32 && mlp_lds_floats(d.mlp_in, d.mlp_hidden, d.mlp_out) * 4 <= 150 * 1024;
+  return d.param_dtype == HF_F32 && mlp_lds_floats(d.mlp_in, d.mlp_hidden, d.mlp_out, MLP_ROWS) * 4 <= 150 * 1024;
 }
 
 }  // namespace hf
@@ -260,12 +314,23 @@ int hf_ctx::hvp_mlp_fused(const float* params, const float* inputs, const int32_
   p.params = params; p.v = v; p.x = inputs; p.labels = labels;
   p.B = B; p.I = desc.mlp_in; p.H = desc.mlp_hidden; p.O = desc.mlp_out;
   p.seed = seed; p.accumulate = acc_mode; p.part = mlp_part; p.part_loss = mlp_part_loss; p.flags = flags;
-  const int lds = (int)(mlp_lds_floats(p.I, p.H, p.O) * 4), nb = mlp_blocks(B);
-  static OncePerDevice once;
-  hipError_t e = once.lds_limit((const void*)mlp_hvp_kernel, 150 * 1024);
+  const int nb = mlp_blocks(B);
+  constexpr int LDS_MAX = 150 * 1024;
+  // Several turns a block: one wave a sample where LDS has room for sixteen (figures above; with two waves 32-32-10 at 16384 samples 81, 64-64-10
+  // 112, 8-8-2 67).
+  const int64_t lds16 = mlp_lds_floats(p.I, p.H, p.O, 2 * MLP_ROWS) * 4, lds8 = mlp_lds_floats(p.I, p.H, p.O, MLP_ROWS) * 4;
+  const bool one_wave = B > MLP_BLOCKS * MLP_ROWS && lds16 <= LDS_MAX;
+  static OncePerDevice once1, once2;
+  hipError_t e = one_wave ? once1.lds_limit((const void*)mlp_hvp_kernel<1>, LDS_MAX) : once2.lds_limit((const void*)mlp_hvp_kernel<2>, LDS_MAX);
   if (e == hipSuccess) {
-    hipLaunchKernelGGL(mlp_hvp_kernel, dim3(nb), dim3(256), lds, st, p);
-    hipLaunchKernelGGL(mlp_sum_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, mlp_part, mlp_part_loss, nb, (int)n, flags,
+    if (one_wave) hipLaunchKernelGGL(mlp_hvp_kernel<1>, dim3(nb), dim3(MLP_THREADS), (size_t)lds16, st, p);
+    else hipLaunchKernelGGL(mlp_hvp_kernel<2>, dim3(nb), dim3(MLP_THREADS), (size_t)lds8, st, p);
+    if (then_update && !acc_mode && nb * n <= MLP_ADD_IN_UPDATE) {
+      hipLaunchKernelGGL(mlp_sum_update_kernel, dim3(1), dim3(1024), (size_t)then_update->lds(), st, mlp_part, mlp_part_loss, nb, flags,
+                         (double)seed, loss_dev, host_hvp, *then_update);
+      then_update = nullptr;
+    } else
+      hipLaunchKernelGGL(mlp_sum_kernel, dim3((unsigned)((n + 31) / 32)), dim3(256), 0, st, mlp_part, mlp_part_loss, nb, (int)n, flags,
                        (double)seed, acc_mode, out, loss_dev, host_hvp);
     e = hipGetLastError();
   }
