@@ -413,7 +413,9 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
   CK(launch_zero_ranges(zp.data(), zn.data(), (int)zp.size(), st));
   // The Lanczos update leaves the bf16 copy of q_{k+1} in vb; every other direction is converted here.
   if (bf && !(vb_of != nullptr && vb_of == v)) {
-    CK(launch_f32_to_bf16(v, vb, n, st));
+    // (embeddings read the direction itself, so an untied table, a fifth of a 7B model with two layers, is left out)
+    const int64_t from = off_head >= 0 ? layers_begin / 8 * 8 : 0;
+    CK(launch_f32_to_bf16(v + from, vb + from, n - from, st));
     vb_cur = vb;
   }
   vb_of = nullptr;
