@@ -253,7 +253,7 @@ int32_t hf_lanczos_init(hf_ctx* ctx, const float* q0_dev, int32_t reorth, void* 
     hipError_t e_ = (expr);                                                                         \
     if (e_ != hipSuccess) return c->fail(HF_EDEVICE, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
-  CKI(launch_fill_f32((float*)c->scal, S_COUNT * 2, 0.f, st));
+  CKI(launch_fill_f32((float*)c->scal, S_DEVICE * 2, 0.f, st));
   if ((uintptr_t)q0_dev & 15) {  // the kernels read 16 bytes at a time: stage an unaligned probe in r
     CKI(hipMemcpyAsync(c->lz_vec[c->ir], q0_dev, (size_t)c->n * 4, hipMemcpyDeviceToDevice, st));
     q0_dev = c->lz_vec[c->ir];
@@ -269,6 +269,7 @@ int32_t hf_lanczos_init(hf_ctx* ctx, const float* q0_dev, int32_t reorth, void* 
   bf16* vdst = c->bf ? ((bq && row0) ? nullptr : ((rows && c->basis_bf) ? c->basis_bf : c->vb)) : nullptr;
   CKI(lz_scale(q0_dev, rows ? nullptr : c->lz_vec[c->iq], row0, bq, vdst, c->n, c->scal, S_Q0NORM, 0.0, nullptr, st));
   c->lz_k = 0;
+  c->lz_r_is_q = false;
   c->lz_done = 0;
   c->lz_beta_prev = 0.0;
   c->vb_cur = c->bf ? ((bq && row0) ? (const bf16*)row0 : vdst) : nullptr;
@@ -312,6 +313,10 @@ int32_t hf_lanczos_get_vector(hf_ctx* ctx, int32_t which, float* dst_dev, void* 
   hipStream_t st = (hipStream_t)hip_stream;
   if (!dst_dev) return c->fail(HF_EINVAL, "hf_lanczos_get_vector: NULL dst_dev");
   if (c->lz_k < 0) return c->fail(HF_ESTATE, "hf_lanczos_get_vector: no iteration in progress");
+  if (which == 2 && c->lz_r_is_q && c->lz_k > 0) {
+    CKI(lz_times(c->cur_q(), c->lz_beta_prev, dst_dev, c->n, st));
+    return HF_OK;
+  }
   if (which >= 0 && which < 3) {
     const float* src = which == 0 ? c->cur_q() : (which == 1 ? c->prev_q() : c->lz_vec[c->ir]);
     CKI(hipMemcpyAsync(dst_dev, src, (size_t)c->n * 4, hipMemcpyDeviceToDevice, st));
@@ -594,7 +599,7 @@ int32_t hf_lanczos_import(hf_ctx* ctx, const void* state_dev, int64_t bytes, voi
   const char* base = (const char*)state_dev;
   const int64_t vb = lz_align(c->n * 4);
   c->iq = 0; c->iqp = 1; c->ir = 2;
-  CKI(launch_fill_f32((float*)c->scal, S_COUNT * 2, 0.f, st));
+  CKI(launch_fill_f32((float*)c->scal, S_DEVICE * 2, 0.f, st));
   // (with an fp32 basis q_k and q_{k-1} are also rows k and k - 1 below, which is where the
   // iteration reads them; the copies in lz_vec serve a full basis, whose last q has no row)
   CKI(hipMemcpyAsync(c->lz_vec[0], base + 128, (size_t)c->n * 4, hipMemcpyDeviceToDevice, st));
@@ -610,6 +615,7 @@ int32_t hf_lanczos_import(hf_ctx* ctx, const void* state_dev, int64_t bytes, voi
   CKI(hipStreamSynchronize(st));
   c->lz_k = (int)h.k;
   c->lz_reorth = (int)h.reorth;
+  c->lz_r_is_q = false;
   c->lz_done = (int)h.done;
   c->lz_beta_prev = h.beta_prev;
   return HF_OK;

@@ -137,6 +137,7 @@ struct hf_ctx {
   int lz_reorth = 0;
   int lz_done = 0;
   double lz_beta_prev = 0.0;    // beta_{k-1}
+  bool lz_r_is_q = false;       // the last update left no r: it is beta_{k-1} q_k
   bool lz_rows_are_vectors() const { return lz_reorth == HF_REORTH_FULL && desc.basis_dtype == HF_F32; }
   float* cur_q() const;         // q_k
   float* prev_q() const;        // q_{k-1} (meaningful for k >= 1)

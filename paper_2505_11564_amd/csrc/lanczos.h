@@ -11,13 +11,17 @@ namespace hf {
 enum {
   S_ALPHA = 0,       // alpha_k
   S_BETA = 1,        // current ||r|| (beta_k once the iteration's updates are done)
-  S_NRM_BEFORE = 3,  // ||r|| before the orthogonalisation pass in flight
+  S_NRM_BEFORE = 3,  // ||r|| before the orthogonalisation pass in flight; -1.0 after a pass that wrote q_{k+1} itself: there is no r then
   S_REDO = 4,        // 1.0 when a second orthogonalisation pass is required
   S_Q0NORM = 5,      // ||q0|| before normalisation
   S_FLAG0 = 6,       // error bits and number of valid labels of the Hessian-vector product that made
   S_FLAG1 = 7,       //   w, copied here by the kernel that writes q_{k+1}
   S_STOP = 2,        // 1.0 once an iteration of a chained run (host ahead of the results) could not advance
-  S_COUNT = 8
+  S_COUNT = 8,
+  // device only
+  S_EST = 8,         // > 0: the first orthogonalisation pass writes q_{k+1} itself, with this estimate of beta_k
+  S_FIX = 9,         // what that q_{k+1} still has to be multiplied by; 1.0: nothing
+  S_DEVICE = 10
 };
 
 constexpr int HF_MAX_M = 2000;  // most basis vectors a context may hold
@@ -32,7 +36,7 @@ hipError_t lz_norm_q0(const float* z, int64_t n, double* scal, double* partials,
 hipError_t lz3_update(const float* w, const float* q, float* qp, bf16* vb, int64_t n, int use_prev, double beta_prev,
                       double tol, const int* flags, double* scal, double* partials, hipStream_t st);
 // q_{k+1} = src / scal[idx] into dst (fp32, may be NULL), its basis row (may be NULL) and vb (bf16,
-// may be NULL), under the same test.
+// may be NULL), under the same test.  idx = S_BETA after a pass that wrote q_{k+1} itself: only what S_FIX asks for.
 hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, bf16* vb, int64_t n, double* scal, int idx,
                     double tol, const int* flags, hipStream_t st);
 // One classical Gram-Schmidt pass of r against Q[0..nq); pass 1 is a no-op
@@ -41,13 +45,23 @@ hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, b
 // reads rows 0 .. nq-3 from them.
 hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int pass,
                           double* scal, double* c, double* partials, hipStream_t st);
-// The first pass applied to w = H q_k itself against an fp32 basis holding q_0 .. q_k (nq = k + 1):
-// also yields alpha_k, in place of lz_axpy_dot and lz_axpy_nrm.
-hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, double* scal,
+// Where q_{k+1} goes (fp32; bf16, may be NULL), and the test that decides whether it may be written.
+struct LzNext {
+  float* q;
+  bf16* qb;
+  const int* flags;
+  double tol;
+};
+// The first pass applied to w = H q_k itself against an fp32 basis holding q_0 .. q_k (nq = k + 1): also yields alpha_k.  Writes
+// q_{k+1} instead of r where beta_k is known well enough beforehand (scal[S_EST] > 0; see lz_direct_scal_kernel).
+// c: nq + 4 doubles, partials: (nq + 4) * LZ_NBLK.
+hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, const LzNext& next, double* scal,
                             double* c, double* partials, hipStream_t st);
 // The same for a bf16 basis: q_k and q_{k-1} come from the fp32 working vectors, rows 0 .. k-2 from the basis.
 hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, const float* qk, float* r, int64_t n, int k,
-                                 double* scal, double* c, double* partials, hipStream_t st);
+                                 const LzNext& next, double* scal, double* c, double* partials, hipStream_t st);
+// dst = f src
+hipError_t lz_times(const float* src, double f, float* dst, int64_t n, hipStream_t st);
 // Vectors so short that one block does the whole update of an iteration (see lanczos.hip): full orthogonalisation against an
 // fp32 basis, and the three-term recurrence.  `host`: S_COUNT doubles of pinned host memory that also receive the scalars.
 // chained: return at once after an iteration that could not advance; the three-term kernel takes beta_{k-1} from scal.

@@ -13,9 +13,10 @@
 // With a stored basis the first Gram-Schmidt pass is applied to w itself (against q_0 .. q_k; with
 // a bf16 basis q_k and q_{k-1} are taken from the fp32 working vectors): alpha_k is its k-th
 // coefficient and the two three-term subtractions are part of the pass:
-//   lz_qtr      : c = Q^T r      (k+1 dot products, Q read once)
-//   lz_sub_qc   : r -= Q c;  beta_k = ||r||   (Q read once)
-//   lz_scale    : q_{k+1} = r / beta_k, written to its basis row                          (1R + 1W)
+//   lz_qtr      : c = Q^T w      (k+1 dot products, Q read once)
+//   lz_sub_qc   : q_{k+1} = (w - Q c) / beta_k, written to its basis row (Q read once), with beta_k from c and <w, w>
+// or, where that difference has lost digits or a second pass is likely, r = w - Q c, the second pass, and
+//   lz_scale    : q_{k+1} = r / beta_k                                                     (1R + 1W)
 // Scalars stay on the device (array `scal` of doubles) so consecutive kernels
 // need no host round trip; the kernels that write q_{k+1} test beta_k against the
 // tolerance (and the error flags of the product that made w) themselves and leave
@@ -179,7 +180,13 @@ __global__ __launch_bounds__(256) void lz_finish_kernel(const double* partials, 
   if (what == 0) scal[S_Q0NORM] = sqrt(s);
   else if (what == 2) { scal[S_BETA] = sqrt(s); scal[S_REDO] = 0.0; }
   else {
-    const double nb = sqrt(s);
+    const double nb = sqrt(s), est = pass == 0 ? scal[S_EST] : 0.0;
+    if (est > 0.0) {  // the vector written is q_{k+1}: its norm is 1 up to the error of the estimate (fp32: 6e-8)
+      scal[S_BETA] = est * nb;
+      scal[S_FIX] = fabs(nb - 1.0) > 6e-8 ? 1.0 / nb : 1.0;
+      scal[S_NRM_BEFORE] = -1.0;
+      return;
+    }
     scal[S_BETA] = nb;
     scal[S_REDO] = (pass == 0 && nb < scal[S_NRM_BEFORE] * 0.70710678118654752) ? 1.0 : 0.0;
     scal[S_NRM_BEFORE] = nb;
@@ -244,11 +251,15 @@ __global__ __launch_bounds__(256) void lz3_normalise_kernel(const float* __restr
 // basis, fp32 or bf16 rounded to nearest even), vb (bf16 copy for the next Hessian-vector product).
 // One thread per two 16-byte groups.
 template <typename BT>
-__global__ __launch_bounds__(256) void lz_scale_kernel(const float* __restrict__ src, float* __restrict__ dst,
-                                                       BT* __restrict__ basis, bf16* __restrict__ vb, int64_t n,
+__global__ __launch_bounds__(256) void lz_scale_kernel(const float* src, float* dst, BT* basis, bf16* __restrict__ vb, int64_t n,
                                                        double* scal, int idx, double tol, const int* flags) {
   if (!lz_may_advance(scal, idx, tol, flags)) return;
-  const float inv = (float)(1.0 / scal[idx]);
+  float inv = (float)(1.0 / scal[idx]);
+  if (idx == S_BETA && scal[S_EST] > 0.0) {  // q_{k+1} is there already
+    if (scal[S_FIX] == 1.0) return;
+    inv = (float)scal[S_FIX];
+    src = dst ? dst : (const float*)basis;
+  }
   const int64_t n4 = n >> 2, half = (int64_t)gridDim.x * 256;
   const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, i1 = i0 + half;
   const bool ok0 = i0 < n4, ok1 = i1 < n4;
@@ -326,7 +337,9 @@ __device__ __forceinline__ void load_r_slice(const float* __restrict__ r, int64_
 #pragma unroll
     for (int h = 0; h < V::E / 4; ++h) {
       float4 x = make_float4(0.f, 0.f, 0.f, 0.f);
-      if (e0 + h * 4 + 4 <= n) x = *(const float4*)(r + e0 + h * 4);
+      // (non-temporal where a wave's load covers whole lines: 40.6 -> 38.8 ms for thirty passes of an fp32 basis at n = 1.2e8; beside bf16 rows, 32
+      // bytes a lane, 36.5 -> 39.9 ms for ten at 1.3e9)
+      if (e0 + h * 4 + 4 <= n) x = V::E == 4 ? ldnt4(r + e0 + h * 4, 0) : *(const float4*)(r + e0 + h * 4);
       else {
         float t4[4] = {0.f, 0.f, 0.f, 0.f};
         for (int q = 0; q < 4; ++q) if (e0 + h * 4 + q < n) t4[q] = r[e0 + h * 4 + q];
@@ -356,9 +369,9 @@ __device__ __forceinline__ void load_q_slice(const BT* __restrict__ q, int64_t b
 }
 
 // c_j = <Q_j, r>: partials[j * nblk + block] (fp64), summed by lz_qtr_finish_kernel.
-// RR: one more result, c_nq = <r, r>.
 // x0, x1 (optional, fp32 vectors): two more "rows" after the nq stored ones, results nq and nq + 1
-// (x1 alone is not allowed); the <r, r> result then follows them.
+// (x1 alone is not allowed).
+// RR: four more results after those of the rows: <r, r>, the last row's and the one before its product with itself and with each other.
 template <typename BT, bool RR = false, bool XR = false>
 __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, int64_t ldq, const float* __restrict__ r,
                                                      int64_t n, int nq, int64_t nslices, const double* scal, int pass,
@@ -369,7 +382,7 @@ __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, i
   if (pass == 1 && scal[S_REDO] == 0.0) return;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nx = XR ? (x0 ? 1 : 0) + (x1 ? 1 : 0) : 0;
-  const int na = nq + nx + (RR ? 1 : 0);
+  const int rows = nq + nx, na = rows + (RR ? 4 : 0);
   for (int j = threadIdx.x; j < 4 * na; j += 256) accs[j] = 0.0;
   __syncthreads();
   for (int64_t sl = blockIdx.x; sl < nslices; sl += gridDim.x) {
@@ -383,22 +396,42 @@ __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, i
       for (int k = 0; k < LZ_RPT; ++k) s = fmaf(rv[k], rv[k], s);
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) accs[wave * na + nq + nx] += (double)s;
+      if (lane == 0) accs[wave * na + rows] += (double)s;
     }
-    // the fp32 rows, in r's register layout
-    auto dot_x = [&](const float* __restrict__ x, int j) {
-      float xv[LZ_RPT];
-      load_r_slice<BT>(x, base, n, xv);
-      float s = 0.f;
-#pragma unroll
-      for (int k = 0; k < LZ_RPT; ++k) s = fmaf(xv[k], rv[k], s);
+    auto add = [&](float s, int at) {
 #pragma unroll
       for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) accs[wave * na + j] += (double)s;
+      if (lane == 0) accs[wave * na + at] += (double)s;
     };
+    // The rows' own products in fp64: q_0 of a run is often plus or minus one number throughout, whose square rounds the same way n times.
+    auto add_d = [&](double s, int at) {
+      s = wave_sum_d(s);
+      if (lane == 0) accs[wave * na + at] += s;
+    };
+    // the fp32 rows, in r's register layout
     if constexpr (XR) {
-      if (x0) dot_x(x0, nq);
-      if (x1) dot_x(x1, nq + 1);
+      float xv[LZ_RPT], yv[LZ_RPT];
+      load_r_slice<BT>(x0, base, n, xv);
+      if (x1) load_r_slice<BT>(x1, base, n, yv);
+      auto dot_x = [&](const float (&a)[LZ_RPT], int at) {
+        float s = 0.f;
+#pragma unroll
+        for (int k = 0; k < LZ_RPT; ++k) s = fmaf(a[k], rv[k], s);
+        add(s, at);
+      };
+      auto dot_xx = [&](const float (&a)[LZ_RPT], const float (&b)[LZ_RPT], int at) {
+        double s = 0.0;
+#pragma unroll
+        for (int k = 0; k < LZ_RPT; ++k) s += (double)a[k] * (double)b[k];
+        add_d(s, at);
+      };
+      dot_x(xv, nq);
+      dot_xx(xv, xv, x1 ? rows + 2 : rows + 1);
+      if (x1) {
+        dot_x(yv, nq + 1);
+        dot_xx(yv, yv, rows + 1);
+        dot_xx(xv, yv, rows + 3);
+      }
       if (nq == 0) continue;
     }
     auto dot_j = [&](const typename V::raw (&qv)[V::U], int j) {
@@ -410,9 +443,7 @@ __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, i
 #pragma unroll
         for (int k = 0; k < V::E; ++k) s = fmaf(qf[k], rv[u * V::E + k], s);
       }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-      if (lane == 0) accs[wave * na + j] += (double)s;
+      add(s, j);
     };
     typename V::raw qa[V::U], qb[V::U];
     load_q_slice<BT>(Q, base, n, full, qa);
@@ -423,24 +454,56 @@ __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, i
       if (j + 2 < nq) load_q_slice<BT>(Q + (int64_t)(j + 2) * ldq, base, n, full, qa);
       if (j + 1 < nq) dot_j(qb, j + 1);
     }
+    if constexpr (RR && !XR) {  // the last two rows are still there
+      double ga = 0.0, gb = 0.0, gab = 0.0;
+#pragma unroll
+      for (int u = 0; u < V::U; ++u) {
+        float a[V::E], b[V::E];
+        V::unpack(qa[u], a);
+        V::unpack(qb[u], b);
+#pragma unroll
+        for (int k = 0; k < V::E; ++k) {
+          ga += (double)a[k] * (double)a[k];
+          gb += (double)b[k] * (double)b[k];
+          gab += (double)a[k] * (double)b[k];
+        }
+      }
+      add_d(nq & 1 ? ga : gb, rows + 1);
+      if (nq > 1) {
+        add_d(nq & 1 ? gb : ga, rows + 2);
+        add_d(gab, rows + 3);
+      }
+    }
   }
   __syncthreads();
   for (int j = threadIdx.x; j < na; j += 256)
     partials[(int64_t)j * gridDim.x + blockIdx.x] = accs[j] + accs[na + j] + accs[2 * na + j] + accs[3 * na + j];
 }
 
-// After c = Q^T w and c_nq = <w, w> (w = H q_k, Q = q_0 .. q_k in fp32): alpha_k = c_k, and the
+// After c = Q^T w, c_nq = <w, w> and the last two rows' products with themselves and each other (w = H q_k, Q = q_0 .. q_k): alpha_k = c_k, and the
 // norm that the three-term recurrence would have left before the orthogonalisation pass,
 // ||w - alpha_k q_k - c_{k-1} q_{k-1}||, follows from the three numbers.  Where that difference
 // has lost its digits (beta_k tiny against alpha_k) the norm is set to infinity, which makes the
 // pass that follows ask for a second one.
-__global__ void lz_direct_scal_kernel(const double* __restrict__ c, int nq, double* __restrict__ scal) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// beta_k itself, ||w - Q c||, follows as well: ||w||^2 - sum c_j^2 (2 - <q_j, q_j>) + 2 c_k c_{k-1} <q_k, q_{k-1}>, up to products of small
+// coefficients (1e-12) and the coefficients' rounding (1e-9 of ||w||).  Where it is no small difference, and neither a second pass nor an end of the iteration is in sight,
+// the pass that follows divides by it and writes q_{k+1} at once, which saves a vector's way to memory and back (lz_finish_kernel
+// then looks at the norm of what was written).
+__global__ void lz_direct_scal_kernel(const double* __restrict__ c, int nq, LzNext next, double* __restrict__ scal) {
+  double others = 0.0;
+  for (int j = threadIdx.x; j < nq - 2; j += 64) others += c[j] * c[j];
+  others = wave_sum_d(others);
+  if (threadIdx.x != 0) return;
   const double a = c[nq - 1], p = nq >= 2 ? c[nq - 2] : 0.0, ww = c[nq];
   const double rest = ww - a * a - p * p;
+  const double b2 = ww - a * a * (2.0 - c[nq + 1]) - others + (nq >= 2 ? 2.0 * a * p * c[nq + 3] - p * p * (2.0 - c[nq + 2]) : 0.0);
+  const double before = rest > 1e-5 * ww ? sqrt(rest) : INFINITY;
   scal[S_ALPHA] = a;
-  scal[S_NRM_BEFORE] = rest > 1e-5 * ww ? sqrt(rest) : INFINITY;
+  scal[S_NRM_BEFORE] = before;
   scal[S_REDO] = 0.0;
+  bool ok = b2 > 1e-3 * ww && sqrt(b2) >= 0.7072 * before && sqrt(b2) >= 1.001 * next.tol;
+  if (next.flags) ok = ok && next.flags[0] == 0 && next.flags[1] != 0;
+  scal[S_EST] = ok ? sqrt(b2) : 0.0;
 }
 
 __global__ __launch_bounds__(256) void lz_qtr_finish_kernel(const double* partials, int nblk, const double* scal,
@@ -454,17 +517,21 @@ __global__ __launch_bounds__(256) void lz_qtr_finish_kernel(const double* partia
   if (threadIdx.x == 0) c[j] = s;
 }
 
-// r -= sum_j c_j Q_j, partial ||r||^2.
-// x0, x1 (optional, fp32 vectors): two more rows with coefficients c[nq], c[nq + 1].
+// r -= sum_j c_j Q_j, partial ||r||^2; or, with an estimate of beta_k (pass 0), q_{k+1} = (r - sum_j c_j Q_j) / beta_k to `next` and the
+// partial ||q_{k+1}||^2, r as it is.
+// x0, x1 (optional, fp32 vectors): two more rows with coefficients c[nq], c[nq + 1].  next.q may be x0 (q_{k+1} over q_{k-1}): a thread
+// writes what it has read.
 template <typename BT, bool XR = false>
 __global__ __launch_bounds__(256) void lz_sub_qc_kernel(const BT* __restrict__ Q, int64_t ldq, float* __restrict__ r,
                                                         int64_t n, int nq, int64_t nslices, const double* __restrict__ c,
-                                                        const double* scal, int pass, double* __restrict__ partials,
-                                                        const float* __restrict__ x0 = nullptr, const float* __restrict__ x1 = nullptr) {
+                                                        const double* scal, int pass, double* __restrict__ partials, LzNext next,
+                                                        const float* x0 = nullptr, const float* x1 = nullptr) {
   typedef QVec<BT> V;
   extern __shared__ float cs[];
   __shared__ double red[4];
   if (pass == 1 && scal[S_REDO] == 0.0) return;
+  const double est = pass == 0 ? scal[S_EST] : 0.0;
+  const float inv = est > 0.0 ? (float)(1.0 / est) : 0.f, inv_lo = est > 0.0 ? (float)(1.0 / est - (double)inv) : 0.f;
   const int nx = XR ? (x0 ? 1 : 0) + (x1 ? 1 : 0) : 0;
   for (int j = threadIdx.x; j < nq + nx; j += 256) cs[j] = (float)c[j];
   __syncthreads();
@@ -484,7 +551,7 @@ __global__ __launch_bounds__(256) void lz_sub_qc_kernel(const BT* __restrict__ Q
         for (int k = 0; k < V::E; ++k) rv[u * V::E + k] = fmaf(-cj, qf[k], rv[u * V::E + k]);
       }
     };
-    auto sub_x = [&](const float* __restrict__ x, int j) {
+    auto sub_x = [&](const float* x, int j) {
       float xv[LZ_RPT];
       load_r_slice<BT>(x, base, n, xv);
       const float cj = cs[j];
@@ -521,6 +588,37 @@ __global__ __launch_bounds__(256) void lz_sub_qc_kernel(const BT* __restrict__ Q
       }
     }
     float s = 0.f;
+    if (est > 0.0) {
+#pragma unroll
+      for (int u = 0; u < V::U; ++u) {
+        const int64_t e0 = base + (int64_t)(threadIdx.x + 256 * u) * V::E;
+#pragma unroll
+        for (int h = 0; h < V::E / 4; ++h) {
+          float* x = rv + u * V::E + h * 4;
+#pragma unroll
+          for (int q = 0; q < 4; ++q) x[q] = fmaf(x[q], inv, x[q] * inv_lo);
+          const int64_t e = e0 + h * 4;
+          if (e + 4 <= n) {
+            const float4 v = make_float4(x[0], x[1], x[2], x[3]);
+            *(float4*)(next.q + e) = v;
+            if (next.qb) {
+              const bf16 o[4] = {(bf16)x[0], (bf16)x[1], (bf16)x[2], (bf16)x[3]};
+              *(uint2*)(next.qb + e) = *(const uint2*)o;
+            }
+            s += x[0] * x[0] + x[1] * x[1] + x[2] * x[2] + x[3] * x[3];
+          } else {
+            for (int q = 0; q < 4; ++q)
+              if (e + q < n) {
+                next.q[e + q] = x[q];
+                if (next.qb) next.qb[e + q] = (bf16)x[q];
+                s += x[q] * x[q];
+              }
+          }
+        }
+      }
+      acc += (double)s;
+      continue;
+    }
 #pragma unroll
     for (int u = 0; u < V::U; ++u) {
       const int64_t e0 = base + (int64_t)(threadIdx.x + 256 * u) * V::E;
@@ -608,13 +706,13 @@ hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, b
 // rounding of a copy changes r far below its own last bit) and rows nq-2, nq-1, which carry
 // beta_{k-1} and alpha_k, from the basis.
 static void launch_sub_f32(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int64_t nslices,
-                           int nb, const double* c, const double* scal, int pass, double* partials, hipStream_t st) {
+                           int nb, const double* c, const double* scal, int pass, double* partials, const LzNext& next, hipStream_t st) {
   const size_t sh = (size_t)nq * sizeof(float);
   if (copies && nq >= 3)
     hipLaunchKernelGGL((lz_sub_qc_kernel<bf16, true>), dim3(nb), dim3(256), sh, st, copies, ldq, r, n, nq - 2, nslices, c, scal,
-                       pass, partials, Q + (int64_t)(nq - 2) * ldq, Q + (int64_t)(nq - 1) * ldq);
+                       pass, partials, next, Q + (int64_t)(nq - 2) * ldq, Q + (int64_t)(nq - 1) * ldq);
   else
-    hipLaunchKernelGGL(lz_sub_qc_kernel<float>, dim3(nb), dim3(256), sh, st, Q, ldq, r, n, nq, nslices, c, scal, pass, partials);
+    hipLaunchKernelGGL(lz_sub_qc_kernel<float>, dim3(nb), dim3(256), sh, st, Q, ldq, r, n, nq, nslices, c, scal, pass, partials, next);
 }
 
 hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int pass,
@@ -626,11 +724,11 @@ hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int
   if (basis_bf16) {
     hipLaunchKernelGGL(lz_qtr_kernel<bf16>, dim3(nb), dim3(256), sh1, st, (const bf16*)Q, ldq, r, n, nq, nslices, scal, pass, partials);
     hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, pass, c);
-    hipLaunchKernelGGL(lz_sub_qc_kernel<bf16>, dim3(nb), dim3(256), sh2, st, (const bf16*)Q, ldq, r, n, nq, nslices, c, scal, pass, partials);
+    hipLaunchKernelGGL(lz_sub_qc_kernel<bf16>, dim3(nb), dim3(256), sh2, st, (const bf16*)Q, ldq, r, n, nq, nslices, c, scal, pass, partials, LzNext{});
   } else {
     hipLaunchKernelGGL(lz_qtr_kernel<float>, dim3(nb), dim3(256), sh1, st, (const float*)Q, ldq, r, n, nq, nslices, scal, pass, partials);
     hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, pass, c);
-    launch_sub_f32((const float*)Q, copies, ldq, r, n, nq, nslices, nb, c, scal, pass, partials, st);
+    launch_sub_f32((const float*)Q, copies, ldq, r, n, nq, nslices, nb, c, scal, pass, partials, LzNext{}, st);
   }
   hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(256), 0, st, partials, nb, 3, pass, scal);
   return hipGetLastError();
@@ -640,17 +738,17 @@ hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int
 // (nq = k + 1 rows): the coefficients of rows k and k - 1 are alpha_k and (up to rounding)
 // beta_{k-1}, so the pass subsumes the three-term subtraction, which saves its two passes over the
 // vectors.  Leaves alpha_k, ||r|| and the redo flag in scal as the three-term kernels followed by
-// lz_reorth_pass(pass 0) do.  c: nq + 1 doubles, partials: (nq + 1) * LZ_NBLK doubles.
-hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, double* scal,
+// lz_reorth_pass(pass 0) do.
+hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, const LzNext& next, double* scal,
                             double* c, double* partials, hipStream_t st) {
   if (nq <= 0) return hipErrorInvalidValue;
   const int64_t nslices = (n + LZ_SLICE - 1) / LZ_SLICE;
   const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nslices, LZ_NBLK));
-  const size_t sh1 = (size_t)4 * (nq + 1) * sizeof(double);
+  const size_t sh1 = (size_t)4 * (nq + 4) * sizeof(double);
   hipLaunchKernelGGL((lz_qtr_kernel<float, true>), dim3(nb), dim3(256), sh1, st, Q, ldq, r, n, nq, nslices, scal, 0, partials);
-  hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq + 1), dim3(256), 0, st, partials, nb, scal, 0, c);
-  hipLaunchKernelGGL(lz_direct_scal_kernel, dim3(1), dim3(64), 0, st, c, nq, scal);
-  launch_sub_f32(Q, copies, ldq, r, n, nq, nslices, nb, c, scal, 0, partials, st);
+  hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq + 4), dim3(256), 0, st, partials, nb, scal, 0, c);
+  hipLaunchKernelGGL(lz_direct_scal_kernel, dim3(1), dim3(64), 0, st, c, nq, next, scal);
+  launch_sub_f32(Q, copies, ldq, r, n, nq, nslices, nb, c, scal, 0, partials, next, st);
   hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(256), 0, st, partials, nb, 3, 0, scal);
   return hipGetLastError();
 }
@@ -659,18 +757,18 @@ hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, flo
 // q_{k-1} from the fp32 working vectors instead (alpha_k must come from the unrounded q_k) and the
 // rounded rows 0 .. k-2 from the basis.  qkm1 is ignored for k = 0.
 hipError_t lz_gs_first_pass_bf16(const bf16* Q, int64_t ldq, const float* qkm1, const float* qk, float* r, int64_t n, int k,
-                                 double* scal, double* c, double* partials, hipStream_t st) {
+                                 const LzNext& next, double* scal, double* c, double* partials, hipStream_t st) {
   if (k < 0 || !qk || (k > 0 && !qkm1)) return hipErrorInvalidValue;
   const int64_t nslices = (n + LZ_SLICE - 1) / LZ_SLICE;
   const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nslices, LZ_NBLK));
   const int nqb = std::max(0, k - 1);  // rows taken from the basis
   const float* x0 = k > 0 ? qkm1 : qk;
   const float* x1 = k > 0 ? qk : nullptr;
-  const size_t sh1 = (size_t)4 * (k + 2) * sizeof(double), sh2 = (size_t)(k + 1) * sizeof(float);
+  const size_t sh1 = (size_t)4 * (k + 5) * sizeof(double), sh2 = (size_t)(k + 1) * sizeof(float);
   hipLaunchKernelGGL((lz_qtr_kernel<bf16, true, true>), dim3(nb), dim3(256), sh1, st, Q, ldq, r, n, nqb, nslices, scal, 0, partials, x0, x1);
-  hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(k + 2), dim3(256), 0, st, partials, nb, scal, 0, c);
-  hipLaunchKernelGGL(lz_direct_scal_kernel, dim3(1), dim3(64), 0, st, c, k + 1, scal);
-  hipLaunchKernelGGL((lz_sub_qc_kernel<bf16, true>), dim3(nb), dim3(256), sh2, st, Q, ldq, r, n, nqb, nslices, c, scal, 0, partials, x0, x1);
+  hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(k + 5), dim3(256), 0, st, partials, nb, scal, 0, c);
+  hipLaunchKernelGGL(lz_direct_scal_kernel, dim3(1), dim3(64), 0, st, c, k + 1, next, scal);
+  hipLaunchKernelGGL((lz_sub_qc_kernel<bf16, true>), dim3(nb), dim3(256), sh2, st, Q, ldq, r, n, nqb, nslices, c, scal, 0, partials, next, x0, x1);
   hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(256), 0, st, partials, nb, 3, 0, scal);
   return hipGetLastError();
 }
@@ -679,6 +777,15 @@ bool lz_small(int64_t n, int64_t rows) { return n <= LZ_SMALL_N && n * (rows + 2
 
 hipError_t lz_small_update(const LzSmall& u, const float* hq, const int* flags, hipStream_t st) {
   hipLaunchKernelGGL(lz_small_kernel, dim3(1), dim3(1024), (size_t)u.lds(), st, u, hq, flags);
+  return hipGetLastError();
+}
+
+__global__ void lz_times_kernel(const float* src, float f, float* dst, int64_t n) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) dst[i] = f * src[i];
+}
+hipError_t lz_times(const float* src, double f, float* dst, int64_t n, hipStream_t st) {
+  const int nb = (int)std::max<int64_t>(1, std::min<int64_t>((n + 255) / 256, 8192));
+  hipLaunchKernelGGL(lz_times_kernel, dim3(nb), dim3(256), 0, st, src, (float)f, dst, n);
   return hipGetLastError();
 }
 
