@@ -89,7 +89,10 @@ __device__ __forceinline__ void lz_small_full_block(const LzSmall& u, float* w, 
     if (pass == 0) {  // as lz_direct_scal_kernel
       alpha = sm_c[nq - 1];
       const double p = nq >= 2 ? sm_c[nq - 2] : 0.0, ww = sm_c[nq], rest = ww - alpha * alpha - p * p;
-      before = rest > 1e-5 * ww ? sqrt(rest) : INFINITY;
+      bool grows = false;
+      if (alpha * alpha > 4.0 * rest)
+        for (int j = 0; j < nq - 2; ++j) grows = grows || sm_c[j] * sm_c[j] > 1e-10 * ww;
+      before = rest > 1e-5 * ww && !grows ? sqrt(rest) : INFINITY;
     }
     double s = 0.0;
     for (int i = t; i < n; i += 1024) {

@@ -16,7 +16,7 @@ MODELS = {  # lengths: a part of a slice of 4096, odd; some slices and a part; m
     "middle": si._gpt(1, 72, 3, 200, 97, 5),
     "long": si._gpt(2, 512, 8, 2048, 5003, 16),
 }
-SPECTRA = {"around_zero": (-0.5, 1.5)}
+SPECTRA = {"around_zero": (-0.5, 1.5), "away_from_zero": (0.9, 1.0)}
 
 
 def _vectors(n, lo, hi):
