@@ -111,6 +111,8 @@ struct hf_ctx {
   int gemm_cnt_clear = 0;    // the first product has cleared them
   float* aux_vec = nullptr;  // n floats, allocated on first use (batch-loop partial result, unit vector)
   int dw_layers() const;  // layers whose weight-gradient products may wait for a common launch
+  int clear_padding(int T, hipError_t* er, hipStream_t st);
+  int pad_T = -1;  // number of tokens behind which those rows are zero
   int ensure_aux();
 
   // Lanczos state

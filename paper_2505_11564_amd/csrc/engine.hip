@@ -172,25 +172,26 @@ int hf_ctx::plan_and_alloc(bool may_wait) {
       flash = can && desc.attention != HF_ATTN_STORED && (desc.attention == HF_ATTN_STREAMED || attn_flash_preferred((int)(D / H), B * H, S));
     }
     pairs = bf && (desc.primal == HF_PRIMAL_PAIRS || (desc.primal == HF_PRIMAL_AUTO && llama));
+    const int64_t Tp = bf ? round_up(T, 64) : T;  // rows of what weight-gradient products read (clear_padding)
     const int64_t SSa = flash ? 0 : SS;  // the S x S buffers exist only for the unstreamed paths
     lb.resize(desc.n_layer);
     for (auto& b : lb) {
       b = LayerBuf{};
       pl.add(b.x1, T * D * 4); pl.add(b.x1_t, T * D * 4); pl.add(b.x2, T * D * 4); pl.add(b.x2_t, T * D * 4);
       pl.add(b.st1, T * 16); pl.add(b.st2, T * 16);
-      pl.add(b.a, T * D * e); pl.add(b.a_t, T * D * e);
+      pl.add(b.a, Tp * D * e); pl.add(b.a_t, Tp * D * e);
       pl.add(b.qkv, T * W3 * e); pl.add(b.qkv_t, T * W3 * e);
       pl.add(b.P, SSa * e); pl.add(b.P_t, SSa * e);
       if (flash) pl.add(b.att_stat, SS / S * 2 * 4);
       if (flash && pairs) { pl.add(b.qkv_lo, T * W3 * e); pl.add(b.o_lo, T * D * e); }
-      pl.add(b.o, T * D * e); pl.add(b.o_t, T * D * e);
-      pl.add(b.m, T * D * e); pl.add(b.m_t, T * D * e);
+      pl.add(b.o, Tp * D * e); pl.add(b.o_t, Tp * D * e);
+      pl.add(b.m, Tp * D * e); pl.add(b.m_t, Tp * D * e);
       pl.add(b.f, T * F * e); pl.add(b.f_t, T * F * e);
-      pl.add(b.g, T * F * e); pl.add(b.g_t, T * F * e);
+      pl.add(b.g, Tp * F * e); pl.add(b.g_t, Tp * F * e);
       if (llama) { pl.add(b.up, T * F * e); pl.add(b.up_t, T * F * e); }
     }
     pl.add(xL, T * D * 4); pl.add(xL_t, T * D * 4); pl.add(stf, T * 16);
-    pl.add(xf, T * D * e); pl.add(xf_t, T * D * e);
+    pl.add(xf, Tp * D * e); pl.add(xf_t, Tp * D * e);
     if (pairs) {
       pl.add(xf_lo, T * D * e); pl.add(a_lo, T * D * e); pl.add(o_lo, T * D * e); pl.add(qkv_lo, T * W3 * e);
       pl.add(P_lo, SSa * e); pl.add(f_lo, T * F * e); pl.add(g_lo, T * F * e);
@@ -202,7 +203,7 @@ int hf_ctx::plan_and_alloc(bool may_wait) {
     }
     ldz = round_up(desc.vocab, 64);
     pl.add(z, T * ldz * 4); pl.add(z_t, T * ldz * 4);
-    pl.add(dz, T * ldz * e); pl.add(dz_t, T * ldz * e);
+    pl.add(dz, Tp * ldz * e); pl.add(dz_t, Tp * ldz * e);
     pl.add(loss_rows, T * 4);
     pl.add(sc, SSa * 4); pl.add(sc_t, SSa * 4);
     att_SS = SSa;
@@ -216,11 +217,11 @@ int hf_ctx::plan_and_alloc(bool may_wait) {
     pl.add(dob, T * D * e); pl.add(dob_t, T * D * e);
     adj.assign(may_wait ? dw_layers() : 1, AdjBuf{});
     for (AdjBuf& a : adj) {
-      if (bf) { pl.add(a.x, T * D * e); pl.add(a.x_t, T * D * e); pl.add(a.m, T * D * e); pl.add(a.m_t, T * D * e); }
-      pl.add(a.qkv, T * W3 * e); pl.add(a.qkv_t, T * W3 * e);
-      pl.add(a.g, T * F * e); pl.add(a.g_t, T * F * e);
-      if (llama) { pl.add(a.up, T * F * e); pl.add(a.up_t, T * F * e); }
-      if (llama && Dkv != D && bf && !flash) { pl.add(a.v, T * Dkv * e); pl.add(a.v_t, T * Dkv * e); }
+      if (bf) { pl.add(a.x, Tp * D * e); pl.add(a.x_t, Tp * D * e); pl.add(a.m, Tp * D * e); pl.add(a.m_t, Tp * D * e); }
+      pl.add(a.qkv, Tp * W3 * e); pl.add(a.qkv_t, Tp * W3 * e);
+      pl.add(a.g, Tp * F * e); pl.add(a.g_t, Tp * F * e);
+      if (llama) { pl.add(a.up, Tp * F * e); pl.add(a.up_t, Tp * F * e); }
+      if (llama && Dkv != D && bf && !flash) { pl.add(a.v, Tp * Dkv * e); pl.add(a.v_t, Tp * Dkv * e); }
     }
     if (llama) { pl.add(dy, T * F * e); pl.add(dy_t, T * F * e); }
   }
@@ -394,7 +395,7 @@ int hf_ctx::hvp_enqueue(const void* params, const void* inputs, const int32_t* l
         M[k] = gpt ? Mg[j] : Ml[j];
         N[k] = gpt ? Ng[j] : Nl[j];
       }
-    if (gemm_mfma_group_cuts_k(M, N, k, T, 2)) {
+    if (gemm_mfma_group_cuts_k(M, N, k, (T + 63) / 64 * 64, 2)) {
       CK(launch_fill_f32(out + layers_begin, layers_end - layers_begin, 0.f, st));
       dw_prezeroed = 1;
     }
@@ -439,6 +440,37 @@ int hf_ctx::dw_layers() const {
                                              : 2 * gemm_tiles256(D, D) + 2 * gemm_tiles256(D, Dkv) + 3 * gemm_tiles256(D, F);
   if (fills_rounds(t)) return 1;
   return (int)std::min<int64_t>(desc.n_layer, std::min<int64_t>(4, (255 + t) / t + 1));
+}
+
+// Weight-gradient products of bf16 operands contract over the tokens in slabs of 64; a last slab that is not whole goes through registers
+// and two more barriers, 5 us a round of tiles.  Their operands therefore have rows up to the next multiple of 64, which are zero: cleared
+// when the number of tokens changes, as nothing writes them (GPT-2-small, 999 tokens: 5.15 -> 5.11 ms a product; drawn models of 100 to 800
+// tokens up to 1.2 %).  Returns the number of rows to contract over.
+int hf_ctx::clear_padding(int T, hipError_t* er, hipStream_t st) {
+  const int D = desc.d_model, F = desc.d_ff, Dkv = D / desc.n_head * (desc.n_kv_head > 0 ? desc.n_kv_head : desc.n_head);
+  *er = hipSuccess;
+  if (!bf || D % 8 || F % 8 || Dkv % 8) return T;  // (other widths take other kernels)
+  const int Tp = (T + 63) / 64 * 64;
+  if (pad_T != T && Tp != T) {
+    std::vector<float*> p;
+    std::vector<int64_t> len;
+    auto add = [&](void* x, int64_t width) {
+      if (!x) return;
+      p.push_back((float*)((bf16*)x + T * width));
+      len.push_back((Tp - T) * width / 2);
+    };
+    for (const LayerBuf& b : lb) {
+      add(b.a, D); add(b.a_t, D); add(b.o, D); add(b.o_t, D); add(b.m, D); add(b.m_t, D); add(b.g, F); add(b.g_t, F);
+    }
+    for (const AdjBuf& a : adj) {
+      add(a.x, D); add(a.x_t, D); add(a.m, D); add(a.m_t, D); add(a.g, F); add(a.g_t, F); add(a.up, F); add(a.up_t, F);
+      add(a.qkv, D + 2 * Dkv); add(a.qkv_t, D + 2 * Dkv); add(a.v, Dkv); add(a.v_t, Dkv);
+    }
+    add(xf, D); add(xf_t, D); add(dz, ldz); add(dz_t, ldz);
+    *er = launch_zero_ranges(p.data(), len.data(), (int)p.size(), st);
+  }
+  pad_T = T;
+  return Tp;
 }
 
 int hf_ctx::ensure_aux() {
@@ -508,6 +540,10 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
   auto at = [&](void* p, int64_t elems) -> void* { return (char*)p + elems * e; };
   auto cat = [&](const void* p, int64_t elems) -> const void* { return (const char*)p + elems * e; };
   int rc;
+
+  hipError_t er_pad;
+  const int Tk = clear_padding(T, &er_pad, st);  // rows that weight-gradient products contract over
+  CK(er_pad);
 
   // Batched per-(batch, head) attention products.  Scores are [B,H,S,S].
   const int64_t SS = (int64_t)S * S;
@@ -679,7 +715,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
   if (tied) {
     // z = xf wte^T:  (Hv)_wte = dz_t^T xf + dz^T xf_t  [V, D];  dxf = dz wte
     Gemm g;
-    g.M = V; g.N = D; g.K = T; g.lda = ldz; g.ldb = D; g.ldc = D; g.transA = 1; g.in_bf16 = bf;
+    g.M = V; g.N = D; g.K = Tk; g.lda = ldz; g.ldb = D; g.ldc = D; g.transA = 1; g.in_bf16 = bf;
     g.A[0] = dz_t; g.B[0] = xf; g.A[1] = dz; g.B[1] = xf_t; g.C = out + off_wte;
     if (acc_mode) g.Cadd = out + off_wte;
     L.scratch(g);
@@ -687,7 +723,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     if ((rc = L.bwd_dx(dz, dz_t, T, D, V, ldz, off_wte, tmpd, tmpd_t, D, 0, nullptr, nullptr, 1, D))) return rc;
   } else {
     Gemm g;
-    if ((rc = L.bwd_dw(xf, xf_t, dz, dz_t, T, D, V, D, ldz, off_head, -1, nullptr, 0, &g))) return rc;
+    if ((rc = L.bwd_dw(xf, xf_t, dz, dz_t, Tk, D, V, D, ldz, off_head, -1, nullptr, 0, &g))) return rc;
     CK(head_dw(g));
     if ((rc = L.bwd_dx(dz, dz_t, T, D, V, ldz, off_head, tmpd, tmpd_t, D, 0))) return rc;
   }
@@ -706,21 +742,21 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     Gemm g_dw;
     // ---- MLP branch
     if (!llama) {
-      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, T, F, D, F, D, o.wproj, -1, nullptr, 0, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, Tk, F, D, F, D, o.wproj, -1, nullptr, 0, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(ad.x, ad.x_t, T, F, D, D, o.wproj, dg, dg_t, F, bf))) return rc;
       CK(launch_act_bwd_bias(bf, gelu_kind, b.f, b.f_t, dg, dg_t, dg, dg_t, T, F, out + o.bfc, st));  // and the bias block of H v
-      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wfc, -1, nullptr, 0, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, Tk, D, F, D, F, o.wfc, -1, nullptr, 0, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dg, dg_t, T, D, F, F, o.wfc, tmpd, tmpd_t, D, 0))) return rc;
     } else {
-      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, T, F, D, F, D, o.wdown, -1, nullptr, 0, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.g, b.g_t, ad.x, ad.x_t, Tk, F, D, F, D, o.wdown, -1, nullptr, 0, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(ad.x, ad.x_t, T, F, D, D, o.wdown, dy, dy_t, F, bf))) return rc;
       CK(launch_swiglu_bwd(bf, b.f, b.f_t, b.up, b.up_t, dy, dy_t, dg, dg_t, dup, dup_t, (int64_t)T * F, st));
-      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, T, D, F, D, F, o.wgate, -1, nullptr, 0, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.m, b.m_t, dg, dg_t, Tk, D, F, D, F, o.wgate, -1, nullptr, 0, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
-      if ((rc = L.bwd_dw(b.m, b.m_t, dup, dup_t, T, D, F, D, F, o.wup, -1, nullptr, 0, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.m, b.m_t, dup, dup_t, Tk, D, F, D, F, o.wup, -1, nullptr, 0, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dg, dg_t, T, D, F, F, o.wgate, tmpd, tmpd_t, D, 0))) return rc;
       if ((rc = L.bwd_dx(dup, dup_t, T, D, F, F, o.wup, tmpd, tmpd_t, D, 0, tmpd, tmpd_t))) return rc;
@@ -730,7 +766,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
                        out + o.n2g, rms ? nullptr : out + o.n2b, norm_part, st, bf ? ad.m : nullptr, bf ? ad.m_t : nullptr,
                        o.bo >= 0 ? out + o.bo : nullptr));
     // ---- attention branch
-    if ((rc = L.bwd_dw(b.o, b.o_t, ad.m, ad.m_t, T, D, D, D, D, o.wo, -1, nullptr, 0, &g_dw))) return rc;
+    if ((rc = L.bwd_dw(b.o, b.o_t, ad.m, ad.m_t, Tk, D, D, D, D, o.wo, -1, nullptr, 0, &g_dw))) return rc;
     CK(queue_dw(g_dw, l));
     if ((rc = L.bwd_dx(ad.m, ad.m_t, T, D, D, D, o.wo, dob, dob_t, D, bf))) return rc;
     // Products whose result belongs to a key/value head sum over the grp query heads that share
@@ -832,7 +868,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     }
     }
     if (!llama) {
-      if ((rc = L.bwd_dw(b.a, b.a_t, dqkv, dqkv_t, T, D, 3 * D, D, W3, o.wqkv, o.bqkv, dqkv_t, bf, &g_dw))) return rc;
+      if ((rc = L.bwd_dw(b.a, b.a_t, dqkv, dqkv_t, Tk, D, 3 * D, D, W3, o.wqkv, o.bqkv, dqkv_t, bf, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
       if ((rc = L.bwd_dx(dqkv, dqkv_t, T, D, 3 * D, W3, o.wqkv, tmpd, tmpd_t, D, 0))) return rc;
     } else {
@@ -849,7 +885,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
           dyi_t = bf ? (const void*)ad.v_t : (const void*)rv_t;
           ldy = Dkv;
         }
-        if ((rc = L.bwd_dw(b.a, b.a_t, dyi, dyi_t, T, D, Ni, D, ldy, w3[i], -1, nullptr, 0, &g_dw))) return rc;
+        if ((rc = L.bwd_dw(b.a, b.a_t, dyi, dyi_t, Tk, D, Ni, D, ldy, w3[i], -1, nullptr, 0, &g_dw))) return rc;
         CK(queue_dw(g_dw, l));
         if ((rc = L.bwd_dx(dyi, dyi_t, T, D, Ni, ldy, w3[i], tmpd, tmpd_t, D, 0, i ? tmpd : nullptr, i ? tmpd_t : nullptr))) return rc;
       }
