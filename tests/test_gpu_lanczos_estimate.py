@@ -64,10 +64,11 @@ def test_update_of_long_vectors(name, dtype, basis, spectrum):
         assert abs(a - al[k]) <= 1e-5 and abs(b - be[k]) <= 1e-5
     ctx.hf_lanczos_get_vector(0, q)  # q_m
     assert abs(q.double().norm().item() - 1.0) <= 1e-7
-    # an iteration leaves rounding errors times alpha / beta (1 and 38); bf16 rows have some of 2^-9 in random directions, 2^-9 / sqrt(n) of which lie along
-    # any one vector, and m iterations of them come together (measured: 7.8e-3 at n = 10608)
+    # An iteration leaves rounding errors times alpha / beta (1 and 38).  bf16 rows have some of 2^-9: the part in random directions lies along any one
+    # vector with 2^-9 / sqrt(n), and m iterations of it come together (measured 7.8e-3 at n = 10608); q_0, whose elements are all rounded alike,
+    # leaves 5e-5 to 7e-5 whatever n (a quarter of what is allowed).
     grown = 38.0 if spectrum == "away_from_zero" else 1.0
-    assert (q.double() - qs[m]).norm().item() <= (2 * m * 2.0**-9 * grown / n**0.5 if basis == "bf16" else 5e-5 * grown)
+    assert (q.double() - qs[m]).norm().item() <= (max(3e-4, 2 * m * 2.0**-9 * grown / n**0.5) if basis == "bf16" else 5e-5 * grown)
     ctx.close()
 
 
