@@ -249,7 +249,7 @@ __global__ __launch_bounds__(256) void lz3_normalise_kernel(const float* __restr
 
 // q_{k+1} = src / scal[idx] into any of: dst (fp32 working vector), basis (its row of the stored
 // basis, fp32 or bf16 rounded to nearest even), vb (bf16 copy for the next Hessian-vector product).
-// One thread per two 16-byte groups.
+// A thread has two 16-byte groups at a time.
 template <typename BT>
 __global__ __launch_bounds__(256) void lz_scale_kernel(const float* src, float* dst, BT* basis, bf16* __restrict__ vb, int64_t n,
                                                        double* scal, int idx, double tol, const int* flags) {
@@ -261,11 +261,6 @@ __global__ __launch_bounds__(256) void lz_scale_kernel(const float* src, float* 
     src = dst ? dst : (const float*)basis;
   }
   const int64_t n4 = n >> 2, half = (int64_t)gridDim.x * 256;
-  const int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x, i1 = i0 + half;
-  const bool ok0 = i0 < n4, ok1 = i1 < n4;
-  float4 v0 = make_float4(0.f, 0.f, 0.f, 0.f), v1 = v0;
-  if (ok0) v0 = ldnt4(src, i0);
-  if (ok1) v1 = ldnt4(src, i1);
   auto put = [&](int64_t i, float4 v) {
     v = scale4(v, inv);
     if (dst) stnt4(dst, i, v);
@@ -275,8 +270,13 @@ __global__ __launch_bounds__(256) void lz_scale_kernel(const float* src, float* 
     }
     if (vb) stnt_bf16x4(vb, i, v);
   };
-  if (ok0) put(i0, v0);
-  if (ok1) put(i1, v1);
+  for (int64_t i0 = (int64_t)blockIdx.x * 256 + threadIdx.x; i0 < n4; i0 += 2 * half) {
+    const int64_t i1 = i0 + half;
+    float4 v0 = ldnt4(src, i0), v1 = v0;
+    if (i1 < n4) v1 = ldnt4(src, i1);
+    put(i0, v0);
+    if (i1 < n4) put(i1, v1);
+  }
   const int64_t e = (n4 << 2) + threadIdx.x;
   if (blockIdx.x == 0 && e < n) {
     const float v = src[e] * inv;
@@ -703,7 +703,9 @@ hipError_t lz3_update(const float* w, const float* q, float* qp, bf16* vb, int64
 
 hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, bf16* vb, int64_t n, double* scal, int idx,
                     double tol, const int* flags, hipStream_t st) {
-  const unsigned nb = wide_blocks(n);
+  // after a pass over the basis there is seldom anything left to do, and blocks that return at once take their time too: 25 us of them at
+  // n = 1.2e8, 200 at 1.3e9, against 4 for this many
+  const unsigned nb = idx == S_BETA ? std::min(wide_blocks(n), 4096u) : wide_blocks(n);
   if (basis_bf16) hipLaunchKernelGGL(lz_scale_kernel<bf16>, dim3(nb), dim3(256), 0, st, src, dst, (bf16*)basis, vb, n, scal, idx, tol, flags);
   else hipLaunchKernelGGL(lz_scale_kernel<float>, dim3(nb), dim3(256), 0, st, src, dst, (float*)basis, vb, n, scal, idx, tol, flags);
   return hipGetLastError();
