@@ -870,6 +870,7 @@ int hf_ctx::hvp_transformer(const void* params, const int32_t* tok, const int32_
     if (!llama) {
       if ((rc = L.bwd_dw(b.a, b.a_t, dqkv, dqkv_t, Tk, D, 3 * D, D, W3, o.wqkv, o.bqkv, dqkv_t, bf, &g_dw))) return rc;
       CK(queue_dw(g_dw, l));
+      if (!bf) CK(launch_dw());
       if ((rc = L.bwd_dx(dqkv, dqkv_t, T, D, 3 * D, W3, o.wqkv, tmpd, tmpd_t, D, 0))) return rc;
     } else {
       CK(launch_rope(bf, rq, rq_t, RQ, dqkv, dqkv_t, nullptr, W3, T, S, H + Hkv, dh, desc.rope_theta, 1, st));
