@@ -467,7 +467,8 @@ int hf_ctx::clear_padding(int T, hipError_t* er, hipStream_t st) {
       add(a.qkv, D + 2 * Dkv); add(a.qkv_t, D + 2 * Dkv); add(a.v, Dkv); add(a.v_t, Dkv);
     }
     add(xf, D); add(xf_t, D); add(dz, ldz); add(dz_t, ldz);
-    *er = launch_zero_ranges(p.data(), len.data(), (int)p.size(), st);
+    pad_T = -1;  // not before all of them are on their way
+    if ((*er = launch_zero_ranges(p.data(), len.data(), (int)p.size(), st)) != hipSuccess) return T;
   }
   pad_T = T;
   return Tp;
