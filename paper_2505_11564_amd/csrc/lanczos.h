@@ -1,6 +1,7 @@
 // Internal interface of the Lanczos vector kernels (lanczos.hip).
 #pragma once
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "hf_internal.h"
@@ -45,6 +46,38 @@ hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, b
 // reads rows 0 .. nq-3 from them.
 hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int pass,
                           double* scal, double* c, double* partials, hipStream_t st);
+// What the first orthogonalisation pass decides from c = Q^T w and a few products more (w = H q_k, Q = q_0 .. q_k).
+struct LzFirst {
+  double a, p;              // c_k = alpha_k, c_{k-1} (0 for k = 0)
+  double ww;                // <w, w>
+  double others, sum, most; // of the older rows: sum of c_j^2, sum of |c_j|, largest c_j^2
+  double gkk, gpp, gkp;     // <q_k, q_k>; <q_{k-1}, q_{k-1}>, <q_k, q_{k-1}> (0 for k = 0)
+};
+// before: the norm that the three-term recurrence would have left, ||w - alpha_k q_k - c_{k-1} q_{k-1}||; the pass asks for a second one where it
+// leaves less than 1 / sqrt(2) of that.  Where the difference has lost its digits (beta_k tiny against alpha_k) it is infinite, which makes
+// the pass ask.  So it is where an older row has a coefficient above 1e-5 ||w|| and alpha_k > 2 beta_k: that may say that q_k has lost as much
+// orthogonality, and what one pass leaves of it, alpha_k <q_k, q_j> / beta_k, then grows from iteration to iteration (a spectrum that
+// keeps away from zero: 0.9 .. 1.0 lost the basis in five iterations).
+// est: beta_k itself, ||w - Q c||, or 0.  ||w||^2 - sum c_j^2 (2 - <q_j, q_j>) + 2 c_k c_{k-1} <q_k, q_{k-1}> leaves out what the older rows' products with
+// each other, with themselves beyond 1, and with q_k and q_{k-1} add: at most LZ_OFF times (sum |c_j|)^2 + 2 sum |c_j| (|c_k| + |c_{k-1}|), as no
+// such product is off by more than LZ_OFF (rounding a row to bf16 moves it by 2^-9 of its length; rows of fp32 are a thousand times closer).
+// In a run the c_j are rounding errors and the bound is far below the 1e-3 asked for.  Where beta_k less that bound is no small difference, and
+// neither a second pass nor, with 1e-3 to spare for the fp32 sums in <w, w>, an end of the iteration is in sight, the pass divides by
+// beta_k and writes q_{k+1} at once, over q_{k-1} if need be, which saves a vector's way to memory and back.
+constexpr double LZ_OFF = 1.0 / 128.0;
+struct LzFirstPlan { double before, est; };
+__host__ __device__ inline LzFirstPlan lz_first_plan(const LzFirst& s, double tol) {
+  const double rest = s.ww - s.a * s.a - s.p * s.p;
+  const double b2 = s.ww - s.a * s.a * (2.0 - s.gkk) - s.others + 2.0 * s.a * s.p * s.gkp - s.p * s.p * (2.0 - s.gpp);
+  const double low = b2 - LZ_OFF * s.sum * (s.sum + 2.0 * (fabs(s.a) + fabs(s.p)));
+  const bool grows = s.most > 1e-10 * s.ww && s.a * s.a > 4.0 * b2;
+  LzFirstPlan plan;
+  plan.before = rest > 1e-5 * s.ww && !grows ? sqrt(rest) : INFINITY;
+  const bool ok = low > 1e-3 * s.ww && sqrt(low) >= 0.7072 * plan.before && sqrt(low) >= 1.001 * tol;  // (false for NaN)
+  plan.est = ok ? sqrt(b2) : 0.0;
+  return plan;
+}
+
 // Where q_{k+1} goes (fp32; bf16, may be NULL), and the test that decides whether it may be written.
 struct LzNext {
   float* q;
@@ -53,7 +86,7 @@ struct LzNext {
   double tol;
 };
 // The first pass applied to w = H q_k itself against an fp32 basis holding q_0 .. q_k (nq = k + 1): also yields alpha_k.  Writes
-// q_{k+1} instead of r where beta_k is known well enough beforehand (scal[S_EST] > 0; see lz_direct_scal_kernel).
+// q_{k+1} instead of r where beta_k is known well enough beforehand (scal[S_EST] > 0).
 // c: nq + 4 doubles, partials: (nq + 4) * LZ_NBLK.
 hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, const LzNext& next, double* scal,
                             double* c, double* partials, hipStream_t st);

@@ -480,38 +480,28 @@ __global__ __launch_bounds__(256) void lz_qtr_kernel(const BT* __restrict__ Q, i
     partials[(int64_t)j * gridDim.x + blockIdx.x] = accs[j] + accs[na + j] + accs[2 * na + j] + accs[3 * na + j];
 }
 
-// After c = Q^T w, c_nq = <w, w> and the last two rows' products with themselves and each other (w = H q_k, Q = q_0 .. q_k): alpha_k = c_k, and the
-// norm that the three-term recurrence would have left before the orthogonalisation pass,
-// ||w - alpha_k q_k - c_{k-1} q_{k-1}||, follows from the three numbers.  Where that difference
-// has lost its digits (beta_k tiny against alpha_k) the norm is set to infinity, which makes the
-// pass that follows ask for a second one.  So does a coefficient of an older row above 1e-5 ||w|| where alpha_k > 2 beta_k: it may say that q_k
-// has lost that much orthogonality, and what one pass leaves of it, alpha_k <q_k, q_j> / beta_k, then grows from iteration to iteration (a
-// spectrum that keeps away from zero: 0.9 .. 1.0 lost the basis in five iterations).
-// beta_k itself, ||w - Q c||, follows as well: ||w||^2 - sum c_j^2 (2 - <q_j, q_j>) + 2 c_k c_{k-1} <q_k, q_{k-1}>, up to products of small
-// coefficients (1e-12) and the coefficients' rounding (1e-9 of ||w||).  Where it is no small difference, and neither a second pass nor an end of the iteration is in sight,
-// the pass that follows divides by it and writes q_{k+1} at once, which saves a vector's way to memory and back (lz_finish_kernel
-// then looks at the norm of what was written).
+// After c = Q^T w, c_nq = <w, w> and the last two rows' products with themselves and each other (w = H q_k, Q = q_0 .. q_k): alpha_k = c_k, and
+// what lz_first_plan makes of them; with an estimate lz_finish_kernel then looks at the norm of what was written.
 __global__ void lz_direct_scal_kernel(const double* __restrict__ c, int nq, LzNext next, double* __restrict__ scal) {
-  double others = 0.0, most = 0.0;
+  LzFirst s = {};
   for (int j = threadIdx.x; j < nq - 2; j += 64) {
-    others += c[j] * c[j];
-    most = fmax(most, c[j] * c[j]);
+    s.others += c[j] * c[j];
+    s.sum += fabs(c[j]);
+    s.most = fmax(s.most, c[j] * c[j]);
   }
-  others = wave_sum_d(others);
+  s.others = wave_sum_d(s.others);
+  s.sum = wave_sum_d(s.sum);
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) most = fmax(most, __shfl_xor(most, o, 64));
+  for (int o = 32; o > 0; o >>= 1) s.most = fmax(s.most, __shfl_xor(s.most, o, 64));
   if (threadIdx.x != 0) return;
-  const double a = c[nq - 1], p = nq >= 2 ? c[nq - 2] : 0.0, ww = c[nq];
-  const double rest = ww - a * a - p * p;
-  const double b2 = ww - a * a * (2.0 - c[nq + 1]) - others + (nq >= 2 ? 2.0 * a * p * c[nq + 3] - p * p * (2.0 - c[nq + 2]) : 0.0);
-  const bool grows = most > 1e-10 * ww && a * a > 4.0 * b2;
-  const double before = rest > 1e-5 * ww && !grows ? sqrt(rest) : INFINITY;
-  scal[S_ALPHA] = a;
-  scal[S_NRM_BEFORE] = before;
+  s.a = c[nq - 1]; s.ww = c[nq]; s.gkk = c[nq + 1];
+  if (nq >= 2) { s.p = c[nq - 2]; s.gpp = c[nq + 2]; s.gkp = c[nq + 3]; }
+  const LzFirstPlan plan = lz_first_plan(s, next.tol);
+  const bool valid = !next.flags || (next.flags[0] == 0 && next.flags[1] != 0);
+  scal[S_ALPHA] = s.a;
+  scal[S_NRM_BEFORE] = plan.before;
   scal[S_REDO] = 0.0;
-  bool ok = b2 > 1e-3 * ww && sqrt(b2) >= 0.7072 * before && sqrt(b2) >= 1.001 * next.tol;
-  if (next.flags) ok = ok && next.flags[0] == 0 && next.flags[1] != 0;
-  scal[S_EST] = ok ? sqrt(b2) : 0.0;
+  scal[S_EST] = valid ? plan.est : 0.0;
 }
 
 __global__ __launch_bounds__(256) void lz_qtr_finish_kernel(const double* partials, int nblk, const double* scal,

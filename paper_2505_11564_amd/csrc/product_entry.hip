@@ -1,7 +1,9 @@
-// One matrix product as the engine launches it, and the launchers' choices, behind C entries: what the tests of single products call.
+// One matrix product as the engine launches it, the launchers' choices and those of an orthogonalisation, behind C entries: what the tests of
+// single products and of rules call.
 // Not part of the API.
 #include "gemm_params.h"
 #include "hf_internal.h"
+#include "lanczos.h"
 
 // ptr: A[3], B[3], C, C_lo, Cadd, At, Bt, Ct, Cadd_t, ws, counters (device memory; nullptr where absent).
 // num: M, N, K, lda, ldb, ldc, transA, transB, in_bf16, out_bf16, klimit, elements of ws, force_cfg, force_ks.
@@ -51,4 +53,12 @@ extern "C" __attribute__((visibility("default"))) int hf_internal_f32_plan(const
     ps[i].M = (int)num[4 * i]; ps[i].N = (int)num[4 * i + 1]; ps[i].K = (int)num[4 * i + 2]; ps[i].nterm = (int)num[4 * i + 3];
   }
   return hf::f32_plan(ps, n, 1, ws_elems, parts);
+}
+
+// What the first orthogonalisation pass decides: a, p, ww, others, sum, most, gkk, gpp, gkp of LzFirst and a tolerance; before and est into out.
+extern "C" __attribute__((visibility("default"))) void hf_internal_lz_first_plan(const double* in, double* out) {
+  const hf::LzFirst s = {in[0], in[1], in[2], in[3], in[4], in[5], in[6], in[7], in[8]};
+  const hf::LzFirstPlan plan = hf::lz_first_plan(s, in[9]);
+  out[0] = plan.before;
+  out[1] = plan.est;
 }
