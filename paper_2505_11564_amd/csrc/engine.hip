@@ -982,7 +982,7 @@ int hf_ctx::lanczos_update(float* r, double tol, double* alpha_k, double* beta_k
     const LzNext next = {spill ? spill : (float*)row, (bq && row) ? (bf16*)row : vdst, hvp_flags, tol};
     if (!bq) CK(lz_gs_first_pass((const float*)basis, basis_bf, ldq, r, n, k + 1, next, scal, cvec, partials, st));
     else CK(lz_gs_first_pass_bf16((const bf16*)basis, ldq, qp, q, r, n, k, next, scal, cvec, partials, st));
-    CK(lz_reorth_pass(basis, bq, bq ? nullptr : basis_bf, ldq, r, n, k + 1, 1, scal, cvec, partials, st));
+    CK(lz_gs_second_pass(basis, bq, bq ? nullptr : basis_bf, ldq, r, n, k + 1, scal, cvec, partials, st));
     CK(lz_scale(r, spill, row, bq, vdst, n, scal, S_BETA, tol, hvp_flags, st));
     next_vb = bf ? ((bq && row) ? (const bf16*)row : vdst) : nullptr;
   } else {

@@ -40,12 +40,11 @@ hipError_t lz3_update(const float* w, const float* q, float* qp, bf16* vb, int64
 // may be NULL), under the same test.  idx = S_BETA after a pass that wrote q_{k+1} itself: only what S_FIX asks for.
 hipError_t lz_scale(const float* src, float* dst, void* basis, int basis_bf16, bf16* vb, int64_t n, double* scal, int idx,
                     double tol, const int* flags, hipStream_t st);
-// One classical Gram-Schmidt pass of r against Q[0..nq); pass 1 is a no-op
-// unless pass 0 set the redo flag.
+// The second classical Gram-Schmidt pass, of r against Q[0..nq): a no-op unless the first set the redo flag.
 // copies (optional, fp32 basis only): bf16 copies of the rows, same row stride; the subtraction
 // reads rows 0 .. nq-3 from them.
-hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int pass,
-                          double* scal, double* c, double* partials, hipStream_t st);
+hipError_t lz_gs_second_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq,
+                             double* scal, double* c, double* partials, hipStream_t st);
 // What the first orthogonalisation pass decides from c = Q^T w and a few products more (w = H q_k, Q = q_0 .. q_k).
 struct LzFirst {
   double a, p;              // c_k = alpha_k, c_{k-1} (0 for k = 0)

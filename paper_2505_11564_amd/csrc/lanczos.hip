@@ -715,30 +715,29 @@ static void launch_sub_f32(const float* Q, const bf16* copies, int64_t ldq, floa
     hipLaunchKernelGGL(lz_sub_qc_kernel<float>, dim3(nb), dim3(256), sh, st, Q, ldq, r, n, nq, nslices, c, scal, pass, partials, next);
 }
 
-hipError_t lz_reorth_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, int pass,
-                          double* scal, double* c, double* partials, hipStream_t st) {
+hipError_t lz_gs_second_pass(const void* Q, int basis_bf16, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq,
+                             double* scal, double* c, double* partials, hipStream_t st) {
   if (nq <= 0) return hipSuccess;
   const int64_t nslices = (n + LZ_SLICE - 1) / LZ_SLICE;
   const int nb = (int)std::max<int64_t>(1, std::min<int64_t>(nslices, LZ_NBLK));
   const size_t sh1 = (size_t)4 * nq * sizeof(double), sh2 = (size_t)nq * sizeof(float);
   if (basis_bf16) {
-    hipLaunchKernelGGL(lz_qtr_kernel<bf16>, dim3(nb), dim3(256), sh1, st, (const bf16*)Q, ldq, r, n, nq, nslices, scal, pass, partials);
-    hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, pass, c);
-    hipLaunchKernelGGL(lz_sub_qc_kernel<bf16>, dim3(nb), dim3(256), sh2, st, (const bf16*)Q, ldq, r, n, nq, nslices, c, scal, pass, partials, LzNext{});
+    hipLaunchKernelGGL(lz_qtr_kernel<bf16>, dim3(nb), dim3(256), sh1, st, (const bf16*)Q, ldq, r, n, nq, nslices, scal, 1, partials);
+    hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, 1, c);
+    hipLaunchKernelGGL(lz_sub_qc_kernel<bf16>, dim3(nb), dim3(256), sh2, st, (const bf16*)Q, ldq, r, n, nq, nslices, c, scal, 1, partials, LzNext{});
   } else {
-    hipLaunchKernelGGL(lz_qtr_kernel<float>, dim3(nb), dim3(256), sh1, st, (const float*)Q, ldq, r, n, nq, nslices, scal, pass, partials);
-    hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, pass, c);
-    launch_sub_f32((const float*)Q, copies, ldq, r, n, nq, nslices, nb, c, scal, pass, partials, LzNext{}, st);
+    hipLaunchKernelGGL(lz_qtr_kernel<float>, dim3(nb), dim3(256), sh1, st, (const float*)Q, ldq, r, n, nq, nslices, scal, 1, partials);
+    hipLaunchKernelGGL(lz_qtr_finish_kernel, dim3(nq), dim3(256), 0, st, partials, nb, scal, 1, c);
+    launch_sub_f32((const float*)Q, copies, ldq, r, n, nq, nslices, nb, c, scal, 1, partials, LzNext{}, st);
   }
-  hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(256), 0, st, partials, nb, 3, pass, scal);
+  hipLaunchKernelGGL(lz_finish_kernel, dim3(1), dim3(256), 0, st, partials, nb, 3, 1, scal);
   return hipGetLastError();
 }
 
 // First Gram-Schmidt pass straight on w = H q_k against an fp32 basis that holds q_0 .. q_k
 // (nq = k + 1 rows): the coefficients of rows k and k - 1 are alpha_k and (up to rounding)
 // beta_{k-1}, so the pass subsumes the three-term subtraction, which saves its two passes over the
-// vectors.  Leaves alpha_k, ||r|| and the redo flag in scal as the three-term kernels followed by
-// lz_reorth_pass(pass 0) do.
+// vectors.  Leaves alpha_k, beta_k or ||r|| and the redo flag in scal.
 hipError_t lz_gs_first_pass(const float* Q, const bf16* copies, int64_t ldq, float* r, int64_t n, int nq, const LzNext& next, double* scal,
                             double* c, double* partials, hipStream_t st) {
   if (nq <= 0) return hipErrorInvalidValue;
