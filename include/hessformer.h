@@ -29,7 +29,12 @@
  *     its rows k and k-1 serve as q_k and q_{k-1}), max_m basis
  *     vectors, a bf16 copy of the direction when parameters are bf16, and with
  *     bf16 parameters and an fp32 basis a bf16 copy of every basis row, i.e.
- *     half the basis again) and frees it in hf_destroy.
+ *     half the basis again) and frees it in hf_destroy.  bf16 transformers
+ *     narrower than about 2048 also get buffers for the adjoints of up to three
+ *     layers more, 1 to 10 % of the whole, so that weight-gradient products of
+ *     several layers run as one launch; not where that would leave less than an
+ *     eighth of the GPU's memory, and hf_hessian_column gives them back where
+ *     its vector finds no room.  Results do not depend on them beyond rounding.
  *   - Work is enqueued on the HIP stream passed as `hip_stream` (a hipStream_t
  *     cast to void*, NULL = the default stream).  Calls that return host
  *     scalars synchronise that stream before returning.
@@ -157,7 +162,8 @@ int32_t hf_create(const hf_model_desc* desc, int32_t hip_device,
                   int32_t max_batch, int32_t max_m, hf_ctx** out);
 void hf_destroy(hf_ctx* ctx);
 int64_t hf_num_params(const hf_ctx* ctx);
-/* Bytes of device memory the context allocated. */
+/* Bytes of device memory the context holds (without the vector of
+ * hf_hessian_column, which its first call allocates). */
 int64_t hf_workspace_bytes(const hf_ctx* ctx);
 const char* hf_last_error(const hf_ctx* ctx);
 
@@ -268,7 +274,8 @@ int32_t hf_hvp_accumulate(hf_ctx* ctx, const void* params_dev, const void* input
 /* One column of the Hessian (section "Banded Hessians"): the product with the
  * vector that is 1 at `index` (0 <= index < n, canonical order) and 0
  * elsewhere.  column_dev: device, fp32[n], caller-owned, must not alias
- * params_dev.  Uses the context's auxiliary vector (see hf_hvp_accumulate).
+ * params_dev.  The first call allocates the vector (fp32[n], kept by the
+ * context; HF_ENOMEM where it does not fit).
  * Other arguments and errors as hf_hvp. */
 int32_t hf_hessian_column(hf_ctx* ctx, const void* params_dev, const void* inputs_dev,
                           const int32_t* labels_dev, int32_t batch, int32_t seq, int64_t index,

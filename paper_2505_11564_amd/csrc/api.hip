@@ -208,6 +208,7 @@ int32_t hf_create(const hf_model_desc* desc, int32_t hip_device, int32_t max_bat
 void hf_destroy(hf_ctx* ctx) {
   if (!ctx) return;
   if (ctx->arena) (void)hipFree(ctx->arena);
+  if (ctx->adj_arena) (void)hipFree(ctx->adj_arena);
   ctx->release_host();
   for (auto ev : ctx->ahead_ev) if (ev) (void)hipEventDestroy(ev);
   if (ctx->aux_vec) (void)hipFree(ctx->aux_vec);
@@ -215,7 +216,7 @@ void hf_destroy(hf_ctx* ctx) {
 }
 
 int64_t hf_num_params(const hf_ctx* ctx) { return ctx ? ctx->n : (int64_t)HF_EINVAL; }
-int64_t hf_workspace_bytes(const hf_ctx* ctx) { return ctx ? ctx->arena_bytes : (int64_t)HF_EINVAL; }
+int64_t hf_workspace_bytes(const hf_ctx* ctx) { return ctx ? ctx->arena_bytes + ctx->adj_bytes : (int64_t)HF_EINVAL; }
 
 const char* hf_last_error(const hf_ctx* ctx) {
   if (ctx) return ctx->err.c_str();

@@ -97,7 +97,10 @@ struct hf_ctx {
   void *dS = nullptr, *dS_t = nullptr;
   float *dx = nullptr, *dx_t = nullptr, *tmpd = nullptr, *tmpd_t = nullptr;
   void *dob = nullptr, *dob_t = nullptr, *dy = nullptr, *dy_t = nullptr;
-  std::vector<hf::AdjBuf> adj;  // layer l's are adj[l % adj.size()]
+  std::vector<hf::AdjBuf> adj;  // layer l's are adj[l % adj.size()]; those beyond the first lie in adj_arena
+  char* adj_arena = nullptr;
+  int64_t adj_bytes = 0;
+  void drop_waiting();  // back to one: weight-gradient products then never wait beyond their layer
   float* mlp_part = nullptr;  // MLP products in one kernel: the blocks' shares of H v and of the loss; nullptr = not that size
   double* mlp_part_loss = nullptr;
   void* xin = nullptr;  // MLP input in operand type (bf16 mode)
@@ -109,7 +112,7 @@ struct hf_ctx {
   int64_t gemm_ws_elems = 0;
   int* gemm_cnt = nullptr;   // fp32 parameters: arrival counters of those products (F32_COUNTERS, zero between launches)
   int gemm_cnt_clear = 0;    // the first product has cleared them
-  float* aux_vec = nullptr;  // n floats, allocated on first use (batch-loop partial result, unit vector)
+  float* aux_vec = nullptr;  // n floats, allocated on first use (the unit vector of a Hessian column)
   int dw_layers() const;  // layers whose weight-gradient products may wait for a common launch
   int clear_padding(int T, hipError_t* er, hipStream_t st);
   int pad_T = -1;  // number of tokens behind which those rows are zero
@@ -145,7 +148,7 @@ struct hf_ctx {
   float* prev_q() const;        // q_{k-1} (meaningful for k >= 1)
 
   int fail(int code, const std::string& m) { err = m; return code; }
-  int plan_and_alloc(bool may_wait = true);  // false: weight-gradient products never wait beyond their layer (least memory)
+  int plan_and_alloc();
   // out = seed_scale * H v, or out += seed_scale * H v when accumulate (the batch loop of Algorithm 1:
   // the weight of a batch multiplies the adjoint seeds, in which the backward sweep is linear)
   int hvp_enqueue(const void* params, const void* inputs, const int32_t* labels, int batch, int seq, const float* v,

@@ -138,8 +138,8 @@ void hf_ctx::release_host() {
   host_scal = host_hvp = nullptr;
 }
 
-int hf_ctx::plan_and_alloc(bool may_wait) {
-  Planner pl;
+int hf_ctx::plan_and_alloc() {
+  Planner pl, waiting;  // waiting: the adjoints' buffers beyond the first
   const int64_t e = bf ? 2 : 4;
   if (desc.arch == HF_ARCH_MLP) {
     const int64_t B = max_batch, Hd = desc.mlp_hidden, O = desc.mlp_out;
@@ -215,13 +215,14 @@ int hf_ctx::plan_and_alloc(bool may_wait) {
     pl.add(dS, SSa * e); pl.add(dS_t, SSa * e);
     pl.add(dx, T * D * 4); pl.add(dx_t, T * D * 4); pl.add(tmpd, T * D * 4); pl.add(tmpd_t, T * D * 4);
     pl.add(dob, T * D * e); pl.add(dob_t, T * D * e);
-    adj.assign(may_wait ? dw_layers() : 1, AdjBuf{});
+    adj.assign(dw_layers(), AdjBuf{});
     for (AdjBuf& a : adj) {
-      if (bf) { pl.add(a.x, Tp * D * e); pl.add(a.x_t, Tp * D * e); pl.add(a.m, Tp * D * e); pl.add(a.m_t, Tp * D * e); }
-      pl.add(a.qkv, Tp * W3 * e); pl.add(a.qkv_t, Tp * W3 * e);
-      pl.add(a.g, Tp * F * e); pl.add(a.g_t, Tp * F * e);
-      if (llama) { pl.add(a.up, Tp * F * e); pl.add(a.up_t, Tp * F * e); }
-      if (llama && Dkv != D && bf && !flash) { pl.add(a.v, Tp * Dkv * e); pl.add(a.v_t, Tp * Dkv * e); }
+      Planner& pa = &a == &adj[0] ? pl : waiting;
+      if (bf) { pa.add(a.x, Tp * D * e); pa.add(a.x_t, Tp * D * e); pa.add(a.m, Tp * D * e); pa.add(a.m_t, Tp * D * e); }
+      pa.add(a.qkv, Tp * W3 * e); pa.add(a.qkv_t, Tp * W3 * e);
+      pa.add(a.g, Tp * F * e); pa.add(a.g_t, Tp * F * e);
+      if (llama) { pa.add(a.up, Tp * F * e); pa.add(a.up_t, Tp * F * e); }
+      if (llama && Dkv != D && bf && !flash) { pa.add(a.v, Tp * Dkv * e); pa.add(a.v_t, Tp * Dkv * e); }
     }
     if (llama) { pl.add(dy, T * F * e); pl.add(dy_t, T * F * e); }
   }
@@ -250,10 +251,21 @@ int hf_ctx::plan_and_alloc(bool may_wait) {
   if (e1 != hipSuccess) {
     arena = nullptr;
     (void)hipGetLastError();
-    if (adj.size() > 1) return plan_and_alloc(false);
     return fail(HF_ENOMEM, "hipMalloc of " + std::to_string(arena_bytes) + " bytes failed: " + hipGetErrorString(e1));
   }
   for (auto& f : pl.fix) *f.first = arena + f.second;
+  // Those buffers only make products faster, so they do not take memory that a caller may be counting on: none where less than an
+  // eighth of the card would be left, and ensure_aux gives them up for a vector that finds no room.
+  if (adj.size() > 1) {
+    size_t left = 0, all = 0;
+    if (hipMemGetInfo(&left, &all) == hipSuccess && left >= (size_t)waiting.off + all / 8 && hipMalloc((void**)&adj_arena, (size_t)waiting.off) == hipSuccess) {
+      adj_bytes = waiting.off;
+      for (auto& f : waiting.fix) *f.first = adj_arena + f.second;
+    } else {
+      (void)hipGetLastError();
+      drop_waiting();
+    }
+  }
   e1 = take_host_slot(&host_scal, &host_slot);
   if (e1 != hipSuccess) {
     host_scal = nullptr;
@@ -430,7 +442,8 @@ static bool fills_rounds(int64_t tiles) { return tiles * 100 >= (tiles + 255) / 
 // bf16 weight-gradient products (A^T B over all tokens, few tiles each) wait until together they fill whole rounds of the CUs with
 // 256 x 256 tiles, which do a third more per us than the 128 x 128 ones that a layer's 108 tiles (width 768) would need to fill the
 // chip alone.  That takes the adjoints of as many layers as make a round and one, up to four; none where a layer's own fill rounds
-// (width 2048: 768).  The memory is a hundredth to a tenth of a context's.  Measured, a launch a layer / this (ms): GPT-2-small
+// (width 2048: 768) or no launch takes several of them (widths that are no multiples of eight).  The memory is a hundredth to a tenth of
+// a context's.  Measured, a launch a layer / this (ms): GPT-2-small
 // 4096 tokens 12.15 / 11.79 (735 tiles in three rounds with the head's, then 252 a round), 999 tokens 5.19 / 5.11; 1.3B 87.4 / 85.9 (W_o's 64
 // tiles next to W_qkv's 192); LLAMA-7B widths, two layers, 512 tokens 6.70 / 6.61.
 int hf_ctx::dw_layers() const {
@@ -438,7 +451,7 @@ int hf_ctx::dw_layers() const {
   const int D = desc.d_model, F = desc.d_ff, Dkv = D / desc.n_head * (desc.n_kv_head > 0 ? desc.n_kv_head : desc.n_head);
   const int64_t t = desc.arch == HF_ARCH_GPT ? gemm_tiles256(D, D) + gemm_tiles256(D, 3 * D) + 2 * gemm_tiles256(D, F)
                                              : 2 * gemm_tiles256(D, D) + 2 * gemm_tiles256(D, Dkv) + 3 * gemm_tiles256(D, F);
-  if (fills_rounds(t)) return 1;
+  if (fills_rounds(t) || D % 8 || F % 8 || Dkv % 8) return 1;
   return (int)std::min<int64_t>(desc.n_layer, std::min<int64_t>(4, (255 + t) / t + 1));
 }
 
@@ -474,9 +487,21 @@ int hf_ctx::clear_padding(int T, hipError_t* er, hipStream_t st) {
   return Tp;
 }
 
+void hf_ctx::drop_waiting() {
+  if (adj_arena) (void)hipFree(adj_arena);  // (waits for what is running)
+  adj_arena = nullptr;
+  adj_bytes = 0;
+  adj.resize(1);
+}
+
 int hf_ctx::ensure_aux() {
   if (aux_vec) return HF_OK;
   hipError_t e = hipMalloc((void**)&aux_vec, (size_t)n * 4);
+  if (e != hipSuccess && adj_arena) {
+    (void)hipGetLastError();
+    drop_waiting();
+    e = hipMalloc((void**)&aux_vec, (size_t)n * 4);
+  }
   if (e != hipSuccess) {
     aux_vec = nullptr;
     (void)hipGetLastError();
