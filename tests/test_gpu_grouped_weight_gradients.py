@@ -1,5 +1,6 @@
-"""The weight-gradient products of a layer in one launch, in each of its plans (128 x 128 and 256 x 256 tiles, k whole or cut
-into parts), writing and adding, through whole products against the float64 oracle.
+"""The weight-gradient products of one or two layers in one launch, in each of its plans (128 x 128 and 256 x 256 tiles, k whole or cut
+into parts; test_waiting_launches_cpu.py holds the models to them), writing and adding, through whole products against the float64 oracle.
+A ragged k, which these widths do not have, is in test_gpu_ragged_k.py.
 
 Tolerance 2e-2, the bound of bf16 products everywhere (operands rounded to 2^-9); a wrong or missing tile of a weight
 gradient is far above it."""
@@ -11,10 +12,10 @@ from oracle import models as om
 
 pytestmark = pytest.mark.gpu
 
-# model, batch: tiles and parts of k that the estimate chooses
+# model, batch: tiles and parts of k that the estimate chooses; the products contract over the next multiple of 64 tokens
 SHAPES = {
-    "128_whole": (si._gpt(1, 264, 3, 1048, 97, 77), 2),        # ragged tiles, ragged last slab, fewer slabs than a part needs
-    "128_cut": (si._gpt(2, 192, 3, 776, 97, 301), 4),          # parts of a ragged k; ragged tiles
+    "128_whole": (si._gpt(1, 264, 3, 1048, 97, 77), 2),        # ragged tiles, 154 tokens: fewer slabs than a part needs
+    "128_cut": (si._gpt(2, 192, 3, 776, 97, 301), 4),          # two layers, parts of 1204 tokens; ragged tiles
     "256_whole": (si._gpt(1, 1000, 10, 4040, 97, 67), 2),      # more than one round of 128 x 128 tiles
     "256_cut": (si._gpt(1, 512, 8, 3336, 97, 344), 16),        # long k, between 65 and 128 tiles of 256 x 256
 }

@@ -12,14 +12,17 @@ from oracle import models as om
 
 pytestmark = pytest.mark.gpu
 
-# model, batch: tiles of 256 x 256 a layer, buffers
+# model, batch: tiles of 256 x 256 a layer, buffers; what starts the launches (test_waiting_launches_cpu.py holds the comments to it)
 SHAPES = {
     "many_products": (si._gpt(6, 264, 3, 1048, 97, 77), 2),             # 32, 4: 16 products fill a launch; six layers go twice round the buffers
-    "inside_a_layer": (si._gpt(3, 1000, 10, 4040, 300, 67), 1),         # 192, 3: full rounds after the first product of a layer
-    "odd_head": (si._gpt(5, 512, 8, 2048, 4099, 40, tie=0), 2),         # 48, 4: untied head of odd width
-    "llama": (si._llama(5, 320, 5, 856, 515, 50), 2),                   # 40, 4: two layers a launch
-    "llama_grouped": (si._llama(4, 240, 10, 648, 130, 45, n_kv=2), 3),  # stored attention, shared key / value heads
-    "cut": (si._gpt(7, 128, 2, 512, 97, 301), 4),                       # k in parts, results cleared beforehand
+    "inside_a_layer": (si._gpt(3, 1000, 10, 4040, 300, 67), 1),         # 192, 3: one launch, of the head and all three layers, at the end
+    "odd_head": (si._gpt(5, 512, 8, 2048, 4099, 40, tie=0), 2),         # 48, 4: untied head of odd width; 16 products
+    "llama": (si._llama(5, 320, 5, 856, 515, 50), 2),                   # 40, 4: 16 products, two layers and a part
+    "llama_grouped": (si._llama(4, 240, 10, 648, 130, 45, n_kv=2), 3),  # stored attention, shared key / value heads; 16 products
+    "cut": (si._gpt(7, 128, 2, 512, 97, 301), 4),                       # k in parts, results cleared beforehand; 16 products, without the head
+    "three_buffers": (si._gpt(7, 264, 3, 8456, 97, 33), 2),             # 148, 3: each third layer the next one needs the buffers
+    "two_buffers": (si._gpt(5, 264, 3, 18440, 97, 33), 2),              # 300, 2: each second layer, for the head's buffer as well
+    "full_rounds": (si._gpt(5, 264, 3, 9736, 97, 33), 2),               # 168, 3: a full round after the first, later the second product of a layer
 }
 
 
