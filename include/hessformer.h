@@ -194,13 +194,19 @@ int32_t hf_lanczos_init(hf_ctx* ctx, const float* q0_dev, int32_t reorth,
 /* Iteration k of Algorithm 2: r = H q_k; r -= beta_{k-1} q_{k-1};
  * alpha_k = <q_k, r>; r -= alpha_k q_k; [full orthogonalisation of r against
  * q_0..q_k: classical Gram-Schmidt, a second pass when the first shrank ||r||
- * below 1/sqrt(2)]; beta_k = ||r||; q_{k+1} = r / beta_k unless beta_k < tol.
+ * below 1/sqrt(2), or when alpha_k > 2 beta_k and an older row than q_{k-1}
+ * had a coefficient above 1e-5 ||H q_k||, as the error of one pass would then
+ * grow from iteration to iteration]; beta_k = ||r||; q_{k+1} = r / beta_k unless
+ * beta_k < tol.
  * With full orthogonalisation the two subtractions are carried out by the
  * first Gram-Schmidt pass itself, applied to H q_k against q_0..q_k (alpha_k
  * is its k-th coefficient): the same r and alpha_k up to rounding.  The
  * coefficients are always formed against the stored rows; where the context
  * also holds bf16 copies of an fp32 basis, the subtraction reads rows 0..k-2
- * (whose coefficients are at rounding level) from the copies.  Without a
+ * (whose coefficients are at rounding level) from the copies.  Where beta_k
+ * follows from the coefficients and ||H q_k|| without loss of digits, and is
+ * safely above tol, that pass writes q_{k+1} itself and r is never stored (see
+ * hf_lanczos_get_vector).  Without a
  * basis r is never stored: alpha_k, <r', r'> and <q_k, q_k> (r' = H q_k -
  * beta_{k-1} q_{k-1}) come from one read-only pass, beta_k^2 = <r', r'> -
  * alpha_k^2 (2 - <q_k, q_k>) (formed explicitly when that difference loses its
@@ -220,8 +226,12 @@ int32_t hf_lanczos_step(hf_ctx* ctx, const void* params_dev,
 /* Number of iterations done since hf_lanczos_init. */
 int32_t hf_lanczos_iterations(const hf_ctx* ctx);
 
-/* Copies working vector `which` (0: q_k, 1: q_{k-1}, 2: r) or, for
- * which = 16 + j, stored basis vector j widened to fp32, to dst_dev[n]. */
+/* Copies working vector `which` (0: q_k, 1: q_{k-1}, 2: r of the last
+ * iteration) or, for which = 16 + j, stored basis vector j widened to fp32, to
+ * dst_dev[n].  r is the vector itself where the iteration stored it and
+ * beta_{k-1} q_k, the same up to rounding, where a step wrote q_k without it;
+ * without a basis it is H q_{k-1}, as r is never formed there.  After
+ * hf_lanczos_update what there is of r is in the caller's vector. */
 int32_t hf_lanczos_get_vector(hf_ctx* ctx, int32_t which, float* dst_dev,
                               void* hip_stream);
 
