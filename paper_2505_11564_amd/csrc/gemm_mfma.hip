@@ -650,7 +650,9 @@ static void choose_group_plan(const GemmP* ps, int n, int zeroed, int& cfg, int&
   // products of 12 / 6 layers (us; 256 x 256 in 1 or 2 parts, 128 x 128 in 1, 2 or 5; * chosen): width 768, 4096 tokens
   // 14806 14135 14006* 14357 14859; 999 tokens 6482 6560 6171* 6568 7173; 6 layers, 2048 tokens 4079 4020 3868* 4065 4305;
   // width 1024, 4096 tokens 8340* 8732 8727 8735 8974; width 256, 4096 tokens 3349 2963 2952 2665 2534* (4 parts chosen).
-  // (256 x 128 tiles were slower than the better of the two everywhere.)
+  // (256 x 128 tiles were slower than the better of the two everywhere.)  Of products of several layers, where 256 x 256 tiles are chosen: those / 128 x
+  // 128 for all, ms: GPT-2-small 4096 tokens 11.98 / 12.33, 999 5.07 / 5.11, LLAMA-7B widths 512 6.46 / 6.61.  The estimate has no term for what
+  // a round takes beside its slabs (15 to 30 us with the large tile), so where the two come close at few tokens it may name the slower one.
   cfg = 0;
   ks = 1;
   double best = 1e300;

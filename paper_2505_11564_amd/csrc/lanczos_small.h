@@ -86,7 +86,7 @@ __device__ __forceinline__ void lz_small_full_block(const LzSmall& u, float* w, 
       if (lane == 0) sm_c[j] = d;
     }
     __syncthreads();
-    if (pass == 0) {  // as lz_direct_scal_kernel
+    if (pass == 0) {  // as lz_first_plan, with what three terms would leave for beta_k
       alpha = sm_c[nq - 1];
       const double p = nq >= 2 ? sm_c[nq - 2] : 0.0, ww = sm_c[nq], rest = ww - alpha * alpha - p * p;
       bool grows = false;
