@@ -258,11 +258,16 @@ int hf_ctx::plan_and_alloc() {
   // eighth of the card would be left, and ensure_aux gives them up for a vector that finds no room.
   if (adj.size() > 1) {
     size_t left = 0, all = 0;
-    if (hipMemGetInfo(&left, &all) == hipSuccess && left >= (size_t)waiting.off + all / 8 && hipMalloc((void**)&adj_arena, (size_t)waiting.off) == hipSuccess) {
+    hipError_t e2 = hipMemGetInfo(&left, &all);
+    if (e2 == hipSuccess && left >= (size_t)waiting.off + all / 8) {
+      e2 = hipMalloc((void**)&adj_arena, (size_t)waiting.off);
+      if (e2 != hipSuccess) adj_arena = nullptr;
+    }
+    if (e2 != hipSuccess) (void)hipGetLastError();
+    if (adj_arena) {
       adj_bytes = waiting.off;
       for (auto& f : waiting.fix) *f.first = adj_arena + f.second;
     } else {
-      (void)hipGetLastError();
       drop_waiting();
     }
   }

@@ -16,7 +16,7 @@ typedef struct { unsigned x, y, z; } dim3;
 static const void* fn[1024]; static const char* fn_name[1024]; static int n_fn;
 static dim3 c_grid, c_block; static size_t c_shm; static void* c_st;
 static int last_error, fail_at; static char fail_name[64];
-static size_t used, limit = (size_t)1 << 60, total = (size_t)1 << 60;
+static size_t used, limit = (size_t)1 << 60, total = (size_t)1 << 60, free_said;
 static struct { void* p; size_t n; } held[4096]; static int n_held;
 static char* text; static size_t text_n, text_cap;
 static void say(const char* a, const char* b, size_t x, size_t y) {
@@ -31,6 +31,8 @@ const char* standin_log(void) { return text ? text : ""; }
 void standin_clear(void) { text_n = 0; if (text) text[0] = 0; }
 void standin_limit(size_t n) { limit = total = n; }
 size_t standin_used(void) { return used; }
+/* what is free by its own account, until 0 is said: a program beside this one may take it in between */
+void standin_free(size_t n) { free_said = n; }
 /* the nth launch from now of a kernel whose name has `name` in it fails */
 void standin_fail(const char* name, int nth) { strncpy(fail_name, name, 63); fail_at = nth; }
 
@@ -54,7 +56,7 @@ const char* hipGetErrorString(int e) { return "stand-in error"; }
 int hipSetDevice(int d) { return 0; }
 int hipGetDevice(int* d) { *d = 0; return 0; }
 int hipFuncSetAttribute(const void* f, int a, int v) { return 0; }
-int hipMemGetInfo(size_t* f, size_t* t) { *f = limit - used; *t = total; return 0; }
+int hipMemGetInfo(size_t* f, size_t* t) { *f = free_said ? free_said : limit - used; *t = total; return 0; }
 int hipMalloc(void** p, size_t n) {
   if (used + n > limit || n_held == 4096) { last_error = 2; say("refused", "-", n, used); return 2; }
   *p = aligned_alloc(256, 256);
@@ -85,7 +87,7 @@ import ctypes as C, json, sys
 S = C.CDLL(sys.argv[1], mode=C.RTLD_GLOBAL)  # ahead of the real runtime in the order of symbols
 L = C.CDLL(sys.argv[2])
 S.standin_log.restype = C.c_char_p
-S.standin_limit.argtypes = [C.c_size_t]
+S.standin_limit.argtypes = S.standin_free.argtypes = [C.c_size_t]
 S.standin_used.restype = C.c_size_t
 S.standin_fail.argtypes = [C.c_char_p, C.c_int]
 vp, i32 = C.c_void_p, C.c_int32

@@ -35,6 +35,19 @@ show([a, b, rc, L.hf_last_error(None).decode()])
     assert got[2] == -2 and "hipMalloc" in got[3]
 
 
+def test_room_that_is_gone_when_it_is_asked_for(tmp_path):
+    got = standin.run(tmp_path, SIZES + """
+L.hf_destroy(c)
+log()
+S.standin_free(1 << 40)
+rc, c = create(desc, 4)
+tried = [l[0] for l in log()]
+pending = S.hipGetLastError()
+show([rc, tried, pending, S.standin_used() == least == L.hf_workspace_bytes(c), hvp(c, 4, 77)])
+""", desc=standin.desc(MODEL))
+    assert got == [0, ["malloc", "refused"], 0, True, standin.ENQUEUED]
+
+
 def test_they_leave_an_eighth_of_the_card(tmp_path):
     got = standin.run(tmp_path, SIZES + """
 L.hf_destroy(c)
